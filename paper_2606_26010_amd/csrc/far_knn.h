@@ -156,6 +156,31 @@ __device__ inline void map_knn_query(const MapView& m, double qx, double qy, dou
   }
 }
 
+// The same search around a query in occupied voxel V (cnt points), whose
+// neighbours and their counts come from its row of the neighbour table
+// instead of a hash probe each.  The visiting order and bounds are those of
+// map_knn_query, so the results are the same.
+template <int K>
+__device__ inline void map_knn_row(const MapView& m, double qx, double qy, double qz, int32_t V,
+                                   int32_t cnt, const uint32_t* row, double r2, TopK<K>& top) {
+  top.init();
+  int64_t kx, ky, kz;
+  if (!voxel_index(qx, m.v, &kx) || !voxel_index(qy, m.v, &ky) ||
+      !voxel_index(qz, m.v, &kz))
+    return;
+  Query q = make_query(qx, qy, qz, r2);
+  scan_voxel_points<K>(m.vox_pts, V * m.nmax, cnt, q, r2, top);
+  for (int t = 1; t < 27; ++t) {
+    const int code = kNbrOrder[t];
+    const uint32_t e = row[nbr_dir(code)];
+    if (e == kNbrNone) continue;
+    const int ox = code / 9 - 1, oy = (code / 3) % 3 - 1, oz = code % 3 - 1;
+    if (voxel_lb2(qx, qy, qz, kx, ky, kz, ox, oy, oz, m.v) > fmin(r2, top.bound())) continue;
+    scan_voxel_points<K>(m.vox_pts, int32_t(e >> kNbrCountBits) * m.nmax,
+                         int32_t(e & ((1u << kNbrCountBits) - 1u)), q, r2, top);
+  }
+}
+
 // Neighbour offsets in visiting order (faces, edges, corners), packed five
 // bits per entry as code = (ox+1)*9 + (oy+1)*3 + (oz+1): ranks 1-12, 13-24,
 // 25-26 in three words.

@@ -60,6 +60,27 @@ inline unsigned blocks_for(int64_t n, int per = kT) {
   return unsigned(b < 1 ? 1 : b);
 }
 
+// A place in a list for every thread of the block that wants one: the list's
+// count is raised once per block.  Every thread of the block calls it.
+__device__ inline uint32_t block_reserve(bool want, uint32_t* count) {
+  __shared__ uint32_t wcnt[kT / 64];
+  __shared__ uint32_t base;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint64_t bal = __ballot(want);
+  if (lane == 0) wcnt[wave] = uint32_t(__popcll(bal));
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t total = 0;
+    for (int w = 0; w < kT / 64; ++w) total += wcnt[w];
+    base = total ? atomicAdd(count, total) : 0u;
+  }
+  __syncthreads();
+  uint32_t at = base + uint32_t(__popcll(bal & ((uint64_t(1) << lane) - 1)));
+  for (int w = 0; w < wave; ++w) at += wcnt[w];
+  __syncthreads();   // the words are free for a next call
+  return at;
+}
+
 // ---------------------------------------------------------------- keys
 // Voxel key of every point (Sec. III-A.2: the key is the voxel's 3-D index).
 // Non-finite points get the empty key (they sort last and are skipped);
@@ -297,89 +318,180 @@ __global__ __launch_bounds__(kT) void k_counts(int64_t n_seg, const int32_t* seg
 // Certificates an insert invalidates: those of the points within v of an
 // added point, all of which lie in the 27 voxels around the added point's
 // voxel.  Every voxel run that gained points marks itself and its existing
-// neighbours with this insert's generation (plain stores of one value).
+// neighbours with this insert's generation (plain stores of one value), one
+// thread per (run, cell).
 __global__ __launch_bounds__(kT) void k_cert_mark(int64_t n_seg, const int32_t* seg_vox,
                                                   const uint32_t* seg_changed,
                                                   const uint32_t* vox_nbr, uint32_t* mark,
                                                   uint32_t gen) {
-  const int64_t s = int64_t(blockIdx.x) * kT + threadIdx.x;
+  const int64_t t = int64_t(blockIdx.x) * kT + threadIdx.x;
+  const int64_t s = t / 27;
   if (s >= n_seg || !seg_changed[s]) return;
+  const int d = int(t - s * 27);
   const int32_t V = seg_vox[s];
-  mark[V] = gen;
-  for (int d = 0; d < 26; ++d) {
-    const uint32_t e = vox_nbr[int64_t(V) * 26 + d];
-    if (e != kNbrNone) mark[e >> kNbrCountBits] = gen;
+  if (d == 26) {
+    mark[V] = gen;
+    return;
   }
+  const uint32_t e = vox_nbr[int64_t(V) * 26 + d];
+  if (e != kNbrNone) mark[e >> kNbrCountBits] = gen;
 }
 
-// Certificate of every point of the marked voxels (all voxels when mark is
-// null), one lane per voxel slot: the kCertK + 1 nearest other points
-// within v by (d2, id) from the exact 27-voxel search (the point itself,
-// and so kCertK + 2 entries, included), the first kCertK listed with their
-// coordinates, rho half the distance of the next one (v/2 when there is
-// none), shrunk by 2^-20 and rounded down to float so that it never exceeds
-// the exact half distance.
-__global__ __launch_bounds__(kT) void k_cert_build(MapView m, int64_t n_vox,
-                                                   const uint32_t* mark, uint32_t gen,
-                                                   CertRow* cert) {
-  const int64_t pos = int64_t(blockIdx.x) * kT + threadIdx.x;
-  const int64_t V = pos / m.nmax;
-  if (V >= n_vox) return;
-  if (mark && mark[V] != gen) return;
-  if (pos - V * m.nmax >= m.vox_count[V]) return;
-  const float4 p = m.vox_pts[pos];
-  TopK<kCertK + 2> top;
-  map_knn_query<kCertK + 2>(m, double(p.x), double(p.y), double(p.z), m.v * m.v, top);
-  CertRow r;
-  r.x = p.x;
-  r.y = p.y;
-  r.z = p.z;
-  int n = 0;
-  double next = -1.0;
+// The vox_pts slots of the marked voxels' points (of all voxels when mark is
+// null), appended to list in voxel order within a block of voxels: the
+// certificates below then run one point per lane.  (One lane per slot left
+// 84 % of the lanes of a wave idle on a surface map of 3.3 points per voxel of
+// 20 slots.)
+__global__ __launch_bounds__(kT) void k_cert_list(int64_t n_vox, int32_t nmax,
+                                                  const int32_t* vox_count, const uint32_t* mark,
+                                                  uint32_t gen, uint32_t* list, uint32_t* count) {
+  __shared__ uint32_t wsum[kT / 64];
+  __shared__ uint32_t base;
+  const int64_t V = int64_t(blockIdx.x) * kT + threadIdx.x;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint32_t c = V < n_vox && (!mark || mark[V] == gen) ? uint32_t(vox_count[V]) : 0u;
+  uint32_t x = c;
 #pragma unroll
-  for (int t = 0; t < kCertK + 2; ++t) {
-    if (top.pos[t] < 0 || top.pos[t] == int32_t(pos)) continue;
-    if (n < kCertK) {
-      const float4 u = m.vox_pts[top.pos[t]];
-      r.nbr[n++] = make_float4(u.x, u.y, u.z, __int_as_float(top.pos[t]));
-    } else if (next < 0.0) {
-      next = top.d[t];
-    }
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t u = uint32_t(__shfl_up(int(x), d));
+    if (lane >= d) x += u;
   }
-  for (int t = n; t < kCertK; ++t) r.nbr[t] = make_float4(0.0f, 0.0f, 0.0f, __int_as_float(-1));
-  const double half = 0.5 * (next >= 0.0 ? sqrt(next) : m.v) * (1.0 - 0x1p-20);
-  r.rho = __double2float_rd(half);
-  cert[pos] = r;
+  if (lane == 63) wsum[wave] = x;
+  __syncthreads();
+  uint32_t at = x - c, total = 0;
+#pragma unroll
+  for (int w = 0; w < kT / 64; ++w) {
+    at += w < wave ? wsum[w] : 0u;
+    total += wsum[w];
+  }
+  if (total == 0) return;
+  if (threadIdx.x == 0) base = atomicAdd(count, total);
+  __syncthreads();
+  at += base;
+  for (uint32_t q = 0; q < c; ++q) list[at + q] = uint32_t(V * nmax + q);
 }
 
-// Neighbour table upkeep after an insert, one thread per touched voxel run:
-// the voxel's entry (index and new count) is written into the row of every
-// existing neighbour, and a new voxel's own row is filled from the hash.  An
-// entry is written only by the thread of the voxel it names or of the voxel
-// whose row it is, with the same (final) value, so the writes need no
-// ordering.
+// Certificate of every listed point, one lane each: the kCertK + 1 nearest
+// other points within v by (d2, id) from the exact 27-voxel search (the point
+// itself, and so kCertK + 2 entries, included), the first kCertK listed with
+// their coordinates, rho half the distance of the next one (v/2 when there is
+// none), shrunk by 2^-20 and rounded down to float so that it never exceeds
+// the exact half distance.  With cov given, the points with ids from id0 on
+// (those an insert adds, all of them listed) get their covariance from the
+// k <= K nearest of the same search, into the record by id and by slot: the
+// search they would otherwise repeat.
+//
+// Bound by the latency of the gathers and by FP64 ranking.  The neighbours
+// come from the voxel's row of the neighbour table (in LDS, read in one go)
+// instead of a hash probe each.  On average over two inserts of 500k points
+// into an emptied map: 782 us for one lane per slot with probes and 188 us for the separate
+// covariance search, now 308 us in all; at 15k points 97 + 89 -> 101 us.
+constexpr int kRowPad = 27;   // words per lane of the row copy (26 and a pad)
+
+template <int K>
+__global__ __launch_bounds__(kT) void k_cert_build(MapView m, const uint32_t* list,
+                                                   const uint32_t* count, CertRow* cert,
+                                                   float4* cov, float4* vox_cov, int64_t id0,
+                                                   int32_t k, int32_t reg) {
+  static_assert(K >= kCertK + 2, "a certificate needs kCertK + 2 entries");
+  __shared__ uint32_t rows[kT * kRowPad];
+  uint32_t* row = rows + threadIdx.x * kRowPad;
+  const uint32_t n = *count;
+  for (uint32_t t = blockIdx.x * kT + threadIdx.x; t < n; t += gridDim.x * kT) {
+    const uint32_t pos = list[t];
+    const int32_t V = int32_t(pos / uint32_t(m.nmax));
+    const float4 p = m.vox_pts[pos];
+    {
+      const uint2* r = reinterpret_cast<const uint2*>(m.vox_nbr + int64_t(V) * 26);
+      uint2 e[13];
+#pragma unroll
+      for (int u = 0; u < 13; ++u) e[u] = r[u];
+#pragma unroll
+      for (int u = 0; u < 13; ++u) {
+        row[2 * u] = e[u].x;
+        row[2 * u + 1] = e[u].y;
+      }
+    }
+    const int32_t own = m.vox_count[V];
+    TopK<K> top;
+    map_knn_row<K>(m, double(p.x), double(p.y), double(p.z), V, own, row, m.v * m.v, top);
+    CertRow r;
+    r.x = p.x;
+    r.y = p.y;
+    r.z = p.z;
+    int c = 0;
+    double next = -1.0;
+#pragma unroll
+    for (int u = 0; u < kCertK + 2; ++u) {
+      if (top.pos[u] < 0 || top.pos[u] == int32_t(pos)) continue;
+      if (c < kCertK) {
+        const float4 q = m.vox_pts[top.pos[u]];
+        r.nbr[c++] = make_float4(q.x, q.y, q.z, __int_as_float(top.pos[u]));
+      } else if (next < 0.0) {
+        next = top.d[u];
+      }
+    }
+    for (int u = c; u < kCertK; ++u)
+      r.nbr[u] = make_float4(0.0f, 0.0f, 0.0f, __int_as_float(-1));
+    const double half = 0.5 * (next >= 0.0 ? sqrt(next) : m.v) * (1.0 - 0x1p-20);
+    r.rho = __double2float_rd(half);
+    cert[pos] = r;
+    const int32_t id = __float_as_int(p.w);
+    if (!cov || id < id0) continue;
+    double c6[6] = {0, 0, 0, 0, 0, 0};
+    const bool ok = top.found() >= k;
+    if (ok) regularised_cov<K>(top, k, [&](int32_t at) { return m.vox_pts[at]; }, c6, reg);
+    const float4 a = make_float4(float(c6[0]), float(c6[1]), float(c6[2]), float(c6[3]));
+    const float4 b = make_float4(float(c6[4]), float(c6[5]), ok ? 1.0f : 0.0f, 0.0f);
+    cov[2 * int64_t(id)] = a;
+    cov[2 * int64_t(id) + 1] = b;
+    vox_cov[2 * int64_t(pos)] = a;
+    vox_cov[2 * int64_t(pos) + 1] = b;
+  }
+}
+
+// The upkeep kernels below walk the 26 neighbours of a voxel with one thread
+// per (voxel, direction): each neighbour is a chain of dependent loads (a hash
+// probe, a row, a store), so one thread taking the 26 in turn was bound by
+// that latency with most of the chip idle (an insert of 15k points touches
+// about 4k voxels: 60 waves).  Measured on average over two inserts of 500k
+// points each into an emptied map (0.2M voxels): table 116 -> 38 us, ghost claim 361 -> 132 us, ghost
+// rows 181 -> 47 us, ghost update 110 -> 55 us; at 15k points 28 -> 5,
+// 58 -> 10, 26 -> 5 and 27 -> 6 us.
+__device__ inline int dir_code(int dir) { return dir < 13 ? dir : dir + 1; }
+
+// Neighbour table upkeep after an insert: the entry (index and new count) of
+// every touched voxel is written into the row of every existing neighbour,
+// and a new voxel's own row is filled from the hash.  The neighbours of a
+// voxel that was there before are in its row already; those that are new put
+// their entry there and take its entry from the hash themselves, so only new
+// voxels probe.  An entry is written only by the threads of the voxel it
+// names and of the voxel whose row it is, with the same (final) value, so
+// the writes need no ordering.
 __global__ __launch_bounds__(kT) void k_nbr_update(MapView m, int64_t n_seg, const int32_t* seg_vox,
                                                    const uint32_t* is_new, const uint64_t* vox_key,
                                                    const int32_t* vox_count, uint32_t* vox_nbr) {
-  const int64_t s = int64_t(blockIdx.x) * kT + threadIdx.x;
+  const int64_t t = int64_t(blockIdx.x) * kT + threadIdx.x;
+  const int64_t s = t / 26;
   if (s >= n_seg) return;
+  const int dir = int(t - s * 26), code = dir_code(dir);
   const int32_t V = seg_vox[s];
   const bool fresh = is_new[s] != 0;
-  const uint64_t key = vox_key[V];
-  const int64_t kx = key_x(key), ky = key_y(key), kz = key_z(key);
-  const uint32_t eV = (uint32_t(V) << kNbrCountBits) | uint32_t(vox_count[V]);
-  for (int code = 0; code < 27; ++code) {
-    if (code == 13) continue;
+  int32_t N = -1;
+  if (fresh) {
+    const uint64_t key = vox_key[V];
     int32_t cN;
-    const int32_t N = map_find(m, kx + code / 9 - 1, ky + (code / 3) % 3 - 1, kz + code % 3 - 1, &cN);
-    const int dir = nbr_dir(code), back = nbr_dir(26 - code);
-    if (N >= 0) {
-      vox_nbr[int64_t(N) * 26 + back] = eV;
-      if (fresh) vox_nbr[int64_t(V) * 26 + dir] = (uint32_t(N) << kNbrCountBits) | uint32_t(cN);
-    } else if (fresh) {
-      vox_nbr[int64_t(V) * 26 + dir] = kNbrNone;
-    }
+    N = map_find(m, key_x(key) + code / 9 - 1, key_y(key) + (code / 3) % 3 - 1,
+                 key_z(key) + code % 3 - 1, &cN);
+    vox_nbr[int64_t(V) * 26 + dir] =
+        N >= 0 ? (uint32_t(N) << kNbrCountBits) | uint32_t(cN) : kNbrNone;
+  } else {
+    const uint32_t e = vox_nbr[int64_t(V) * 26 + dir];
+    if (e != kNbrNone) N = int32_t(e >> kNbrCountBits);
   }
+  if (N >= 0)
+    vox_nbr[int64_t(N) * 26 + nbr_dir(26 - code)] =
+        (uint32_t(V) << kNbrCountBits) | uint32_t(vox_count[V]);
 }
 
 // ---------------------------------------------------------------- ghosts
@@ -394,80 +506,87 @@ __global__ __launch_bounds__(kT) void k_nbr_update(MapView m, int64_t n_seg, con
 
 // Claims the empty neighbours of each new voxel run as ghosts (index from
 // gcount; beyond ghost_cap a ghost gets no row and the host switches the
-// ghosts off).
+// ghosts off).  The voxel's neighbour row says which are empty.
 __global__ __launch_bounds__(kT) void k_ghost_claim(MapView m, int64_t n_seg,
                                                     const int32_t* seg_vox,
                                                     const uint32_t* is_new,
                                                     const uint64_t* vox_key, Slot* gslots,
                                                     uint64_t* gkey, uint32_t* gcount,
                                                     int64_t ghost_cap) {
-  const int64_t s = int64_t(blockIdx.x) * kT + threadIdx.x;
-  if (s >= n_seg || (is_new && !is_new[s])) return;
-  const uint64_t key = vox_key[seg_vox[s]];
-  const int64_t kx = key_x(key), ky = key_y(key), kz = key_z(key);
-  for (int code = 0; code < 27; ++code) {
-    if (code == 13) continue;
-    const int64_t nx = kx + code / 9 - 1, ny = ky + (code / 3) % 3 - 1, nz = kz + code % 3 - 1;
-    if (!key_ok(nx) || !key_ok(ny) || !key_ok(nz)) continue;
-    int32_t c;
-    if (map_find(m, nx, ny, nz, &c) >= 0) continue;
-    const uint64_t nk = pack_key(nx, ny, nz);
-    uint32_t h = voxel_hash(nx, ny, nz, m.glog2);
-    for (uint32_t probe = 0; probe <= m.gmask; ++probe) {
-      const unsigned long long old = atomicCAS(
-          reinterpret_cast<unsigned long long*>(&gslots[h].key), (unsigned long long)kEmptyKey,
-          (unsigned long long)nk);
-      if (old == kEmptyKey) {
-        const uint32_t g = atomicAdd(gcount, 1u);
-        gslots[h].vox = int64_t(g) < ghost_cap ? int32_t(g) : -1;
-        if (int64_t(g) < ghost_cap) gkey[g] = nk;
-        break;
+  const int64_t t = int64_t(blockIdx.x) * kT + threadIdx.x;
+  const int64_t s = t / 26;
+  bool won = false;
+  uint32_t h = 0;
+  uint64_t nk = 0;
+  if (s < n_seg && (!is_new || is_new[s])) {
+    const int dir = int(t - s * 26), code = dir_code(dir);
+    const int32_t V = seg_vox[s];
+    const uint64_t key = vox_key[V];
+    const int64_t nx = key_x(key) + code / 9 - 1, ny = key_y(key) + (code / 3) % 3 - 1,
+                  nz = key_z(key) + code % 3 - 1;
+    if (m.vox_nbr[int64_t(V) * 26 + dir] == kNbrNone && key_ok(nx) && key_ok(ny) && key_ok(nz)) {
+      nk = pack_key(nx, ny, nz);
+      h = voxel_hash(nx, ny, nz, m.glog2);
+      for (uint32_t probe = 0; probe <= m.gmask; ++probe) {
+        // (most neighbours were claimed by another voxel's thread: look first)
+        unsigned long long old =
+            *reinterpret_cast<const volatile unsigned long long*>(&gslots[h].key);
+        if (old == kEmptyKey)
+          old = atomicCAS(reinterpret_cast<unsigned long long*>(&gslots[h].key),
+                          (unsigned long long)kEmptyKey, (unsigned long long)nk);
+        won = old == kEmptyKey;
+        if (won || old == nk) break;
+        h = (h + 1) & m.gmask;
       }
-      if (old == nk) break;
-      h = (h + 1) & m.gmask;
     }
+  }
+  // one atomic per block on the shared count (they serialise, 6 to 7 ns each)
+  const uint32_t g = block_reserve(won, gcount);
+  if (won) {
+    gslots[h].vox = int64_t(g) < ghost_cap ? int32_t(g) : -1;
+    if (int64_t(g) < ghost_cap) gkey[g] = nk;
   }
 }
 
-// Full neighbour rows of the ghosts with index in [g0, min(*gcount, cap)).
+// Neighbour rows of the ghosts with index in [g0, min(*gcount, cap)): a grid
+// of any size takes the (ghost, direction) entries in turn.
 __global__ __launch_bounds__(kT) void k_ghost_fill(MapView m, const uint64_t* gkey,
                                                    const uint32_t* gcount, int64_t g0,
-                                                   int64_t n, int64_t ghost_cap,
-                                                   uint32_t* gnbr) {
-  const int64_t g = g0 + int64_t(blockIdx.x) * kT + threadIdx.x;
-  const int64_t end = int64_t(*gcount) < ghost_cap ? int64_t(*gcount) : ghost_cap;
-  if (g >= end || g >= g0 + n) return;
-  const uint64_t key = gkey[g];
-  const int64_t kx = key_x(key), ky = key_y(key), kz = key_z(key);
-  for (int code = 0; code < 27; ++code) {
-    if (code == 13) continue;
+                                                   int64_t ghost_cap, uint32_t* gnbr) {
+  const int64_t end = (int64_t(*gcount) < ghost_cap ? int64_t(*gcount) : ghost_cap) * 26;
+  for (int64_t t = g0 * 26 + int64_t(blockIdx.x) * kT + threadIdx.x; t < end;
+       t += int64_t(gridDim.x) * kT) {
+    const int64_t g = t / 26;
+    const int code = dir_code(int(t - g * 26));
+    const uint64_t key = gkey[g];
     int32_t c;
-    const int32_t N = map_find(m, kx + code / 9 - 1, ky + (code / 3) % 3 - 1,
-                               kz + code % 3 - 1, &c);
-    gnbr[g * 26 + nbr_dir(code)] =
-        N >= 0 ? (uint32_t(N) << kNbrCountBits) | uint32_t(c) : kNbrNone;
+    const int32_t N = map_find(m, key_x(key) + code / 9 - 1, key_y(key) + (code / 3) % 3 - 1,
+                               key_z(key) + code % 3 - 1, &c);
+    gnbr[t] = N >= 0 ? (uint32_t(N) << kNbrCountBits) | uint32_t(c) : kNbrNone;
   }
 }
 
 // The entry of every voxel run whose count changed, written into the rows
-// of the ghosts around it (one writer per entry, as in k_nbr_update).
+// of the ghosts around it (one writer per entry, as in k_nbr_update): the
+// empty neighbours of its own row (a ghost under an occupied voxel is never
+// read).
 __global__ __launch_bounds__(kT) void k_ghost_update(MapView m, int64_t n_seg,
                                                      const int32_t* seg_vox,
                                                      const uint32_t* seg_changed,
                                                      const uint64_t* vox_key,
                                                      const int32_t* vox_count, uint32_t* gnbr) {
-  const int64_t s = int64_t(blockIdx.x) * kT + threadIdx.x;
+  const int64_t t = int64_t(blockIdx.x) * kT + threadIdx.x;
+  const int64_t s = t / 26;
   if (s >= n_seg || !seg_changed[s]) return;
+  const int dir = int(t - s * 26), code = dir_code(dir);
   const int32_t V = seg_vox[s];
+  if (m.vox_nbr[int64_t(V) * 26 + dir] != kNbrNone) return;
   const uint64_t key = vox_key[V];
-  const int64_t kx = key_x(key), ky = key_y(key), kz = key_z(key);
-  const uint32_t eV = (uint32_t(V) << kNbrCountBits) | uint32_t(vox_count[V]);
-  for (int code = 0; code < 27; ++code) {
-    if (code == 13) continue;
-    const int32_t g = ghost_find(m, kx + code / 9 - 1, ky + (code / 3) % 3 - 1,
-                                 kz + code % 3 - 1);
-    if (g >= 0) gnbr[int64_t(g) * 26 + nbr_dir(26 - code)] = eV;
-  }
+  const int32_t g = ghost_find(m, key_x(key) + code / 9 - 1, key_y(key) + (code / 3) % 3 - 1,
+                               key_z(key) + code % 3 - 1);
+  if (g >= 0)
+    gnbr[int64_t(g) * 26 + nbr_dir(26 - code)] =
+        (uint32_t(V) << kNbrCountBits) | uint32_t(vox_count[V]);
 }
 
 // ---------------------------------------------------------------- ASMD
@@ -479,32 +598,33 @@ __global__ __launch_bounds__(kT) void k_asmd_count(const float* xs, const float*
                                                    uint32_t set_mask, int set_log2,
                                                    uint32_t* counters) {
   const int64_t i = int64_t(blockIdx.x) * kT + threadIdx.x;
-  if (i >= n) return;
-  const double sx = xs[i], sy = xs[n + i], sz = xs[2 * n + i];
-  const double mx = xm[i], my = xm[n + i], mz = xm[2 * n + i];
-  if (!(isfinite(sx) && isfinite(sy) && isfinite(sz) && isfinite(mx) && isfinite(my) &&
-        isfinite(mz)))
-    return;
-  if ((sx * sx + sy * sy) + sz * sz > rn2) return;
-  int64_t kx, ky, kz;
-  if (!voxel_index(mx, v, &kx) || !voxel_index(my, v, &ky) || !voxel_index(mz, v, &kz)) {
-    atomicAdd(&counters[2], 1u);
-    return;
-  }
-  atomicAdd(&counters[0], 1u);
-  const uint64_t key = pack_key(kx, ky, kz);
-  uint32_t h = voxel_hash(kx, ky, kz, set_log2);
-  for (uint32_t probe = 0; probe <= set_mask; ++probe) {
-    const unsigned long long old = atomicCAS(reinterpret_cast<unsigned long long*>(&set[h]),
-                                             (unsigned long long)kEmptyKey,
-                                             (unsigned long long)key);
-    if (old == kEmptyKey) {
-      atomicAdd(&counters[1], 1u);
-      return;
+  bool near = false, first = false;
+  if (i < n) {
+    const double sx = xs[i], sy = xs[n + i], sz = xs[2 * n + i];
+    const double mx = xm[i], my = xm[n + i], mz = xm[2 * n + i];
+    near = isfinite(sx) && isfinite(sy) && isfinite(sz) && isfinite(mx) && isfinite(my) &&
+           isfinite(mz) && (sx * sx + sy * sy) + sz * sz <= rn2;
+    if (near) {
+      int64_t kx, ky, kz;
+      if (!voxel_index(mx, v, &kx) || !voxel_index(my, v, &ky) || !voxel_index(mz, v, &kz)) {
+        atomicAdd(&counters[2], 1u);
+        near = false;
+      } else {
+        const uint64_t key = pack_key(kx, ky, kz);
+        uint32_t h = voxel_hash(kx, ky, kz, set_log2);
+        for (uint32_t probe = 0; probe <= set_mask; ++probe) {
+          const unsigned long long old = atomicCAS(reinterpret_cast<unsigned long long*>(&set[h]),
+                                                   (unsigned long long)kEmptyKey,
+                                                   (unsigned long long)key);
+          first = old == kEmptyKey;
+          if (first || old == key) break;
+          h = (h + 1) & set_mask;
+        }
+      }
     }
-    if (old == key) return;
-    h = (h + 1) & set_mask;
   }
+  (void)block_reserve(near, &counters[0]);   // one add per block and count
+  (void)block_reserve(first, &counters[1]);
 }
 
 // cap_i = clamp(floor(mean (1 - r_i / r_max) + 0.5), k, nmax), FP64 in this
@@ -1214,18 +1334,43 @@ __global__ __launch_bounds__(kT, kCovMinWaves) void k_grid_cov(GridView g, int32
   valid[i] = ok ? 1 : 0;
 }
 
+// Probe lengths of the held keys: summed per block before the two atomics (one
+// pair per held slot, all on one address, took 200 us for 0.2M voxels in a
+// table of 1M slots; 13 us now).
 __global__ __launch_bounds__(kT) void k_probe_stats(const Slot* slots, int64_t n_slots,
                                                     uint32_t slot_mask, int log2_slots,
                                                     unsigned long long* sum,
                                                     uint32_t* maxp) {
-  int64_t s = int64_t(blockIdx.x) * kT + threadIdx.x;
-  if (s >= n_slots) return;
-  uint64_t key = slots[s].key;
-  if (key == kEmptyKey) return;
-  uint32_t h = voxel_hash(key_x(key), key_y(key), key_z(key), log2_slots);
-  uint32_t len = ((uint32_t(s) - h) & slot_mask) + 1;
-  atomicAdd(sum, (unsigned long long)len);
-  atomicMax(maxp, len);
+  uint32_t total = 0, longest = 0;
+  for (int64_t s = int64_t(blockIdx.x) * kT + threadIdx.x; s < n_slots;
+       s += int64_t(gridDim.x) * kT) {
+    const uint64_t key = slots[s].key;
+    if (key == kEmptyKey) continue;
+    const uint32_t h = voxel_hash(key_x(key), key_y(key), key_z(key), log2_slots);
+    const uint32_t len = ((uint32_t(s) - h) & slot_mask) + 1;
+    total += len;
+    longest = max(longest, len);
+  }
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) {
+    total += uint32_t(__shfl_xor(int(total), d));
+    longest = max(longest, uint32_t(__shfl_xor(int(longest), d)));
+  }
+  __shared__ uint32_t s_t[kT / 64], s_l[kT / 64];
+  if ((threadIdx.x & 63) == 0) {
+    s_t[threadIdx.x >> 6] = total;
+    s_l[threadIdx.x >> 6] = longest;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  unsigned long long t = 0;
+  for (int w = 0; w < kT / 64; ++w) {
+    t += s_t[w];
+    longest = max(longest, s_l[w]);
+  }
+  if (!t) return;
+  atomicAdd(sum, t);
+  atomicMax(maxp, longest);
 }
 
 __global__ __launch_bounds__(kT) void k_export(const float4* cov, const float* pt_xyz,
@@ -1417,6 +1562,42 @@ far_status_t fine_build(far_map_s* m, hipStream_t st) {
   return FAR_OK;
 }
 
+// Certificates of the points of the voxels marked with gen (of all n_vox
+// voxels when mark is null; at most n_pts points), and with cov given the
+// covariances of the points with ids from id0 on: in the same search when
+// its list is long enough for the map's k_cov (up to 10), else by a search
+// of their own.
+far_status_t certs_build(far_map_s* m, int64_t n_vox, int64_t n_pts, const uint32_t* mark,
+                         uint32_t gen, float4* cov, int64_t id0, int64_t id1, hipStream_t st,
+                         Scratch& scr) {
+  if (n_vox == 0 || n_pts == 0) return FAR_OK;
+  uint32_t *list, *count;
+  FAR_TRY(scr.get(&list, size_t(n_pts)));
+  FAR_TRY(scr.get(&count, 1));
+  FAR_HIP(hipMemsetAsync(count, 0, sizeof(uint32_t), st));
+  k_cert_list<<<blocks_for(n_vox), kT, 0, st>>>(n_vox, m->p.max_pts_per_voxel, m->vox_count,
+                                                mark, gen, list, count);
+  FAR_HIP(hipGetLastError());
+  const int32_t k = m->p.k_cov;
+  const unsigned nb = unsigned(std::min<int64_t>(blocks_for(n_pts), 16 * device_cu_count()));
+  if (k <= kCertK + 2)
+    k_cert_build<kCertK + 2><<<nb, kT, 0, st>>>(m->view(), list, count, m->cert, cov, m->vox_cov,
+                                                id0, k, g_cov_reg);
+  else if (k <= 10)
+    k_cert_build<10><<<nb, kT, 0, st>>>(m->view(), list, count, m->cert, cov, m->vox_cov, id0, k,
+                                        g_cov_reg);
+  else
+    k_cert_build<kCertK + 2><<<nb, kT, 0, st>>>(m->view(), list, count, m->cert, nullptr, nullptr,
+                                                id0, k, g_cov_reg);
+  FAR_HIP(hipGetLastError());
+  if (cov && k > 10 && id1 > id0) {
+    FAR_TRY(map_covariances(m->view(), cov, id0, id1, k, st));
+    k_vox_cov<<<blocks_for(id1 - id0), kT, 0, st>>>(cov, m->pt_loc, id0, id1, m->vox_cov);
+    FAR_HIP(hipGetLastError());
+  }
+  return FAR_OK;
+}
+
 // No ghosts (the voxel structures were cleared): an empty table, ghosts on.
 far_status_t ghosts_reset(far_map_s* m, hipStream_t st) {
   FAR_HIP(hipMemsetAsync(m->gslots, 0xFF, size_t(m->gslots_n) * sizeof(Slot), st));
@@ -1437,17 +1618,18 @@ far_status_t ghosts_update(far_map_s* m, int64_t n_seg, const int32_t* seg_vox,
                            hipStream_t st) {
   if (!m->ghost_ok || n_seg == 0) return FAR_OK;
   const MapView mv = m->view();
-  k_ghost_claim<<<blocks_for(n_seg), kT, 0, st>>>(mv, n_seg, seg_vox, is_new, m->vox_key,
+  k_ghost_claim<<<blocks_for(n_seg * 26), kT, 0, st>>>(mv, n_seg, seg_vox, is_new, m->vox_key,
                                                   m->gslots, m->gkey, m->gcount, m->ghost_cap);
   FAR_HIP(hipGetLastError());
   const int64_t fresh = 26 * n_new;   // at most this many new ghosts
   if (fresh > 0) {
-    k_ghost_fill<<<blocks_for(fresh), kT, 0, st>>>(mv, m->gkey, m->gcount, m->n_ghosts, fresh,
-                                                   m->ghost_cap, m->gnbr);
+    // (about two ghosts per new voxel; the kernel reads how many there are)
+    const unsigned nb = unsigned(std::min<int64_t>(blocks_for(fresh), 16 * device_cu_count()));
+    k_ghost_fill<<<nb, kT, 0, st>>>(mv, m->gkey, m->gcount, m->n_ghosts, m->ghost_cap, m->gnbr);
     FAR_HIP(hipGetLastError());
   }
   if (seg_changed) {
-    k_ghost_update<<<blocks_for(n_seg), kT, 0, st>>>(mv, n_seg, seg_vox, seg_changed,
+    k_ghost_update<<<blocks_for(n_seg * 26), kT, 0, st>>>(mv, n_seg, seg_vox, seg_changed,
                                                      m->vox_key, m->vox_count, m->gnbr);
     FAR_HIP(hipGetLastError());
   }
@@ -1665,7 +1847,7 @@ far_status_t far_map_insert(far_map_t m, const float* xyz, int64_t n, const int3
                                              n_commit, m->vox_count, m->vox_slot,
                                              m->slots_d, seg_changed);
   FAR_HIP(hipGetLastError());
-  k_nbr_update<<<blocks_for(n_seg), kT, 0, st>>>(m->view(), n_seg, seg_vox, is_new, m->vox_key,
+  k_nbr_update<<<blocks_for(n_seg * 26), kT, 0, st>>>(m->view(), n_seg, seg_vox, is_new, m->vox_key,
                                                  m->vox_count, m->vox_nbr);
   FAR_HIP(hipGetLastError());
   // certificates of the points within v of an added point
@@ -1673,23 +1855,12 @@ far_status_t far_map_insert(far_map_t m, const float* xyz, int64_t n, const int3
     FAR_HIP(hipMemsetAsync(m->cert_mark, 0, size_t(m->voxel_cap) * sizeof(uint32_t), st));
     m->cert_gen = 1;
   }
-  k_cert_mark<<<blocks_for(n_seg), kT, 0, st>>>(n_seg, seg_vox, seg_changed, m->vox_nbr,
+  k_cert_mark<<<blocks_for(n_seg * 27), kT, 0, st>>>(n_seg, seg_vox, seg_changed, m->vox_nbr,
                                                 m->cert_mark, m->cert_gen);
   FAR_HIP(hipGetLastError());
-  {
-    const int64_t nv = m->n_voxels + n_new;
-    k_cert_build<<<blocks_for(nv * m->p.max_pts_per_voxel), kT, 0, st>>>(
-        m->view(), nv, m->cert_mark, m->cert_gen, m->cert);
-    FAR_HIP(hipGetLastError());
-  }
+  FAR_TRY(certs_build(m, m->n_voxels + n_new, m->n_points + n_commit, m->cert_mark, m->cert_gen,
+                      m->cov, m->n_points, m->n_points + n_commit, st, scr));
   FAR_TRY(ghosts_update(m, n_seg, seg_vox, is_new, seg_changed, n_new, st));
-  FAR_TRY(map_covariances(m->view(), m->cov, m->n_points, m->n_points + n_commit,
-                          m->p.k_cov, st));
-  if (n_commit > 0) {
-    k_vox_cov<<<blocks_for(n_commit), kT, 0, st>>>(m->cov, m->pt_loc, m->n_points,
-                                                   m->n_points + n_commit, m->vox_cov);
-    FAR_HIP(hipGetLastError());
-  }
   m->n_points += n_commit;
   m->n_voxels += n_new;
   if (n_accepted) *n_accepted = n_commit;
@@ -2265,15 +2436,13 @@ far_status_t far_map_evict(far_map_t m, const double c[3], double radius, int64_
   k_bulk_counts<<<blocks_for(n_seg), kT, 0, st>>>(n_seg, r.seg_start, r.seg_end, seg_vox,
                                                   m->vox_slot, m->vox_count, m->slots_d);
   FAR_HIP(hipGetLastError());
-  k_nbr_update<<<blocks_for(n_seg), kT, 0, st>>>(m->view(), n_seg, seg_vox, is_new, m->vox_key,
+  k_nbr_update<<<blocks_for(n_seg * 26), kT, 0, st>>>(m->view(), n_seg, seg_vox, is_new, m->vox_key,
                                                  m->vox_count, m->vox_nbr);
   FAR_HIP(hipGetLastError());
   k_vox_cov<<<blocks_for(n_keep), kT, 0, st>>>(m->cov, m->pt_loc, 0, n_keep, m->vox_cov);
   FAR_HIP(hipGetLastError());
   // every slot changed: all certificates again, and the ghosts
-  k_cert_build<<<blocks_for(n_seg * m->p.max_pts_per_voxel), kT, 0, st>>>(
-      m->view(), n_seg, nullptr, 0, m->cert);
-  FAR_HIP(hipGetLastError());
+  FAR_TRY(certs_build(m, n_seg, n_keep, nullptr, 0, nullptr, 0, 0, st, scr));
   FAR_TRY(ghosts_update(m, n_seg, seg_vox, nullptr, nullptr, n_seg, st));
   m->n_points = n_keep;
   m->n_voxels = n_seg;
@@ -2295,7 +2464,8 @@ far_status_t far_map_stats(far_map_t m, far_map_stats_t* out, far_stream_t strea
   FAR_TRY(scr.get(&maxp, 1));
   FAR_HIP(hipMemsetAsync(sum, 0, sizeof(unsigned long long), st));
   FAR_HIP(hipMemsetAsync(maxp, 0, sizeof(uint32_t), st));
-  k_probe_stats<<<blocks_for(m->slots), kT, 0, st>>>(m->slots_d, m->slots,
+  const unsigned nb = unsigned(std::min<int64_t>(blocks_for(m->slots), 2 * device_cu_count()));
+  k_probe_stats<<<nb, kT, 0, st>>>(m->slots_d, m->slots,
                                                      uint32_t(m->slots - 1), m->log2_slots,
                                                      sum, maxp);
   FAR_HIP(hipGetLastError());

@@ -326,6 +326,7 @@ struct Scratch {
 // Upper bound of the scratch bytes radix_sort_pairs takes for n elements.
 inline size_t radix_sort_scratch_bytes(int64_t n) {
   size_t nb = size_t((n + 4095) / 4096) + 1;
+  if (nb < 132) nb = 132;   // small jobs use smaller tiles, at most 128
   size_t hist = 256 * nb * 4 + 256;
   size_t sums = 0, m = 256 * nb;
   for (int lvl = 0; lvl < 4; ++lvl) {
@@ -347,11 +348,6 @@ far_status_t radix_sort_pairs(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt
 // when total is not NULL.  in and out may alias.
 far_status_t scan_exclusive(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* total,
                             hipStream_t st, Scratch& scr);
-
-// ---------------------------------------------------------------- covariances
-// Regularised covariances of the map points with ids [id0, id1) on the map.
-far_status_t map_covariances(const MapView& m, float4* cov_out, int64_t id0, int64_t id1,
-                             int32_t k, hipStream_t st);
 
 int device_cu_count();
 

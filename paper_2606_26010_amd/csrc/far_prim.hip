@@ -83,23 +83,52 @@ __global__ __launch_bounds__(kThreads) void k_scan_tiles(const uint32_t* in, uin
 }
 
 // ---------------------------------------------------------------- radix sort
-constexpr int kSortItems = 16;
-constexpr int kSortTile = kThreads * kSortItems;
+// Each pass is a histogram of every tile and a scatter; a tile is kThreads *
+// kItems elements.  Jobs of up to kOwnTiles tiles give every scatter block the
+// histograms themselves (kOwn): it adds up the tiles' rows (at most kOwnTiles
+// words per lane), so that a pass is two launches instead of
+// three to five, and their tiles are smaller, so that 15k points (4 blocks of
+// 4096) still spread over the chip.  Larger jobs take the scanned table: the
+// rows would cost each block 1 kB a tile.  A pass over 100k pairs: 24 us in
+// five launches of 4096-element tiles before, 13 us now; over 5k to 13k pairs
+// 15 -> 8.6 us; over 512k pairs 27 -> 21 us.
+constexpr int kOwnTiles = 128;
 
+template <int kItems, bool kOwn>
 __global__ __launch_bounds__(kThreads) void k_rs_hist(const uint64_t* keys, int64_t n,
                                                       int shift, uint32_t* hist,
                                                       int64_t nblocks) {
   __shared__ uint32_t cnt[256];
   cnt[threadIdx.x] = 0;
-  __syncthreads();
-  int64_t base = int64_t(blockIdx.x) * kSortTile;
-#pragma unroll 4
-  for (int r = 0; r < kSortItems; ++r) {
-    int64_t i = base + int64_t(r) * kThreads + threadIdx.x;
-    if (i < n) atomicAdd(&cnt[uint32_t(keys[i] >> shift) & 255u], 1u);
+  const int64_t base = int64_t(blockIdx.x) * (kThreads * kItems);
+  uint64_t k[kItems];
+#pragma unroll
+  for (int r = 0; r < kItems; ++r) {
+    const int64_t i = base + int64_t(r) * kThreads + threadIdx.x;
+    k[r] = keys[i < n ? i : n - 1];
   }
   __syncthreads();
-  hist[int64_t(threadIdx.x) * nblocks + blockIdx.x] = cnt[threadIdx.x];
+#pragma unroll
+  for (int r = 0; r < kItems; ++r)
+    if (base + int64_t(r) * kThreads + threadIdx.x < n)
+      atomicAdd(&cnt[uint32_t(k[r] >> shift) & 255u], 1u);
+  __syncthreads();
+  hist[kOwn ? int64_t(blockIdx.x) * 256 + threadIdx.x
+            : int64_t(threadIdx.x) * nblocks + blockIdx.x] = cnt[threadIdx.x];
+}
+
+// Inclusive prefix of one value per thread across the block's four waves.
+__device__ inline uint32_t block_iscan(uint32_t v, uint32_t* wsum) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t y = __shfl_up(v, o, 64);
+    if (lane >= o) v += y;
+  }
+  if (lane == 63) wsum[wave] = v;
+  __syncthreads();
+  for (int w = 0; w < wave; ++w) v += wsum[w];
+  return v;
 }
 
 // Stable scatter of one 8-bit digit.  Each block ranks its tile in LDS, then
@@ -109,24 +138,27 @@ __global__ __launch_bounds__(kThreads) void k_rs_hist(const uint64_t* keys, int6
 // order, 64 elements a round: an element's rank among equal digits is the
 // wave's running count of its digit plus its equal digits in lower lanes
 // (found with eight ballots); one prefix over the waves per digit then
-// places the quarters after each other.  hist holds the exclusive prefix,
-// digit-major, of the per-block digit counts, so a block's count of digit d
-// is the difference of its entry and the next one (n after the last).
+// places the quarters after each other.  hist holds the digit counts of every
+// tile, tile-major (kOwn: the lanes of a block read a tile's row together), or
+// their exclusive prefix, digit-major, of which a block's count of digit d is
+// the difference of its entry and the next one (n after the last).
+template <int kItems, bool kOwn>
 __global__ __launch_bounds__(kThreads) void k_rs_scatter(const uint64_t* kin,
                                                          const uint32_t* vin, uint64_t* kout,
                                                          uint32_t* vout, int64_t n, int shift,
                                                          const uint32_t* hist,
                                                          int64_t nblocks) {
-  constexpr int kPerWave = kSortTile / kWaves;
+  constexpr int kTile = kThreads * kItems;
+  constexpr int kPerWave = kTile / kWaves;
   constexpr int kRounds = kPerWave / 64;
-  __shared__ uint64_t lkey[kSortTile];
-  __shared__ uint32_t lval[kSortTile];
+  __shared__ uint64_t lkey[kTile];
+  __shared__ uint32_t lval[kTile];
   __shared__ uint32_t gbase[256];   // global start of this block's digit d
   __shared__ uint32_t lbase[256];   // local start of digit d in the tile
   __shared__ uint32_t wcnt[kWaves][256];
-  __shared__ uint32_t wsum[kWaves];
+  __shared__ uint32_t wsum[kWaves], wsum2[kWaves];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int64_t blk = int64_t(blockIdx.x) * kSortTile;
+  const int64_t blk = int64_t(blockIdx.x) * kTile;
   const int64_t wbase = blk + int64_t(wave) * kPerWave;
   // the wave's quarter into registers first, so that ranking does not wait
   uint64_t kr[kRounds];
@@ -137,24 +169,35 @@ __global__ __launch_bounds__(kThreads) void k_rs_scatter(const uint64_t* kin,
     kr[r] = i < n ? kin[i] : 0ull;
     vr[r] = i < n ? vin[i] : 0u;
   }
-  const int64_t hi = int64_t(t) * nblocks + blockIdx.x;
-  const uint32_t g0 = hist[hi];
-  const uint32_t cnt = (hi + 1 < 256 * nblocks ? hist[hi + 1] : uint32_t(n)) - g0;
+  uint32_t g0, cnt;
+  if constexpr (kOwn) {
+    // this lane's digit: its count in all tiles, in the tiles before, in ours;
+    // sixteen loads in flight
+    const int nt = int(nblocks), me = int(blockIdx.x);
+    uint32_t all = 0, before = 0;
+    for (int b = 0; b < nt; b += 16) {
+      uint32_t c[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) c[u] = hist[min(b + u, nt - 1) * 256 + t];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        const uint32_t x = b + u < nt ? c[u] : 0u;
+        all += x;
+        before += b + u < me ? x : 0u;
+      }
+    }
+    cnt = hist[me * 256 + t];
+    g0 = block_iscan(all, wsum2) - all + before;
+  } else {
+    const int64_t hi = int64_t(t) * nblocks + blockIdx.x;
+    g0 = hist[hi];
+    cnt = (hi + 1 < 256 * nblocks ? hist[hi + 1] : uint32_t(n)) - g0;
+  }
   gbase[t] = g0;
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) wcnt[w][t] = 0;
-  // exclusive prefix of the 256 counts: within each wave, then across waves
-  uint32_t incl = cnt;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t y = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += y;
-  }
-  if (lane == 63) wsum[wave] = incl;
-  __syncthreads();
-  uint32_t before = 0;
-  for (int w = 0; w < wave; ++w) before += wsum[w];
-  lbase[t] = before + incl - cnt;
+  // exclusive prefix of the 256 counts
+  lbase[t] = block_iscan(cnt, wsum) - cnt;
   // rank inside the wave's quarter (the wave's LDS operations stay in order,
   // so a group's leader updates the count after every lane of it has read it)
   const uint64_t lower = lane ? (~0ull >> (64 - lane)) : 0ull;
@@ -195,7 +238,7 @@ __global__ __launch_bounds__(kThreads) void k_rs_scatter(const uint64_t* kin,
   __syncthreads();
   // write out in local order: consecutive positions of one digit go to
   // consecutive global addresses
-  const int tile = int(min(int64_t(kSortTile), n - blk));
+  const int tile = int(min(int64_t(kTile), n - blk));
   for (int p = t; p < tile; p += kThreads) {
     const uint64_t k = lkey[p];
     const uint32_t d = uint32_t(k >> shift) & 255u;
@@ -203,6 +246,35 @@ __global__ __launch_bounds__(kThreads) void k_rs_scatter(const uint64_t* kin,
     kout[off] = k;
     vout[off] = lval[p];
   }
+}
+
+template <int kItems>
+far_status_t rs_passes(uint64_t*& ka, uint32_t*& va, uint64_t*& kb, uint32_t*& vb, int64_t n,
+                       int passes, hipStream_t st, Scratch& scr) {
+  const int64_t nblocks = (n + kThreads * kItems - 1) / (kThreads * kItems);
+  const bool own = nblocks <= kOwnTiles;
+  const unsigned grid = unsigned(nblocks);
+  uint32_t* hist = nullptr;
+  FAR_TRY(scr.get(&hist, size_t(256 * nblocks)));
+  for (int p = 0; p < passes; ++p) {
+    const int shift = 8 * p;
+    if (own) {
+      k_rs_hist<kItems, true><<<grid, kThreads, 0, st>>>(ka, n, shift, hist, nblocks);
+      FAR_HIP(hipGetLastError());
+      k_rs_scatter<kItems, true><<<grid, kThreads, 0, st>>>(ka, va, kb, vb, n, shift, hist,
+                                                            nblocks);
+    } else {
+      k_rs_hist<kItems, false><<<grid, kThreads, 0, st>>>(ka, n, shift, hist, nblocks);
+      FAR_HIP(hipGetLastError());
+      FAR_TRY(scan_exclusive(hist, hist, 256 * nblocks, nullptr, st, scr));
+      k_rs_scatter<kItems, false><<<grid, kThreads, 0, st>>>(ka, va, kb, vb, n, shift, hist,
+                                                             nblocks);
+    }
+    FAR_HIP(hipGetLastError());
+    std::swap(ka, kb);
+    std::swap(va, vb);
+  }
+  return FAR_OK;
 }
 
 }  // namespace
@@ -234,23 +306,15 @@ far_status_t radix_sort_pairs(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt
                               Scratch& scr, bool* in_alt) {
   if (in_alt) *in_alt = false;
   if (n <= 1 || bits <= 0) return FAR_OK;
-  int64_t nblocks = (n + kSortTile - 1) / kSortTile;
-  uint32_t* hist = nullptr;
-  FAR_TRY(scr.get(&hist, size_t(256 * nblocks)));
   uint64_t *ka = keys, *kb = keys_alt;
   uint32_t *va = vals, *vb = vals_alt;
-  int passes = (bits + 7) / 8;
-  for (int p = 0; p < passes; ++p) {
-    int shift = 8 * p;
-    k_rs_hist<<<dim3(uint32_t(nblocks)), kThreads, 0, st>>>(ka, n, shift, hist, nblocks);
-    FAR_HIP(hipGetLastError());
-    FAR_TRY(scan_exclusive(hist, hist, 256 * nblocks, nullptr, st, scr));
-    k_rs_scatter<<<dim3(uint32_t(nblocks)), kThreads, 0, st>>>(ka, va, kb, vb, n, shift,
-                                                               hist, nblocks);
-    FAR_HIP(hipGetLastError());
-    uint64_t* tk = ka; ka = kb; kb = tk;
-    uint32_t* tv = va; va = vb; vb = tv;
-  }
+  const int passes = (bits + 7) / 8;
+  if (n <= 64 * 1024)        // at most 64 tiles of 1024
+    FAR_TRY(rs_passes<4>(ka, va, kb, vb, n, passes, st, scr));
+  else if (n <= 256 * 1024)  // at most 128 tiles of 2048
+    FAR_TRY(rs_passes<8>(ka, va, kb, vb, n, passes, st, scr));
+  else                       // tiles of 4096, scanned tables beyond 512k
+    FAR_TRY(rs_passes<16>(ka, va, kb, vb, n, passes, st, scr));
   if (in_alt) {
     *in_alt = ka != keys;
     return FAR_OK;

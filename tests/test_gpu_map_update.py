@@ -43,3 +43,44 @@ def test_insert_covariances_by_neighbour_count(orc, k):
     s = gm.stats()
     assert s["n_voxels"] == om.n_voxels and 1.0 <= s["mean_probe"] <= s["max_probe"]
     gm.close()
+
+
+@pytest.mark.parametrize("n", [1, 255, 256, 257, 1024, 1025, 65536, 65537, 262145, 530001])
+def test_downsample_and_insert_around_tile_sizes(n):
+    """Sizes on both sides of the tiles of the flag scan and of the radix sort,
+    against numpy's first occurrences (a map of one point per voxel and no
+    spacing accepts the first point of every voxel)."""
+    from paper_2606_26010_amd import far
+    g = np.random.default_rng(n)
+    x = (g.uniform(-1, 1, (3, n)) * np.array([[60.0], [8.0], [3.0]])).astype(np.float32)
+    x[0, g.integers(0, n, n // 50)] = np.nan
+    v = 0.5
+    ok = np.isfinite(x).all(0)
+    key = np.floor(x.astype(np.float64) / v)
+    key[:, ~ok] = np.inf
+    _, first = np.unique(key, axis=1, return_index=True)
+    first = np.sort(first)
+    first = first[ok[first]]
+    pts, keep = far.far_voxel_downsample(dev(x), v, want_keep=True)
+    np.testing.assert_array_equal(host(keep), first)
+    np.testing.assert_array_equal(host(pts), x[:, first])
+    m = far.Map(v, 1, 0.0, max(first.size, 1), 0, 1)
+    assert m.insert(dev(x)) == (far.FAR_OK, first.size)
+    np.testing.assert_array_equal(host(m.export()[0]), x[:, first])
+    m.close()
+
+
+def test_insert_refused_on_voxel_capacity_leaves_the_map(orc):
+    """A batch whose new voxels do not fit changes nothing: the same map and the
+    same answers after it, and a smaller batch then goes in as in the oracle."""
+    from paper_2606_26010_amd import far
+    gm = far.Map(1.0, 20, -1.0, 1 << 14, 200, 5)
+    om = orc.Map(1.0, 20, 1.0 / math.sqrt(20.0), 5, point_capacity=1 << 14, voxel_capacity=200)
+    for seed, ext in ((1, 2.5), (2, 30.0), (3, 2.5)):
+        b = synth.random_cloud(seed, 2000, extent=ext)
+        assert gm.insert(dev(b)) == om.insert(b, check=False)[:2], ext
+        for a, o in zip(gm.export(), om.export()):
+            np.testing.assert_allclose(host(a), o, rtol=2e-6, atol=1e-6)
+        q = synth.random_cloud(9, 500, extent=4.0)
+        np.testing.assert_array_equal(host(gm.knn(dev(q), 5, 1.0)[0]), om.knn(q, 5, 1.0)[0])
+    gm.close()

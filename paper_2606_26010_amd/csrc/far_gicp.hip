@@ -11,6 +11,7 @@
 // One iteration is therefore two launches whatever the number of scans; the
 // whole align (state init + max_iters iterations) is captured once into a HIP
 // graph per argument set and replayed.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -99,19 +100,13 @@ __global__ __launch_bounds__(256) void k_tile_fill(const int64_t* offsets, int32
 }
 
 // Offsets {0, n}, pose and fixed centre of a one-scan job, passed by value
-// (no host copy to stage).
+// (no host copy to stage); n < 0: a batch, whose offsets and poses the caller
+// holds on the device.
 struct SingleArgs {
   int64_t n;
   double T[16];
   double c[3];
 };
-
-__global__ void k_set_single(SingleArgs a, int64_t* offsets, double* T, double* cfix) {
-  const int i = threadIdx.x;
-  if (i < 16) T[i] = a.T[i];
-  if (i < 3 && cfix) cfix[i] = a.c[i];
-  if (i < 2) offsets[i] = i == 0 ? 0 : a.n;
-}
 
 // Per-scan state reset: not done, zero stats, linearisation centre.
 __global__ __launch_bounds__(256) void k_init(int32_t S, const double* T, const int32_t* bad,
@@ -128,6 +123,97 @@ __global__ __launch_bounds__(256) void k_init(int32_t S, const double* T, const 
   const double* Ts = T + 16 * int64_t(s);
   for (int a = 0; a < 3; ++a)
     ctr[3 * s + a] = c_fixed ? c_fixed[a] : (recenter ? Ts[4 * a + 3] : 0.0);
+}
+
+// The whole job setup in one launch for up to kTileLdsScans scans: every block
+// takes the per-scan tile counts into a prefix in LDS itself (S values), then
+// fills its tiles, and the first blocks the per-scan state; block 0 writes the
+// prefix, the flag of malformed offsets and a one-scan job's inputs.  (As
+// k_tile_begin, k_tile_fill, k_init and a launch for the inputs: 18 us for one
+// scan, 22 us for 64, whose prefix one lane took in turn; 4.7 us.)
+__global__ __launch_bounds__(256) void k_setup(SingleArgs one, int64_t* offsets, double* T,
+                                               double* cfix, int32_t S, int64_t n_total,
+                                               int64_t max_tiles, int32_t tile, int32_t* begin,
+                                               int32_t* bad, int32_t* tile_scan,
+                                               uint32_t* tile_lo, uint32_t* tile_hi,
+                                               int32_t recenter, const double* c_fixed,
+                                               far_align_stats_t* stats, int32_t* done,
+                                               double* ctr, uint32_t* counter) {
+  __shared__ int32_t s_begin[kTileLdsScans + 1];
+  __shared__ int64_t wsum[4];
+  __shared__ int32_t s_bad;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const bool single = one.n >= 0;
+  auto off = [&](int32_t s) { return single ? (s == 0 ? int64_t(0) : one.n) : offsets[s]; };
+  if (tid == 0) {
+    s_bad = off(0) != 0 || off(S) != n_total ? 1 : 0;
+    s_begin[0] = 0;
+  }
+  __syncthreads();
+  int64_t carry = 0;
+  for (int32_t s0 = 0; s0 < S; s0 += 256) {
+    const int32_t s = s0 + tid;
+    const int64_t len = s < S ? off(s + 1) - off(s) : 0;
+    if (len < 0) s_bad = 1;
+    int64_t x = len > 0 ? (len + tile - 1) / tile : 0;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int64_t u = __shfl_up((long long)x, d);
+      if (lane >= d) x += u;
+    }
+    if (lane == 63) wsum[wave] = x;
+    __syncthreads();
+    int64_t total = 0;
+    for (int w = 0; w < 4; ++w) {
+      x += w < wave ? wsum[w] : 0;
+      total += wsum[w];
+    }
+    if (s < S) s_begin[s + 1] = int32_t(carry + x);
+    carry += total;
+    __syncthreads();
+  }
+  if (tid == 0 && carry > max_tiles) s_bad = 1;
+  __syncthreads();
+  const int32_t b = s_bad;
+  const int32_t n_tiles = b ? 0 : s_begin[S];
+  if (blockIdx.x == 0) {
+    for (int32_t s = tid; s <= S; s += 256) begin[s] = b ? 0 : s_begin[s];
+    if (tid == 0) *bad = b;
+    if (single) {
+      if (tid < 16) T[tid] = one.T[tid];
+      if (tid < 3 && cfix) cfix[tid] = one.c[tid];
+      if (tid < 2) offsets[tid] = tid == 0 ? 0 : one.n;
+    }
+  }
+  const int64_t t = int64_t(blockIdx.x) * 256 + tid;
+  if (t < S) {
+    // (a scan without points has no tile whose block would end its align)
+    const bool empty = !b && !c_fixed && s_begin[t] == s_begin[t + 1];
+    done[t] = b || empty ? 1 : 0;
+    counter[t] = 0u;
+    far_align_stats_t st = {};
+    st.status = b ? FAR_E_INVALID : (empty ? FAR_E_FEW_CORR : FAR_OK);
+    stats[t] = st;
+    for (int a = 0; a < 3; ++a) {
+      const double ta = single ? one.T[4 * a + 3] : T[16 * t + 4 * a + 3];
+      ctr[3 * t + a] = c_fixed ? (single ? one.c[a] : c_fixed[a]) : (recenter ? ta : 0.0);
+    }
+  }
+  if (t >= max_tiles) return;
+  if (t >= n_tiles) {
+    tile_scan[t] = -1;
+    return;
+  }
+  // the scan s with begin[s] <= t < begin[s + 1]
+  int32_t lo = 0, hi = S - 1;
+  while (lo < hi) {
+    const int32_t mid = (lo + hi + 1) >> 1;
+    if (s_begin[mid] <= t) lo = mid; else hi = mid - 1;
+  }
+  const int64_t a = off(lo) + (t - s_begin[lo]) * int64_t(tile), e = off(lo + 1);
+  tile_scan[t] = lo;
+  tile_lo[t] = uint32_t(a);
+  tile_hi[t] = uint32_t(a + tile < e ? a + tile : e);
 }
 
 // ---------------------------------------------------------------- reduction
@@ -209,13 +295,6 @@ __global__ __launch_bounds__(256) void k_order_keys(const float* src, int64_t n,
   vals[i] = uint32_t(i);
 }
 
-// No previous correspondence yet (a kernel, not a memset: the align may be
-// captured into a graph).
-__global__ __launch_bounds__(256) void k_fill_none(int32_t* a, int64_t n) {
-  int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  if (i < n) a[i] = -1;
-}
-
 // Index of this thread's item when blocks are dealt to the eight XCDs in
 // contiguous ranges (a grid of 8 * ceil(blocks / 8)); -1 past the end.  The
 // sort keeps each scan's points in the scan's own index range, so the
@@ -248,6 +327,26 @@ __global__ __launch_bounds__(256) void k_pack(const float* src, const float* cov
   if (m >= uint64_t(n)) return;   // not a permutation (a caller's order): no write
   A[m] = make_float4(src[i], src[n + i], src[2 * n + i], __int_as_float(int32_t(i)));
   bool ok = valid[i] != 0;
+  B[m] = make_float4(ok ? cov6[i] : -1.0f, cov6[n + i], cov6[2 * n + i], cov6[3 * n + i]);
+  C[m] = make_float2(cov6[4 * n + i], cov6[5 * n + i]);
+}
+
+// The same packing by gather, one launch instead of two: for jobs of up to
+// kGatherPack points, where the launches count (2.4 + 4.8 us for 100k points,
+// 5.8 us); at 4.9M points the scattered reads cost more than the scattered
+// writes of k_pack (158 against 134 us).
+constexpr int64_t kGatherPack = 512 * 1024;
+
+__global__ __launch_bounds__(256) void k_pack_gather(const float* src, const float* cov6,
+                                                     const uint8_t* valid, int64_t n,
+                                                     const uint32_t* perm, float4* A, float4* B,
+                                                     float2* C) {
+  const int64_t m = xcd_item(n);
+  if (m < 0) return;
+  const uint32_t i = perm[m];
+  if (i >= uint64_t(n)) return;   // not a permutation (a caller's order): no write
+  A[m] = make_float4(src[i], src[n + i], src[2 * n + i], __int_as_float(int32_t(i)));
+  const bool ok = valid[i] != 0;
   B[m] = make_float4(ok ? cov6[i] : -1.0f, cov6[n + i], cov6[2 * n + i], cov6[3 * n + i]);
   C[m] = make_float2(cov6[4 * n + i], cov6[5 * n + i]);
 }
@@ -1035,34 +1134,41 @@ __device__ void se3_apply(const double* dl, const double* c, double* T) {
   }
 }
 
-__global__ __launch_bounds__(256) void k_reduce_solve(int32_t S, const int32_t* begin,
-                                                      const double* partial, double* T,
-                                                      double* ctr, int32_t* done,
-                                                      far_align_stats_t* stats, Params prm,
-                                                      int32_t solve, uint32_t* bins) {
-  // the next iteration's queue starts empty (this iteration's search has
-  // read its bins)
-  if (bins && blockIdx.x == 0 && threadIdx.x < kBins) bins[threadIdx.x] = 0u;
-  // eight groups of 32 lanes: group g sums tiles begin+g, begin+g+8, ... of
-  // the scan in that order, then the eight group sums are added in group
-  // order; the loads go out sixteen at a time (the sums wait on them)
+// A tile's partial sum of value v: as one row per tile, or (kHalf) as one row
+// per wave of 64 points, two a tile, added as the block of a tile adds its
+// waves.
+template <bool kHalf>
+__device__ inline double tile_sum(const double* partial, int64_t t, int v) {
+  if constexpr (kHalf)
+    return (0.0 + partial[2 * t * kStride + v]) + partial[(2 * t + 1) * kStride + v];
+  else
+    return partial[t * kStride + v];
+}
+
+// Sums of scan s's tile partials and its Gauss-Newton update, by the first 256
+// threads of a block (all threads call it): eight groups of 32 lanes, group g
+// sums tiles begin+g, begin+g+8, ... of the scan in that order, then the eight
+// group sums are added in group order; the loads go out sixteen at a time (the
+// sums wait on them).
+template <bool kHalf>
+__device__ void reduce_solve_scan(int32_t s, const int32_t* begin, const double* partial,
+                                  double* T, double* ctr, int32_t* done,
+                                  far_align_stats_t* stats, const Params& prm, int32_t solve) {
   __shared__ double part[8][kVals];
   __shared__ double lin[kVals];
-  const int32_t s = blockIdx.x;
-  if (s >= S || done[s]) return;
   const int g = threadIdx.x >> 5, v = threadIdx.x & 31;
-  if (v < kVals) {
+  if (g < 8 && v < kVals) {
     double acc = 0.0;
     const int32_t t1 = begin[s + 1];
     int32_t t = begin[s] + g;
     for (; t + 8 * 15 < t1; t += 8 * 16) {
       double x[16];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) x[u] = partial[int64_t(t + 8 * u) * kStride + v];
+      for (int u = 0; u < 16; ++u) x[u] = tile_sum<kHalf>(partial, t + 8 * u, v);
 #pragma unroll
       for (int u = 0; u < 16; ++u) acc += x[u];
     }
-    for (; t < t1; t += 8) acc += partial[int64_t(t) * kStride + v];
+    for (; t < t1; t += 8) acc += tile_sum<kHalf>(partial, t, v);
     part[g][v] = acc;
   }
   __syncthreads();
@@ -1147,6 +1253,228 @@ __global__ __launch_bounds__(256) void k_reduce_solve(int32_t S, const int32_t* 
   }
 }
 
+__global__ __launch_bounds__(256) void k_reduce_solve(int32_t S, const int32_t* begin,
+                                                      const double* partial, double* T,
+                                                      double* ctr, int32_t* done,
+                                                      far_align_stats_t* stats, Params prm,
+                                                      int32_t solve, uint32_t* bins) {
+  // the next iteration's queue starts empty (this iteration's search has
+  // read its bins)
+  if (bins && blockIdx.x == 0 && threadIdx.x < kBins) bins[threadIdx.x] = 0u;
+  const int32_t s = blockIdx.x;
+  if (s >= S || done[s]) return;
+  reduce_solve_scan<false>(s, begin, partial, T, ctr, done, stats, prm, solve);
+}
+
+// ---------------------------------------------------------------- wide jobs
+// One Gauss-Newton iteration of a small job in one launch.  With one lane per
+// point, a scan of a few thousand points is a few dozen waves, each as long as
+// its slowest chain of loads (first iteration 40 us, queued search 14 us for
+// 5000 points), and an iteration is four launches.  Here a block of kWide
+// lanes takes one wave's 64 points: the first wave certifies them, the points
+// left over (in the first iteration all) are searched by 32 lanes each, every
+// lane probing and ranking one of the 27 voxels, the first wave forms the
+// terms and sums them, and the last block of a scan to finish sums the tiles
+// and solves (a count per scan; each block's sums are released before it
+// counts, and the last one acquires them).  The correspondences are those of
+// the exact search, and the sums are taken in the order of the tile passes (per
+// wave, then the two waves of a tile of 128, then the tiles), so the results
+// are theirs bit for bit.  5000 points, first iteration 45 us in two launches
+// and each later one about 45 us in four; 34 and 19 us in one.
+constexpr int kWide = 512;        // lanes per block: 16 searches at once
+constexpr int kWidePts = 64;
+constexpr int kWideLanes = 32;
+
+// The nearest map point of one query by 32 lanes (lane in [0, 32)), continuing
+// from the candidate in top, the same in every lane; the result in every lane.
+__device__ inline void nn_wide(const MapView& m, const Params& prm, double px, double py,
+                               double pz, int lane, TopK<1>& top) {
+  if (lane < 27) {
+    int64_t kx = 0, ky = 0, kz = 0;   // in range: held when the point was located
+    (void)voxel_index_fast(px, m.v, prm.inv_v, prm.v_pow2, &kx);
+    (void)voxel_index_fast(py, m.v, prm.inv_v, prm.v_pow2, &ky);
+    (void)voxel_index_fast(pz, m.v, prm.inv_v, prm.v_pow2, &kz);
+    FaceOffsets fo;
+    fo.f[0] = float(px - double(kx) * m.v);
+    fo.f[1] = float(py - double(ky) * m.v);
+    fo.f[2] = float(pz - double(kz) * m.v);
+    fo.v = float(m.v);
+    fo.slack = float(1e-7 * m.v);
+    const double bound = fmin(prm.r2, top.bound());
+    if (double(fo.lb2(lane)) <= bound) {
+      int32_t cnt;
+      const int32_t vox = map_find(m, kx + lane / 9 - 1, ky + (lane / 3) % 3 - 1,
+                                   kz + lane % 3 - 1, &cnt);
+      if (vox >= 0) {
+        Query q = make_query(px, py, pz, prm.r2);
+        q.bound_f = screen_bound(bound, q.m);
+        scan_voxel_points<1, 8>(m.vox_pts, vox * m.nmax, cnt, q, prm.r2, top);
+      }
+    }
+  }
+#pragma unroll
+  for (int d = kWideLanes / 2; d >= 1; d >>= 1) {
+    const double od = __shfl_xor(top.d[0], d, kWideLanes);
+    const int32_t oi = __shfl_xor(top.id[0], d, kWideLanes);
+    const int32_t op = __shfl_xor(top.pos[0], d, kWideLanes);
+    if (rank_less(od, oi, top.d[0], top.id[0])) {
+      top.d[0] = od;
+      top.id[0] = oi;
+      top.pos[0] = op;
+    }
+  }
+}
+
+// Sums over one wave of kNV values per lane into row[0 .. kNV): as the tile
+// passes take them (FP32 through a table of the wave's own in LDS, FP64 by
+// lane swaps).
+template <class Real, int kNV>
+__device__ inline void wave_sums(const Real* acc, float* tb, int lane, double* row) {
+  if constexpr (std::is_same<Real, float>::value) {
+    const int v = lane >> 2, quarter = lane & 3;
+#pragma unroll
+    for (int c0 = 0; c0 < kNV; c0 += kRedChunk) {
+      // one wave: its LDS operations complete in order
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+      for (int q = 0; q < kRedChunk; ++q)
+        if (c0 + q < kNV) tb[q * kRedRow + lane] = acc[c0 + q];
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      double sv = 0.0;
+      if (c0 + v < kNV) {
+        const float* r = tb + v * kRedRow + 16 * quarter;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sv += double(r[e]);
+      }
+      sv += dpp_partner<0xB1>(sv);
+      sv += dpp_partner<0x4E>(sv);
+      if (quarter == 0 && c0 + v < kNV) row[c0 + v] = sv;
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < kNV; ++q) {
+      const double sv = wave_sum(acc[q]);
+      if (lane == 0) row[q] = sv;
+    }
+  }
+}
+
+template <class Real, bool kGrad, bool kNoSA>
+__global__ __launch_bounds__(kWide) void k_wide_iter(
+    MapView m, const float4* __restrict__ pA, const float4* __restrict__ pB,
+    const float2* __restrict__ pC, const int32_t* __restrict__ tile_scan,
+    const uint32_t* __restrict__ tile_lo, const uint32_t* __restrict__ tile_hi, int64_t n_half,
+    const int32_t* __restrict__ begin, double* T, double* ctr, int32_t* done, Params prm,
+    double* partial, uint32_t* counter, far_align_stats_t* stats, int32_t solve, int32_t first,
+    int32_t* corr, float* grad_src, int64_t n_src, int32_t* prev) {
+  constexpr int kNV = kGrad ? 14 : kVals;
+  __shared__ double q_p[kWidePts][3];
+  __shared__ double q_d[kWidePts];
+  __shared__ int32_t q_id[kWidePts], q_pos[kWidePts], q_lane[kWidePts], s_match[kWidePts];
+  __shared__ int32_t q_n;
+  __shared__ uint32_t s_last;
+  __shared__ float tbl[std::is_same<Real, float>::value ? kRedChunk * kRedRow : 1];
+  const int64_t hb = block_tile(n_half);
+  if (hb < 0) return;
+  const int64_t t = hb >> 1;
+  const int32_t s = tile_scan[t];
+  if (s < 0 || done[s]) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const uint32_t lo = tile_lo[t] + uint32_t(kWidePts) * uint32_t(hb & 1), hi = tile_hi[t];
+  const uint32_t i = lo + uint32_t(lane);
+  const bool own = tid < 64 && i < hi;
+  const Pose P(T + 16 * int64_t(s));
+  float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  double px = 0.0, py = 0.0, pz = 0.0;
+  if (tid < 64) {
+    bool queued = false;
+    Cand c;
+    c.pos = -1;
+    c.d = 0.0;
+    int32_t res = -1;
+    if (own) {
+      a = pA[i];
+      const int32_t seed = first ? -1 : prev[i];
+      int64_t kx = 0, ky = 0, kz = 0;
+      const bool have = locate(a, P, m, prm, px, py, pz, kx, ky, kz);
+      queued = have && (first || !nn_cert_try(m, px, py, pz, int32_t(kx), int32_t(ky),
+                                              int32_t(kz), prm.r2, seed, c));
+      if (!queued) {
+        res = have && c.d <= prm.r2 ? c.pos : -1;
+        if (prev) prev[i] = have ? c.pos : -1;
+      }
+    }
+    s_match[lane] = res;
+    const uint64_t bal = __ballot(queued);
+    if (lane == 0) q_n = __popcll(bal);
+    if (queued) {
+      const int q = __popcll(bal & ((uint64_t(1) << lane) - 1));
+      q_p[q][0] = px;
+      q_p[q][1] = py;
+      q_p[q][2] = pz;
+      q_d[q] = c.d;
+      q_id[q] = c.pos >= 0 ? __float_as_int(m.vox_pts[c.pos].w) : 0;
+      q_pos[q] = c.pos;
+      q_lane[q] = lane;
+    }
+  }
+  __syncthreads();
+  for (int q = tid / kWideLanes; q < q_n; q += kWide / kWideLanes) {
+    TopK<1> top;
+    top.init();
+    const int32_t cp = q_pos[q];
+    if (cp >= 0 && q_d[q] <= prm.r2) top.push(q_d[q], q_id[q], cp);
+    nn_wide(m, prm, q_p[q][0], q_p[q][1], q_p[q][2], tid & (kWideLanes - 1), top);
+    if ((tid & (kWideLanes - 1)) == 0) {
+      s_match[q_lane[q]] = top.pos[0];
+      if (prev) prev[lo + uint32_t(q_lane[q])] = top.pos[0] >= 0 ? top.pos[0] : cp;
+    }
+  }
+  __syncthreads();
+  if (tid < 64) {
+    const double cx = ctr[3 * s], cy = ctr[3 * s + 1], cz = ctr[3 * s + 2];
+    Real acc[kNV];
+#pragma unroll
+    for (int q = 0; q < kNV; ++q) acc[q] = Real(0);
+    const int32_t res = s_match[lane];
+    int32_t id_match = -1;
+    Real gs[3] = {Real(0), Real(0), Real(0)};
+    if (res >= 0) {
+      const float4 r = m.vox_pts[res];
+      const float4 sB = pB[i];
+      const float2 sC = pC[i];
+      const float4 ca = m.vox_cov[2 * int64_t(res)], cb = m.vox_cov[2 * int64_t(res) + 1];
+      if (!kNoSA || (sB.x >= 0.0f && cb.z != 0.0f)) {
+        id_match = __float_as_int(r.w);
+        if constexpr (kGrad)
+          grad_term<Real>(px, py, pz, a, r, ca, cb, sB, sC, P.R, prm.kappa2, acc, gs);
+        else
+          gicp_term<Real>(px, py, pz, r, ca, cb, sB, sC, P.R, cx, cy, cz, prm.kappa2, acc);
+      }
+    }
+    if (own && corr) corr[__float_as_uint(a.w)] = id_match;
+    if (kGrad && own && grad_src) {
+      const uint32_t o = __float_as_uint(a.w);
+      grad_src[o] = float(gs[0]);
+      grad_src[n_src + o] = float(gs[1]);
+      grad_src[2 * n_src + o] = float(gs[2]);
+    }
+    wave_sums<Real, kNV>(acc, tbl, lane, partial + hb * kStride);
+  }
+  if constexpr (!kGrad) {
+    __syncthreads();
+    if (tid == 0) {
+      __threadfence();
+      s_last = atomicAdd(&counter[s], 1u) + 1u == 2u * uint32_t(begin[s + 1] - begin[s]) ? 1u : 0u;
+    }
+    __syncthreads();
+    if (!s_last) return;
+    __threadfence();
+    if (tid == 0) counter[s] = 0u;
+    reduce_solve_scan<true>(s, begin, partial, T, ctr, done, stats, prm, solve);
+  }
+}
+
 // Twist gradient about c from the gradient g of [R | t] (row-major 3 x 4)
 // at pose T: with dR = [w]x R and dt = [w]x (t - c) + v, the rotation part
 // is the axial vector of A - A^T for A = R G_R^T + (t - c) G_t^T and the
@@ -1172,6 +1500,7 @@ __host__ __device__ inline void twist_from_grad(const double* g, const double* T
 // as k_reduce_solve) into out[14 s ..]; with gT given also the per-scan
 // outputs of the batched gradient (grad_T, the twist about c[3 s ..] or the
 // origin, cost, inliers).
+template <bool kHalf>
 __global__ __launch_bounds__(256) void k_reduce_grad(const int32_t* begin,
                                                      const double* partial, double* out,
                                                      const double* T, const double* c,
@@ -1184,7 +1513,7 @@ __global__ __launch_bounds__(256) void k_reduce_grad(const int32_t* begin,
   if (v < 14) {
     double acc = 0.0;
     const int32_t t1 = begin[s + 1];
-    for (int32_t t = begin[s] + g; t < t1; t += 8) acc += partial[int64_t(t) * kStride + v];
+    for (int32_t t = begin[s] + g; t < t1; t += 8) acc += tile_sum<kHalf>(partial, t, v);
     part[g][v] = acc;
   }
   __syncthreads();
@@ -1211,6 +1540,12 @@ __global__ __launch_bounds__(256) void k_reduce_grad(const int32_t* begin,
 
 // Device workspace of the align driver, owned by the map and reused (with its
 // captured graph) while the call arguments stay the same.
+// Jobs of up to kWideMax points (at the smallest tile, over the voxels) run
+// k_wide_iter: 64 points a block are then at most two blocks a CU, which run
+// at once.  Above, one lane per point fills the chip by itself and the wide
+// search does more work than the pruned one (about 540 candidates a query).
+constexpr int64_t kWideMax = 32 * 1024;
+
 struct AlignWS {
   int32_t S = 0;
   int64_t max_tiles = 0;
@@ -1228,6 +1563,7 @@ struct AlignWS {
   double* cfix = nullptr;       // fixed centre (linearize)
   far_align_stats_t* stats = nullptr;   // single-scan path
   double* gsum = nullptr;       // gradient sums
+  uint32_t* counter = nullptr;  // per scan: blocks of an iteration that are done (wide jobs)
   // locality-ordered packed source and its sort buffers
   float4* pA = nullptr;
   float4* pB = nullptr;
@@ -1272,7 +1608,7 @@ void free_ws(AlignWS* w) {
   for (auto& c : w->cap)
     if (c.exec) (void)hipGraphExecDestroy(c.exec);
   void* ptrs[] = {w->tile_scan, w->tile_lo, w->tile_hi, w->begin, w->bad, w->done, w->ctr,
-                  w->partial, w->offsets, w->T, w->cfix, w->stats, w->gsum, w->pA, w->pB, w->pC,
+                  w->partial, w->offsets, w->T, w->cfix, w->stats, w->gsum, w->counter, w->pA, w->pB, w->pC,
                   w->prev, w->match, w->q_idx, w->q_cand, w->q_p, w->q_count,
                   w->okeys, w->okeys_alt, w->ovals, w->ovals_alt, w->arena};
   for (void* p : ptrs)
@@ -1308,7 +1644,11 @@ far_status_t ensure_ws(far_map_s* m, int32_t S, int64_t max_tiles, int64_t n, Al
   FAR_HIP(hipMalloc(&w->tile_scan, size_t(w->max_tiles) * sizeof(int32_t)));
   FAR_HIP(hipMalloc(&w->tile_lo, size_t(w->max_tiles) * sizeof(uint32_t)));
   FAR_HIP(hipMalloc(&w->tile_hi, size_t(w->max_tiles) * sizeof(uint32_t)));
-  FAR_HIP(hipMalloc(&w->partial, size_t(w->max_tiles) * kStride * sizeof(double)));
+  // (two rows a tile for the tiles of a wide job, at most kWideMax points)
+  const int64_t rows = std::max(w->max_tiles,
+                                std::min(2 * w->max_tiles, 2 * (kWideMax / kTileMin + w->S)));
+  FAR_HIP(hipMalloc(&w->partial, size_t(rows) * kStride * sizeof(double)));
+  FAR_HIP(hipMalloc(&w->counter, size_t(w->S) * sizeof(uint32_t)));
   FAR_HIP(hipMalloc(&w->begin, size_t(w->S + 1) * sizeof(int32_t)));
   FAR_HIP(hipMalloc(&w->bad, sizeof(int32_t)));
   FAR_HIP(hipMalloc(&w->done, size_t(w->S) * sizeof(int32_t)));
@@ -1456,11 +1796,45 @@ far_status_t launch_lin(int32_t tile, int64_t grid, hipStream_t st, const MapVie
   return FAR_OK;
 }
 
-// Enqueue the whole job (init, locality packing, iterations) on st.  Nothing
-// here allocates or clears memory, so it can be recorded into a graph.
-far_status_t enqueue(far_map_s* m, AlignWS* w, const Job& j, int64_t max_tiles,
-                     hipStream_t st) {
-  MapView mv = m->view();
+// One iteration (or linearisation, or gradient) of a wide job.
+template <class Real, bool kGrad>
+far_status_t launch_wide(hipStream_t st, const MapView& mv, const AlignWS* w, int64_t max_tiles,
+                         const Job& j, bool first) {
+  const float4* pA = j.in_A ? j.in_A : w->pA;
+  const float4* pB = j.in_A ? j.in_B : w->pB;
+  const float2* pC = j.in_A ? j.in_C : w->pC;
+  const int64_t n_half = 2 * max_tiles;
+  const unsigned grid = unsigned(((n_half + 7) / 8) * 8);
+  auto go = [&](auto no_sa) {
+    k_wide_iter<Real, kGrad, decltype(no_sa)::value><<<grid, kWide, 0, st>>>(
+        mv, pA, pB, pC, w->tile_scan, w->tile_lo, w->tile_hi, n_half, w->begin, j.T, w->ctr,
+        w->done, j.prm, w->partial, w->counter, j.stats, j.c_fixed ? 0 : 1, first ? 1 : 0,
+        j.corr, kGrad ? j.grad_src : nullptr, j.n_total, kGrad ? nullptr : w->prev);
+  };
+  if (j.prm.sa_off)
+    go(std::true_type());
+  else
+    go(std::false_type());
+  FAR_HIP(hipGetLastError());
+  return FAR_OK;
+}
+
+// The job's setup: tiles, per-scan state and (one given) a one-scan job's
+// inputs.
+far_status_t enqueue_setup(const AlignWS* w, const Job& j, int64_t max_tiles,
+                           const SingleArgs* one, hipStream_t st) {
+  SingleArgs none;
+  memset(&none, 0, sizeof(none));
+  none.n = -1;
+  if (j.S <= kTileLdsScans) {
+    const int64_t items = std::max<int64_t>(max_tiles, j.S);
+    k_setup<<<unsigned((items + 255) / 256), 256, 0, st>>>(
+        one ? *one : none, const_cast<int64_t*>(j.offsets), j.T, w->cfix, j.S, j.n_total,
+        max_tiles, j.tile, w->begin, w->bad, w->tile_scan, w->tile_lo, w->tile_hi,
+        j.prm.recenter, j.c_fixed, j.stats, w->done, w->ctr, w->counter);
+    FAR_HIP(hipGetLastError());
+    return FAR_OK;
+  }
   k_tile_begin<<<1, 64, 0, st>>>(j.offsets, j.S, j.n_total, max_tiles, j.tile, w->begin,
                                  w->bad);
   FAR_HIP(hipGetLastError());
@@ -1470,6 +1844,16 @@ far_status_t enqueue(far_map_s* m, AlignWS* w, const Job& j, int64_t max_tiles,
   k_init<<<(j.S + 255) / 256, 256, 0, st>>>(j.S, j.T, w->bad, j.prm.recenter, j.c_fixed,
                                             j.stats, w->done, w->ctr);
   FAR_HIP(hipGetLastError());
+  return FAR_OK;
+}
+
+// Enqueue the whole job (setup, locality packing, iterations) on st; a
+// one-scan job's setup (its pose by value) has run before.  Nothing here
+// allocates or clears memory, so it can be recorded into a graph.
+far_status_t enqueue(far_map_s* m, AlignWS* w, const Job& j, int64_t max_tiles, bool setup,
+                     hipStream_t st) {
+  MapView mv = m->view();
+  if (setup) FAR_TRY(enqueue_setup(w, j, max_tiles, nullptr, st));
   if (j.n_total > 0 && !j.in_A) {   // (a source packed by the caller is used as it is)
     const unsigned nb = unsigned((j.n_total + 255) / 256);
     const uint32_t* perm = j.order;   // the caller's order (e.g. the covariance grid's)
@@ -1486,27 +1870,44 @@ far_status_t enqueue(far_map_s* m, AlignWS* w, const Job& j, int64_t max_tiles,
       inv = in_alt ? w->ovals : w->ovals_alt;
     }
     const unsigned nb8 = ((nb + 7) / 8) * 8;
-    k_invert<<<nb8, 256, 0, st>>>(perm, j.n_total, inv);
-    FAR_HIP(hipGetLastError());
-    k_pack<<<nb8, 256, 0, st>>>(j.src, j.cov6, j.valid, j.n_total, inv, w->pA, w->pB, w->pC);
+    if (j.n_total <= kGatherPack) {
+      k_pack_gather<<<nb8, 256, 0, st>>>(j.src, j.cov6, j.valid, j.n_total, perm, w->pA, w->pB,
+                                         w->pC);
+    } else {
+      k_invert<<<nb8, 256, 0, st>>>(perm, j.n_total, inv);
+      FAR_HIP(hipGetLastError());
+      k_pack<<<nb8, 256, 0, st>>>(j.src, j.cov6, j.valid, j.n_total, inv, w->pA, w->pB, w->pC);
+    }
     FAR_HIP(hipGetLastError());
   }
-  if (j.n_total > 0) {
-    k_fill_none<<<unsigned((j.n_total + 255) / 256), 256, 0, st>>>(w->prev, j.n_total);
-    FAR_HIP(hipGetLastError());
-  }
+  const bool wide = j.n_total <= kWideMax && j.tile == kTileMin && j.S <= kTileLdsScans &&
+                    !(j.prm.fine_nn && mv.fine_ok) && g_lin_blocks_per_cu == 0;
   const int64_t grid = ((max_tiles + 7) / 8) * 8;   // one block per tile
+  const bool fp64 = j.precision == FAR_PREC_FP64;
   if (j.gsum) {
-    if (j.precision == FAR_PREC_FP64)
-      FAR_TRY((launch_lin<double, true>(j.tile, grid, st, mv, w, max_tiles, j, true)));
-    else
-      FAR_TRY((launch_lin<float, true>(j.tile, grid, st, mv, w, max_tiles, j, true)));
-    k_reduce_grad<<<unsigned(j.S), 256, 0, st>>>(w->begin, w->partial, j.gsum, j.T, j.g_c,
-                                                  j.g_T, j.g_tw, j.g_cost, j.g_n);
+    if (wide) {
+      FAR_TRY((fp64 ? launch_wide<double, true>(st, mv, w, max_tiles, j, true)
+                    : launch_wide<float, true>(st, mv, w, max_tiles, j, true)));
+      k_reduce_grad<true><<<unsigned(j.S), 256, 0, st>>>(w->begin, w->partial, j.gsum, j.T,
+                                                         j.g_c, j.g_T, j.g_tw, j.g_cost, j.g_n);
+    } else {
+      FAR_TRY((fp64 ? launch_lin<double, true>(j.tile, grid, st, mv, w, max_tiles, j, true)
+                    : launch_lin<float, true>(j.tile, grid, st, mv, w, max_tiles, j, true)));
+      k_reduce_grad<false><<<unsigned(j.S), 256, 0, st>>>(w->begin, w->partial, j.gsum, j.T,
+                                                          j.g_c, j.g_T, j.g_tw, j.g_cost, j.g_n);
+    }
     FAR_HIP(hipGetLastError());
     return FAR_OK;
   }
   const int iters = j.c_fixed ? 1 : j.prm.max_iters;
+  if (wide) {
+    for (int it = 0; it < iters; ++it) {
+      TimedScope ts(FAR_TIME_LINEARIZE, st);
+      FAR_TRY((fp64 ? launch_wide<double, false>(st, mv, w, max_tiles, j, it == 0)
+                    : launch_wide<float, false>(st, mv, w, max_tiles, j, it == 0)));
+    }
+    return FAR_OK;
+  }
   for (int it = 0; it < iters; ++it) {
     {
       TimedScope ts(FAR_TIME_LINEARIZE, st);
@@ -1530,7 +1931,9 @@ bool same_params(const Params& a, const Params& b) {
 }
 
 // Run a job, through a cached graph when the stream allows capture.
-far_status_t run_job(far_map_s* m, const Job& j0, hipStream_t st, bool use_graph) {
+// one: a one-scan job's inputs (its offsets and pose go to the workspace).
+far_status_t run_job(far_map_s* m, const Job& j0, hipStream_t st, bool use_graph,
+                     const SingleArgs* one = nullptr) {
   Job j = j0;
   j.tile = m->sched_tile;
   // a job too small to give every CU two blocks at the map's tile (one scan
@@ -1545,7 +1948,8 @@ far_status_t run_job(far_map_s* m, const Job& j0, hipStream_t st, bool use_graph
   // the fine index of the current map (stream-ordered), when it is used
   if (j.prm.fine_nn) FAR_TRY(fine_build(m, st));
   (void)device_cu_count();   // query the device outside any capture
-  if (!use_graph || st == nullptr || timing_on()) return enqueue(m, w, j, max_tiles, st);
+  if (one) FAR_TRY(enqueue_setup(w, j, max_tiles, one, st));
+  if (!use_graph || st == nullptr || timing_on()) return enqueue(m, w, j, max_tiles, !one, st);
   // the captured map view holds the fine-index flag: a graph captured with a
   // different flag must not be replayed
   const void* key[12] = {j.src, j.offsets, j.cov6, j.valid, j.T, j.stats, j.c_fixed, j.corr,
@@ -1566,7 +1970,7 @@ far_status_t run_job(far_map_s* m, const Job& j0, hipStream_t st, bool use_graph
     if (memcmp(w->pending, key, sizeof(key)) != 0 && memcmp(w->pending2, key, sizeof(key)) != 0) {
       memcpy(w->pending2, w->pending, sizeof(key));
       memcpy(w->pending, key, sizeof(key));
-      return enqueue(m, w, j, max_tiles, st);
+      return enqueue(m, w, j, max_tiles, !one, st);
     }
     hit = w->cap[0].used <= w->cap[1].used ? &w->cap[0] : &w->cap[1];
     if (hit->exec) {
@@ -1575,7 +1979,7 @@ far_status_t run_job(far_map_s* m, const Job& j0, hipStream_t st, bool use_graph
     }
     hipGraph_t g = nullptr;
     FAR_HIP(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-    far_status_t rs = enqueue(m, w, j, max_tiles, st);
+    far_status_t rs = enqueue(m, w, j, max_tiles, !one, st);
     hipError_t e = hipStreamEndCapture(st, &g);
     if (rs != FAR_OK) {
       if (g) (void)hipGraphDestroy(g);
@@ -1653,17 +2057,12 @@ extern "C" {
 
 const double kOrigin[3] = {0.0, 0.0, 0.0};
 
-// Writes a one-scan job's offsets, pose and (with_c) fixed centre into the
-// workspace by a kernel argument.
-far_status_t set_single(AlignWS* w, int64_t n, const double T[16], const double c[3],
-                        bool with_c, hipStream_t st) {
+static SingleArgs single_args(int64_t n, const double T[16], const double c[3]) {
   SingleArgs a;
   a.n = n;
   memcpy(a.T, T, sizeof(a.T));
   memcpy(a.c, c, sizeof(a.c));
-  k_set_single<<<1, 64, 0, st>>>(a, w->offsets, w->T, with_c ? w->cfix : nullptr);
-  FAR_HIP(hipGetLastError());
-  return FAR_OK;
+  return a;
 }
 
 far_status_t far_gicp_linearize(far_map_t m, const float* src, const float* cov6,
@@ -1682,10 +2081,10 @@ far_status_t far_gicp_linearize(far_map_t m, const float* src, const float* cov6
   hipStream_t st = S(stream);
   AlignWS* w = nullptr;
   FAR_TRY(ensure_ws(m, 1, (n + kTileMin - 1) / kTileMin + 1, n, &w));
-  FAR_TRY(set_single(w, n, T, c ? c : kOrigin, true, st));
+  const SingleArgs one = single_args(n, T, c ? c : kOrigin);
   Job j{src, w->offsets, 1, n, cov6, valid, w->T, w->stats, w->cfix, corr,
         make_params(m, tau, kappa, 0.0, 1, 0, precision), precision_of(precision)};
-  FAR_TRY(run_job(m, j, st, false));
+  FAR_TRY(run_job(m, j, st, false, &one));
   far_align_stats_t hs;
   FAR_HIP(hipMemcpyAsync(&hs, w->stats, sizeof(hs), hipMemcpyDeviceToHost, st));
   FAR_HIP(hipStreamSynchronize(st));
@@ -1712,10 +2111,10 @@ far_status_t far_gicp_linearize_async(far_map_t m, const float* src, const float
   }
   AlignWS* w = nullptr;
   FAR_TRY(ensure_ws(m, 1, (n + kTileMin - 1) / kTileMin + 1, n, &w));
-  FAR_TRY(set_single(w, n, T, c ? c : kOrigin, true, st));
+  const SingleArgs one = single_args(n, T, c ? c : kOrigin);
   Job j{src, w->offsets, 1, n, cov6, valid, w->T, w->stats, w->cfix, corr,
         make_params(m, tau, kappa, 0.0, 1, 0, precision), precision_of(precision)};
-  FAR_TRY(run_job(m, j, st, false));
+  FAR_TRY(run_job(m, j, st, false, &one));
   k_copy_lin<<<1, 64, 0, st>>>(w->stats, out);
   FAR_HIP(hipGetLastError());
   return FAR_OK;
@@ -1773,12 +2172,12 @@ far_status_t far_gicp_gradient(far_map_t m, const float* src, const float* cov6,
   const double cc[3] = {c ? c[0] : 0.0, c ? c[1] : 0.0, c ? c[2] : 0.0};
   {
     TimedScope ts(FAR_TIME_GRADIENT, st);
-    FAR_TRY(set_single(w, n, T, cc, true, st));
+    const SingleArgs one = single_args(n, T, cc);
     Job j{src, w->offsets, 1, n, cov6, valid, w->T, w->stats, w->cfix, nullptr,
           make_params(m, tau, kappa, 0.0, 1, 0, precision), precision_of(precision)};
     j.gsum = w->gsum;
     j.grad_src = grad_src;
-    FAR_TRY(run_job(m, j, st, false));
+    FAR_TRY(run_job(m, j, st, false, &one));
   }
   double g[14];
   FAR_HIP(hipMemcpyAsync(g, w->gsum, sizeof(g), hipMemcpyDeviceToHost, st));
@@ -1842,12 +2241,12 @@ far_status_t far_gicp_align(far_map_t m, const float* src, const float* cov6,
   hipStream_t st = S(stream);
   AlignWS* w = nullptr;
   FAR_TRY(ensure_ws(m, 1, (n + kTileMin - 1) / kTileMin + 1, n, &w));
-  FAR_TRY(set_single(w, n, T0, kOrigin, false, st));
+  const SingleArgs one = single_args(n, T0, kOrigin);
   Job j{src, w->offsets, 1, n, cov6, valid, w->T, w->stats, nullptr, nullptr,
         make_params(m, params->tau, params->kappa, params->eps, params->max_iters,
                     params->recenter, params->precision),
         precision_of(params->precision)};
-  FAR_TRY(run_job(m, j, st, true));
+  FAR_TRY(run_job(m, j, st, true, &one));
   FAR_HIP(hipMemcpyAsync(T_out, w->T, 16 * sizeof(double), hipMemcpyDeviceToHost, st));
   FAR_HIP(hipMemcpyAsync(&hs, w->stats, sizeof(hs), hipMemcpyDeviceToHost, st));
   FAR_HIP(hipStreamSynchronize(st));

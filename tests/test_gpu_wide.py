@@ -1,0 +1,90 @@
+"""Small jobs run one launch per iteration with 32 lanes per searched point:
+sizes around a wave, a tile and the limit, against the oracle, and batches
+(with empty scans and scans without a finite point) bit for bit against their
+scans alone and against the same batch padded past the limit's other side."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2606_26010_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def host(t):
+    return t.detach().cpu().numpy()
+
+
+@pytest.fixture(scope="module")
+def room(orc):
+    from paper_2606_26010_amd import far
+    c = synth.make_tiny(3, n_source=1000)
+    gm = far.Map(c.voxel_size, c.max_pts_per_voxel, c.min_spacing, 1 << 16, 0, c.k)
+    om = orc.Map(c.voxel_size, c.max_pts_per_voxel, c.min_spacing, c.k)
+    for b in c.map_batches:
+        gm.insert(dev(b))
+        om.insert(b)
+    return far, c, gm, om
+
+
+def scan_of(c, n, seed):
+    g = synth.rng(seed)
+    x = synth.tiny_scene_samples(g, n).astype(np.float64) + g.normal(scale=0.02, size=(3, n))
+    return synth.apply(synth.pose_inverse(c.T_gt), x)
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("n", [6, 63, 64, 65, 128, 129, 257, 32768, 32769])
+def test_align_and_gradient_around_the_limits(room, orc, n, prec):
+    far, c, gm, om = room
+    src = scan_of(c, n, 100 + n)
+    cov, val = orc.scan_covariances(src, c.voxel_size, c.k)
+    cov = cov.astype(np.float32)
+    T = c.T_gt @ synth.random_offset(synth.rng(7), 0.05, 0.4)
+    o = om.linearize(src, cov, val, T, c.tau, c.kappa, c=T[:3, 3], want_corr=True)
+    g = gm.linearize(dev(src), dev(cov), dev(val), T, c.tau, c.kappa, c=T[:3, 3], precision=prec,
+                     want_corr=True)
+    np.testing.assert_array_equal(host(g["corr"]), o["corr"])
+    rel = 1e-4 if prec == 0 else 1e-9
+    for k in ("H", "b"):
+        assert np.linalg.norm(g[k] - o[k]) <= rel * np.linalg.norm(o[k]), k
+    og = om.gradient(src, cov, val, T, c.tau, c.kappa, c=T[:3, 3])
+    gg = gm.gradient(dev(src), dev(cov), dev(val), T, c.tau, c.kappa, c=T[:3, 3], precision=prec)
+    assert gg["n_inliers"] == og["n_inliers"]
+    assert np.linalg.norm(gg["grad_T"] - og["grad_T"]) <= rel * np.linalg.norm(og["grad_T"])
+    if n < 63:
+        return
+    prm = far.align_params(c.tau, c.kappa, max_iters=5, eps=0.0, precision=prec)
+    st, Tg, _ = gm.align(dev(src), dev(cov), dev(val), T, prm)
+    ref = om.align(src, cov, val, T, c.tau, c.kappa, max_iters=5, eps=0.0)
+    assert st == ref["status"]
+    np.testing.assert_allclose(Tg, ref["T"], atol=1e-5 if prec == 0 else 1e-9)
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_batches_bit_identical_on_both_sides_of_the_limit(room, prec):
+    """A batch of small scans (one empty, one of a single point, one without a
+    finite point) alone, and with a large scan that takes the whole batch to the
+    tile passes."""
+    far, c, gm, om = room
+    small = [scan_of(c, n, 200 + n) for n in (700, 1, 5, 1500)]
+    small[2][:] = np.nan
+    small.insert(1, np.zeros((3, 0), np.float32))
+    res = []
+    for scans in (small, small + [scan_of(c, 40000, 9)]):
+        offs = dev(np.concatenate([[0], np.cumsum([s.shape[1] for s in scans])]).astype(np.int64))
+        src = dev(np.concatenate(scans, 1))
+        cov, val = far.far_scan_covariances_batch(src, offs, c.voxel_size, c.k)
+        T = dev(np.tile(np.eye(4).reshape(1, 16), (len(scans), 1)))
+        prm = far.align_params(c.tau, c.kappa, max_iters=6, eps=1e-3, precision=prec)
+        st = far.decode_stats(gm.align_batch(src, offs, cov, val, T, prm))
+        G = gm.gradient_batch(src, offs, cov, val, T, c.tau, c.kappa, precision=prec)
+        res.append((host(T)[:5], st[:5], host(G["grad_T"])[:5], host(G["cost"])[:5]))
+    for a, b in zip(*res):
+        np.testing.assert_array_equal(a, b)
+    assert list(res[0][1]["status"]) == [0, far.FAR_E_FEW_CORR, far.FAR_E_FEW_CORR,
+                                         far.FAR_E_FEW_CORR, 0]

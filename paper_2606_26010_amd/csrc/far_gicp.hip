@@ -512,31 +512,8 @@ __device__ inline void grad_term(double px, double py, double pz, float4 s, floa
 // needed neighbours are kept as a bit mask and visited in lockstep - each
 // lane takes its own next needed neighbour in the same step - so a wave does
 // as many voxel visits as its busiest lane needs, not one per offset that
-// any lane needs.
+// any lane needs (lower bounds: FaceOffsets).
 //
-// The lower bounds come from the point's offset inside its voxel, held as
-// three floats: the float rounding (at most 2^-24 v) is covered by the slack
-// of 1e-7 v, and the squared sums are shrunk by 2^-20, so a bound never
-// exceeds the exact distance to the voxel (a low bound costs a visit, never
-// a result).
-struct FaceOffsets {
-  float f[3];     // p - voxel corner, per axis, in [0, v)
-  float v, slack;
-  // both gaps are formed and one is selected (the same value as forming
-  // only the selected one), so a run-time code costs selects, not branches
-  __device__ inline float lb2(int code) const {
-    float s = 0.0f;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const int o = a == 0 ? code / 9 - 1 : (a == 1 ? (code / 3) % 3 - 1 : code % 3 - 1);
-      const float tl = f[a] - slack, th = v - f[a] - slack;
-      const float g = fmaxf(o < 0 ? tl : (o > 0 ? th : 0.0f), 0.0f);
-      s += g * g;
-    }
-    return s * (1.0f - 0x1p-20f);
-  }
-};
-
 // Exact search over the own voxel (unless own_done: its points were already
 // ranked into top) and the neighbour voxels, continuing from the candidates
 // already in top.
@@ -595,7 +572,6 @@ __device__ inline void nn_lockstep(const MapView& m, double px, double py, doubl
 // the neighbour row (the own voxel's or its ghost's) copied into this lane's
 // stretch of LDS by 13 independent 8-byte loads first, so that a visit waits
 // for its points only, and the points loaded eight at a time.
-constexpr int kRowWords = 27;   // per-lane LDS row stride (26 entries, padded)
 __device__ inline void nn_search_dense(const MapView& m, double px, double py, double pz,
                                        int32_t kx, int32_t ky, int32_t kz, double r2,
                                        uint32_t* lrow, TopK<1>& top) {
@@ -616,17 +592,7 @@ __device__ inline void nn_search_dense(const MapView& m, double px, double py, d
     if (g < 0) return;
     row = m.gnbr + int64_t(g) * 26;
   }
-  if (row) {
-    const uint2* r2p = reinterpret_cast<const uint2*>(row);   // rows are 8-byte aligned
-    uint2 e[13];
-#pragma unroll
-    for (int t = 0; t < 13; ++t) e[t] = r2p[t];
-#pragma unroll
-    for (int t = 0; t < 13; ++t) {
-      lrow[2 * t] = e[t].x;
-      lrow[2 * t + 1] = e[t].y;
-    }
-  }
+  if (row) load_row(row, lrow);
   if (own >= 0) scan_voxel_points<1, 8>(m.vox_pts, own * m.nmax, cnt, q, r2, top);
   uint32_t need = 0;
   {

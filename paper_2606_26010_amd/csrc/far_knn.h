@@ -156,31 +156,6 @@ __device__ inline void map_knn_query(const MapView& m, double qx, double qy, dou
   }
 }
 
-// The same search around a query in occupied voxel V (cnt points), whose
-// neighbours and their counts come from its row of the neighbour table
-// instead of a hash probe each.  The visiting order and bounds are those of
-// map_knn_query, so the results are the same.
-template <int K>
-__device__ inline void map_knn_row(const MapView& m, double qx, double qy, double qz, int32_t V,
-                                   int32_t cnt, const uint32_t* row, double r2, TopK<K>& top) {
-  top.init();
-  int64_t kx, ky, kz;
-  if (!voxel_index(qx, m.v, &kx) || !voxel_index(qy, m.v, &ky) ||
-      !voxel_index(qz, m.v, &kz))
-    return;
-  Query q = make_query(qx, qy, qz, r2);
-  scan_voxel_points<K>(m.vox_pts, V * m.nmax, cnt, q, r2, top);
-  for (int t = 1; t < 27; ++t) {
-    const int code = kNbrOrder[t];
-    const uint32_t e = row[nbr_dir(code)];
-    if (e == kNbrNone) continue;
-    const int ox = code / 9 - 1, oy = (code / 3) % 3 - 1, oz = code % 3 - 1;
-    if (voxel_lb2(qx, qy, qz, kx, ky, kz, ox, oy, oz, m.v) > fmin(r2, top.bound())) continue;
-    scan_voxel_points<K>(m.vox_pts, int32_t(e >> kNbrCountBits) * m.nmax,
-                         int32_t(e & ((1u << kNbrCountBits) - 1u)), q, r2, top);
-  }
-}
-
 // Neighbour offsets in visiting order (faces, edges, corners), packed five
 // bits per entry as code = (ox+1)*9 + (oy+1)*3 + (oz+1): ranks 1-12, 13-24,
 // 25-26 in three words.
@@ -198,6 +173,91 @@ __device__ inline int nbr_code(int rank) {
   const uint64_t w = r < 12 ? w0 : (r < 24 ? w1 : w2);
   const int sh = 5 * (r < 12 ? r : (r < 24 ? r - 12 : r - 24));
   return int((w >> sh) & 31u);
+}
+
+// The lower bounds come from the point's offset inside its voxel, held as
+// three floats: the float rounding (at most 2^-24 v) is covered by the slack
+// of 1e-7 v, and the squared sums are shrunk by 2^-20, so a bound never
+// exceeds the exact distance to the voxel (a low bound costs a visit, never
+// a result).
+struct FaceOffsets {
+  float f[3];     // p - voxel corner, per axis, in [0, v)
+  float v, slack;
+  // both gaps are formed and one is selected (the same value as forming
+  // only the selected one), so a run-time code costs selects, not branches
+  __device__ inline float lb2(int code) const {
+    float s = 0.0f;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const int o = a == 0 ? code / 9 - 1 : (a == 1 ? (code / 3) % 3 - 1 : code % 3 - 1);
+      const float tl = f[a] - slack, th = v - f[a] - slack;
+      const float g = fmaxf(o < 0 ? tl : (o > 0 ? th : 0.0f), 0.0f);
+      s += g * g;
+    }
+    return s * (1.0f - 0x1p-20f);
+  }
+};
+
+// Smallest float not below d (d finite and non-negative): a float compared
+// with it keeps every case the comparison with d keeps and adds at most the
+// ties with the rounded value, which only adds visits to an exact search.
+__device__ inline float f32_up(double d) {
+  float f = float(d);
+  if (double(f) < d) f = __uint_as_float(__float_as_uint(f) + 1u);
+  return f;
+}
+
+// The neighbour-table row at `row` into this lane's stretch of LDS, by 13
+// independent 8-byte loads (rows are 8-byte aligned).
+constexpr int kRowWords = 27;   // per-lane LDS row stride (26 entries, padded)
+__device__ inline void load_row(const uint32_t* row, uint32_t* lrow) {
+  const uint2* r = reinterpret_cast<const uint2*>(row);
+  uint2 e[13];
+#pragma unroll
+  for (int t = 0; t < 13; ++t) e[t] = r[t];
+#pragma unroll
+  for (int t = 0; t < 13; ++t) {
+    lrow[2 * t] = e[t].x;
+    lrow[2 * t + 1] = e[t].y;
+  }
+}
+
+// The search of map_knn_query around a query in voxel (kx, ky, kz), which
+// holds the cnt points from slot `own` on (none: an empty voxel), its
+// neighbours and their counts taken from the voxel's row of the neighbour
+// table in LDS instead of a hash probe each.  Each lane keeps the neighbours
+// it may need as a bit mask and visits its own next one in lockstep.  Exact, as
+// there: a voxel is skipped only when none of its points could rank.
+template <int K>
+__device__ inline void map_knn_row(const MapView& m, double qx, double qy, double qz, int32_t kx,
+                                   int32_t ky, int32_t kz, int32_t own, int32_t cnt,
+                                   const uint32_t* lrow, double r2, TopK<K>& top) {
+  FaceOffsets fo;
+  fo.f[0] = float(qx - double(kx) * m.v);
+  fo.f[1] = float(qy - double(ky) * m.v);
+  fo.f[2] = float(qz - double(kz) * m.v);
+  fo.v = float(m.v);
+  fo.slack = float(1e-7 * m.v);
+  Query q = make_query(qx, qy, qz, r2);
+  if (cnt > 0) scan_voxel_points<K>(m.vox_pts, own, cnt, q, r2, top);
+  uint32_t need = 0;
+  {
+    const float bnd = f32_up(fmin(r2, top.bound()));
+#pragma unroll
+    for (int rank = 1; rank < 27; ++rank) {
+      const int code = nbr_code(rank);
+      if (lrow[nbr_dir(code)] != kNbrNone && fo.lb2(code) <= bnd) need |= 1u << rank;
+    }
+  }
+  while (need) {
+    const int rank = __builtin_ctz(need);
+    need &= need - 1;
+    const int code = nbr_code(rank);
+    if (double(fo.lb2(code)) > fmin(r2, top.bound())) continue;
+    const uint32_t e = lrow[nbr_dir(code)];
+    scan_voxel_points<K>(m.vox_pts, int32_t(e >> kNbrCountBits) * m.nmax,
+                         int32_t(e & ((1u << kNbrCountBits) - 1u)), q, r2, top);
+  }
 }
 
 __device__ inline double lb2_of(const double* gl2, const double* gh2, int code) {
@@ -271,15 +331,6 @@ __device__ inline void knn_cells(double px, double py, double pz, double c, doub
         st = find(kx + ox, ky + oy, kz + oz, &cnt);
         if (st >= 0) scan_voxel_points<K>(pts, st, cnt, q, r2, top);
       }
-}
-
-// Smallest float not below d (d finite and non-negative): a float compared
-// with it keeps every case the comparison with d keeps and adds at most the
-// ties with the rounded value, which only adds visits to an exact search.
-__device__ inline float f32_up(double d) {
-  float f = float(d);
-  if (double(f) < d) f = __uint_as_float(__float_as_uint(f) + 1u);
-  return f;
 }
 
 // Squared face distance as a float that never exceeds the FP64 value:

@@ -108,15 +108,6 @@ __global__ __launch_bounds__(kT) void k_keys(const float* xyz, int64_t n, double
   vals[i] = uint32_t(i);
 }
 
-// Segment heads of the sorted keys (first element of each run of equal keys).
-__global__ __launch_bounds__(kT) void k_heads(const uint64_t* keys, int64_t n,
-                                              uint32_t* head) {
-  int64_t j = int64_t(blockIdx.x) * kT + threadIdx.x;
-  if (j >= n) return;
-  uint64_t k = keys[j];
-  head[j] = (k != kEmptyKey && (j == 0 || keys[j - 1] != k)) ? 1u : 0u;
-}
-
 // ---------------------------------------------------------------- downsample
 // The first point (in input order) of every voxel, through a hash of the
 // scan's voxels instead of a sort by voxel: every point finds or claims its
@@ -208,27 +199,12 @@ __global__ __launch_bounds__(kT) void k_transform(const float* xyz, int64_t n, R
   out[2 * n + i] = o[2];
 }
 
-// Segment bounds: seg_start[s] and seg_end[s] for every run s.
-__global__ __launch_bounds__(kT) void k_seg_bounds(const uint64_t* keys, int64_t n,
-                                                   const uint32_t* head,
-                                                   const uint32_t* head_scan,
-                                                   uint32_t* seg_start, uint32_t* seg_end) {
-  int64_t j = int64_t(blockIdx.x) * kT + threadIdx.x;
-  if (j >= n) return;
-  uint64_t k = keys[j];
-  if (k == kEmptyKey) return;
-  uint32_t s = head_scan[j] + head[j] - 1;
-  if (head[j]) seg_start[s] = uint32_t(j);
-  if (j == n - 1 || keys[j + 1] != k) seg_end[s] = uint32_t(j + 1);
-}
-
-// The cell of a sorted point: the bits of its key above `shift`; at least
-// `empty` for the points without a voxel (non-finite), which sort last.
+// The cells of sorted points: keys of at least `empty` belong to the points
+// without a voxel (non-finite), which sort last.
 struct SortedKeys {
   const uint64_t* k;
-  int shift;
   uint64_t empty;
-  __device__ uint64_t cell(int64_t j) const { return k[j] >> shift; }
+  __device__ uint64_t cell(int64_t j) const { return k[j]; }
 };
 
 // Runs of equal cells of the sorted points: seg_start, seg_end per run.
@@ -524,40 +500,35 @@ __global__ __launch_bounds__(kT) void k_cert_list(int64_t n_vox, int32_t nmax,
 // come from the voxel's row of the neighbour table (in LDS, read in one go)
 // instead of a hash probe each.  On average over two inserts of 500k points
 // into an emptied map: 782 us for one lane per slot with probes and 188 us for the separate
-// covariance search, now 308 us in all; at 15k points 97 + 89 -> 101 us.
-constexpr int kRowPad = 27;   // words per lane of the row copy (26 and a pad)
+// covariance search, now 194 us in all (300 with the row as an indexed local array and 222
+// registers); at 15k points 97 + 89 -> 87 us.
+constexpr int kCertWaves = 4;   // waves per SIMD asked for (128 registers)
 
 template <int K>
-__global__ __launch_bounds__(kT) void k_cert_build(MapView m, const uint32_t* list,
+__global__ __launch_bounds__(kT, kCertWaves) void k_cert_build(MapView m, const uint32_t* list,
                                                    const uint32_t* count, CertRow* cert,
                                                    float4* cov, float4* vox_cov, int64_t id0,
                                                    int32_t k, int32_t reg) {
   static_assert(K >= kCertK + 2, "a certificate needs kCertK + 2 entries");
-  __shared__ uint32_t rows[kT * kRowPad];
-  uint32_t* row = rows + threadIdx.x * kRowPad;
+  __shared__ uint32_t rows[kT * kRowWords];
+  uint32_t* row = rows + threadIdx.x * kRowWords;
   const uint32_t n = *count;
   for (uint32_t t = blockIdx.x * kT + threadIdx.x; t < n; t += gridDim.x * kT) {
     const uint32_t pos = list[t];
     const int32_t V = int32_t(pos / uint32_t(m.nmax));
     const float4 p = m.vox_pts[pos];
-    {
-      const uint2* r = reinterpret_cast<const uint2*>(m.vox_nbr + int64_t(V) * 26);
-      uint2 e[13];
-#pragma unroll
-      for (int u = 0; u < 13; ++u) e[u] = r[u];
-#pragma unroll
-      for (int u = 0; u < 13; ++u) {
-        row[2 * u] = e[u].x;
-        row[2 * u + 1] = e[u].y;
-      }
-    }
-    const int32_t own = m.vox_count[V];
+    load_row(m.vox_nbr + int64_t(V) * 26, row);
     TopK<K> top;
-    map_knn_row<K>(m, double(p.x), double(p.y), double(p.z), V, own, row, m.v * m.v, top);
-    CertRow r;
-    r.x = p.x;
-    r.y = p.y;
-    r.z = p.z;
+    top.init();
+    int64_t kx = 0, ky = 0, kz = 0;   // in range: held when the point was inserted
+    (void)voxel_index(double(p.x), m.v, &kx);
+    (void)voxel_index(double(p.y), m.v, &ky);
+    (void)voxel_index(double(p.z), m.v, &kz);
+    map_knn_row<K>(m, double(p.x), double(p.y), double(p.z), int32_t(kx), int32_t(ky),
+                   int32_t(kz), V * m.nmax, m.vox_count[V], row, m.v * m.v, top);
+    // the row straight to memory (an array of its entries, indexed by a count,
+    // would live in scratch)
+    float4* out = reinterpret_cast<float4*>(cert + pos);
     int c = 0;
     double next = -1.0;
 #pragma unroll
@@ -565,16 +536,14 @@ __global__ __launch_bounds__(kT) void k_cert_build(MapView m, const uint32_t* li
       if (top.pos[u] < 0 || top.pos[u] == int32_t(pos)) continue;
       if (c < kCertK) {
         const float4 q = m.vox_pts[top.pos[u]];
-        r.nbr[c++] = make_float4(q.x, q.y, q.z, __int_as_float(top.pos[u]));
+        out[++c] = make_float4(q.x, q.y, q.z, __int_as_float(top.pos[u]));
       } else if (next < 0.0) {
         next = top.d[u];
       }
     }
-    for (int u = c; u < kCertK; ++u)
-      r.nbr[u] = make_float4(0.0f, 0.0f, 0.0f, __int_as_float(-1));
+    while (c < kCertK) out[++c] = make_float4(0.0f, 0.0f, 0.0f, __int_as_float(-1));
     const double half = 0.5 * (next >= 0.0 ? sqrt(next) : m.v) * (1.0 - 0x1p-20);
-    r.rho = __double2float_rd(half);
-    cert[pos] = r;
+    out[0] = make_float4(p.x, p.y, p.z, __double2float_rd(half));
     const int32_t id = __float_as_int(p.w);
     if (!cov || id < id0) continue;
     double c6[6] = {0, 0, 0, 0, 0, 0};
@@ -913,18 +882,37 @@ __global__ __launch_bounds__(kT) void k_map_cov(MapView m, float4* cov, float4* 
   }
 }
 
+// Bound by the latency of each lane's chain of voxels.  The neighbours come
+// from the query's voxel's row of the neighbour table, or its ghost's (an empty
+// voxel that is neither has nothing within v), read in one go; a hash probe
+// per neighbour took 124 us for 100k queries at k = 5, 62 us now.
 template <int K>
 __global__ __launch_bounds__(kT) void k_map_knn(MapView m, const float* q, int64_t n, int32_t k,
                                                 double r2, int32_t* idx, float* d2,
                                                 int32_t* count) {
+  __shared__ uint32_t rows[kT * kRowWords];
+  uint32_t* lrow = rows + threadIdx.x * kRowWords;
   int64_t i = int64_t(blockIdx.x) * kT + threadIdx.x;
   if (i >= n) return;
   float x = q[i], y = q[n + i], z = q[2 * n + i];
   TopK<K> top;
-  if (isfinite(x) && isfinite(y) && isfinite(z))
-    map_knn_query<K>(m, double(x), double(y), double(z), r2, top);
-  else
-    top.init();
+  top.init();
+  int64_t kx, ky, kz;
+  if (isfinite(x) && isfinite(y) && isfinite(z) && voxel_index(double(x), m.v, &kx) &&
+      voxel_index(double(y), m.v, &ky) && voxel_index(double(z), m.v, &kz)) {
+    int32_t cnt;
+    const int32_t own = map_find(m, kx, ky, kz, &cnt);
+    const int32_t g = own < 0 && m.ghost_ok ? ghost_find(m, kx, ky, kz) : -1;
+    const uint32_t* row = own >= 0 ? m.vox_nbr + int64_t(own) * 26
+                                   : (g >= 0 ? m.gnbr + int64_t(g) * 26 : nullptr);
+    if (row) {
+      load_row(row, lrow);
+      map_knn_row<K>(m, double(x), double(y), double(z), int32_t(kx), int32_t(ky), int32_t(kz),
+                     own >= 0 ? own * m.nmax : 0, cnt, lrow, r2, top);
+    } else if (!m.ghost_ok) {
+      map_knn_query<K>(m, double(x), double(y), double(z), r2, top);
+    }
+  }
   int f = top.found();
   int c = f < k ? f : k;
 #pragma unroll
@@ -942,13 +930,11 @@ __global__ __launch_bounds__(kT) void k_map_knn(MapView m, const float* q, int64
 // voxel key) (sorted[j] = x, y, z, original index bits), runs [seg_start,
 // seg_end) of equal (scan, key), and a hash table from (scan, key) to run
 // index (the scan id is kept in the slot's spare word and mixed into the hash).
+constexpr uint32_t kNoRun = 0xFFFFFFFFu;
+
 struct GridView {
   const Slot* slots;
   const float4* sorted;
-  const uint64_t* keys;       // sorted keys (kEmptyKey for non-finite points)
-  const uint32_t* sid;        // scan id per sorted position (NULL: one scan)
-  const uint32_t* seg_start;
-  const uint32_t* seg_end;
   double v;          // neighbourhood radius (the voxel edge)
   double c;          // grid cell edge (v / 2 when v is a power of two, else v)
   double inv_c;
@@ -958,11 +944,19 @@ struct GridView {
   double mx;         // runs sorted by x up to a quantum: how far a later point of
                      // a run can lie below an earlier one along x (infinity:
                      // runs unordered)
-  const uint32_t* head;       // 1 where a run starts
-  const uint32_t* head_scan;  // exclusive prefix of head: run of j = head_scan + head - 1
+  // The runs, numbered inside eight ranges of sorted positions, one per XCD:
+  // the runs that start in range x are x * run_chunk up to x * run_chunk +
+  // n_runs[16 x] (in no particular order), so that an XCD works through the
+  // cells of its own scans.
+  int64_t run_chunk;
+  const uint32_t* n_runs;
+  const uint64_t* run_key;
+  const uint32_t* run_sid;    // (NULL: one scan)
+  const uint32_t* run_start;
+  const uint32_t* run_end;
+  uint32_t* run_id;           // per sorted point, its run (kNoRun: a non-finite point)
   const uint2* nbt;           // per run, its 27 cells (code (ox+1)*9 + (oy+1)*3 + oz+1) as
                               // (start, count) in sorted; count 0: no run there
-  const uint32_t* n_runs;     // the number of runs (device)
   float4* pk_B;               // the source packed for the align by sorted position
   float2* pk_C;               // (B, C as the align's pack writes them), or null
 };
@@ -1060,7 +1054,7 @@ __global__ __launch_bounds__(kT) void k_apply_perm(const uint32_t* perm, int64_t
 // order (both are lexicographic, stable on input order), in about half the
 // passes.  The range comes from a two-level reduction (no same-address
 // atomics); points without a finite, in-range key sort last in their scan.
-constexpr int kRangeBlocks = 256;
+constexpr int kRangeBlocks = 1024;
 
 // floor(x / v) as voxel_index computes it, through an exact multiply by 1/v
 // when v is a power of two.
@@ -1160,10 +1154,16 @@ __global__ __launch_bounds__(kT) void k_keys_compact(const float* xyz, int64_t n
                                                      double inv_v, int32_t pow2,
                                                      const int64_t* offsets, int32_t S,
                                                      CompactKey ck, uint64_t* keys,
-                                                     uint32_t* vals, uint32_t* zero) {
+                                                     uint32_t* vals, uint32_t* zero,
+                                                     Slot* slots) {
   const int64_t i = int64_t(blockIdx.x) * kT + threadIdx.x;
   if (i >= n) return;
   if (zero) zero[i] = 0u;
+  if (slots) {   // the scan grid's two slots per point, empty
+    const uint4 e = make_uint4(~0u, ~0u, ~0u, ~0u);
+    reinterpret_cast<uint4*>(slots)[2 * i] = e;
+    reinterpret_cast<uint4*>(slots)[2 * i + 1] = e;
+  }
   int32_t s = 0;
   if (offsets) {
     int32_t lo = 0, hi = S;            // offsets[s] <= i < offsets[s+1]
@@ -1190,109 +1190,145 @@ __global__ __launch_bounds__(kT) void k_keys_compact(const float* xyz, int64_t n
   vals[i] = uint32_t(i);
 }
 
-// Sorted compact keys back to full keys (kEmptyKey for the empty ones) and
-// scan ids.
-__global__ __launch_bounds__(kT) void k_keys_expand(const uint64_t* ckeys, int64_t n,
-                                                    CompactKey ck, uint64_t* keys,
-                                                    uint32_t* sid) {
-  const int64_t i = int64_t(blockIdx.x) * kT + threadIdx.x;
-  if (i >= n) return;
-  const uint64_t c = ckeys[i] >> ck.fb;
-  const uint64_t k = c & ((uint64_t(2) << ck.kb) - 1);
-  if (sid) sid[i] = uint32_t(c >> (ck.kb + 1));
-  if (k >> ck.kb) {
-    keys[i] = kEmptyKey;
-  } else {
-    const uint64_t hi = k >> 6;
+// The sorted keys of a scan grid: compact ones, or full keys beside scan ids.
+struct GridKeys {
+  const uint64_t* k;
+  const uint32_t* sid;   // full keys of several scans
+  int32_t compact, multi;
+  CompactKey ck;
+  __device__ bool same(int64_t a, int64_t b) const {
+    if (compact) return k[a] >> ck.fb == k[b] >> ck.fb;
+    return k[a] == k[b] && (!sid || sid[a] == sid[b]);
+  }
+  __device__ bool empty(int64_t j) const {
+    return compact ? ((k[j] >> (ck.fb + ck.kb)) & 1u) != 0 : k[j] == kEmptyKey;
+  }
+  __device__ uint32_t scan(int64_t j) const {
+    if (!multi) return 0u;
+    return compact ? uint32_t(k[j] >> (ck.fb + ck.kb + 1)) : sid[j];
+  }
+  __device__ uint64_t key(int64_t j) const {
+    if (!compact) return k[j];
+    const uint64_t c = (k[j] >> ck.fb) & ((uint64_t(1) << ck.kb) - 1);
+    const uint64_t hi = c >> 6;
     const int64_t hx = int64_t(hi >> (ck.by + ck.bz - 4));
     const int64_t hy = int64_t((hi >> (ck.bz - 2)) & ((uint64_t(1) << (ck.by - 2)) - 1));
     const int64_t hz = int64_t(hi & ((uint64_t(1) << (ck.bz - 2)) - 1));
-    const int64_t kx = ((hx << 2) | int64_t((k >> 4) & 3)) + ck.mx;
-    const int64_t ky = ((hy << 2) | int64_t((k >> 2) & 3)) + ck.my;
-    const int64_t kz = ((hz << 2) | int64_t(k & 3)) + ck.mz;
-    keys[i] = pack_key(kx, ky, kz);
+    return pack_key(((hx << 2) | int64_t((c >> 4) & 3)) + ck.mx,
+                    ((hy << 2) | int64_t((c >> 2) & 3)) + ck.my,
+                    ((hz << 2) | int64_t(c & 3)) + ck.mz);
   }
-}
+};
 
-__global__ __launch_bounds__(kT) void k_grid_heads(const uint64_t* keys, const uint32_t* sid,
-                                                   int64_t n, uint32_t* head) {
-  int64_t j = int64_t(blockIdx.x) * kT + threadIdx.x;
-  if (j >= n) return;
-  uint64_t k = keys[j];
-  bool h = k != kEmptyKey &&
-           (j == 0 || keys[j - 1] != k || (sid && sid[j - 1] != sid[j]));
-  head[j] = h ? 1u : 0u;
-}
-
-__global__ __launch_bounds__(kT) void k_grid_bounds(const uint64_t* keys, const uint32_t* sid,
-                                                    int64_t n, const uint32_t* head,
-                                                    const uint32_t* head_scan,
-                                                    uint32_t* seg_start, uint32_t* seg_end) {
-  int64_t j = int64_t(blockIdx.x) * kT + threadIdx.x;
-  if (j >= n) return;
-  uint64_t k = keys[j];
-  if (k == kEmptyKey) return;
-  uint32_t s = head_scan[j] + head[j] - 1;
-  if (head[j]) seg_start[s] = uint32_t(j);
-  if (j == n - 1 || keys[j + 1] != k || (sid && sid[j + 1] != sid[j]))
-    seg_end[s] = uint32_t(j + 1);
-}
-
-// Sorted points as float4 (and, when order is not null, the sorted order
-// itself: order[j] = the original index of sorted point j), blocks dealt to
-// the XCDs in contiguous ranges (a scan's points stay in the scan's index
-// range, so each XCD gathers from the few MB of its own scans).
-__global__ __launch_bounds__(kT) void k_gather_sorted(const float* xyz, int64_t n,
-                                                      const uint32_t* vals, float4* sorted,
-                                                      uint32_t* order) {
-  const int64_t nb = (n + kT - 1) / kT, chunk = (nb + 7) >> 3;
-  const int64_t j = (int64_t(blockIdx.x & 7) * chunk + (blockIdx.x >> 3)) * kT + threadIdx.x;
-  if ((blockIdx.x >> 3) >= chunk || j >= n) return;
-  uint32_t i = vals[j];
-  sorted[j] = make_float4(xyz[i], xyz[n + i], xyz[2 * n + i], __int_as_float(int32_t(i)));
-  if (order) order[j] = i;
-}
-
-// The run count stays on the device: the grid-wide kernels over runs are
-// persistent grids (kGridBlocks blocks, a multiple of 8) that split the items
-// into eight contiguous ranges, one per XCD, and walk their range in steps
-// of the XCD's blocks.
-constexpr int kGridBlocks = 8 * 1024;
-
-template <class F>
-__device__ inline void xcd_ranges(int64_t total, F f) {
-  const int64_t chunk = (total + 7) >> 3;
-  const int64_t lo = int64_t(blockIdx.x & 7) * chunk, hi = min(lo + chunk, total);
-  const int64_t step = int64_t(gridDim.x >> 3) * kT;
-  for (int64_t t = lo + int64_t(blockIdx.x >> 3) * kT + threadIdx.x; t < hi; t += step) f(t);
-}
-
-// Run r into the slots of its scan (one XCD fills one scan's slots at a time).
-__device__ inline void grid_claim_run(const GridView& g, Slot* slots, int64_t r) {
-  const uint32_t j = g.seg_start[r];
-  const uint64_t key = g.keys[j];
-  const uint32_t sc = g.sid ? g.sid[j] : 0u;
-  uint32_t base, size;
-  grid_part(g, sc, &base, &size);
-  uint32_t h = grid_hash(key_x(key), key_y(key), key_z(key), size);
-  const uint32_t cnt = g.seg_end[r] - j;   // >= 1, so never the empty word
-  // every run is a different cell, so a slot is claimed on its length word
-  // alone (a 32-bit compare-and-swap); key and start follow as plain stores,
-  // read only by later kernels
-  for (uint32_t probe = 0; probe < size; ++probe) {
-    const uint32_t old = atomicCAS(reinterpret_cast<uint32_t*>(&slots[base + h].aux),
-                                   0xFFFFFFFFu, cnt);
-    if (old == 0xFFFFFFFFu) {
-      slots[base + h].key = key;
-      slots[base + h].vox = int32_t(j);
-      return;
+// From the sorted keys to the grid in one launch (blocks dealt to the XCDs in
+// contiguous ranges; a scan's points stay in the scan's index range, so each
+// XCD gathers from, and claims in, the few MB of its own scans): the sorted
+// points as float4 (and, when order is not null, the sorted order itself), the
+// runs of equal (scan, cell), and each run's slot in its scan's stretch of the
+// hash.  A run's end is the next change of cell: in the block's ballots, or,
+// for a run that leaves the block, by doubling steps past it.  (As key
+// expansion, heads, prefix sum, bounds, gather, clearing and claim: ten
+// launches, 28 us at 5k points and 250 us at 4.9M; 9 and 161 us.)
+template <int kPer>
+__global__ __launch_bounds__(kT) void k_grid_runs(GridView g, GridKeys gk, const float* xyz,
+                                                  int64_t n, const uint32_t* vals, Slot* slots,
+                                                  float4* sorted, uint32_t* order,
+                                                  uint32_t* n_runs, uint64_t* run_key,
+                                                  uint32_t* run_sid, uint32_t* run_start,
+                                                  uint32_t* run_end) {
+  constexpr int kWords = kPer * kT / 64;
+  __shared__ uint64_t starts[kWords];
+  __shared__ uint32_t heads[kWords];
+  __shared__ uint32_t base;
+  const int64_t nb = (n + kT * kPer - 1) / (kT * kPer), chunk = (nb + 7) >> 3;
+  const int x = int(blockIdx.x & 7);
+  const int64_t b = x * chunk + (blockIdx.x >> 3);
+  if ((blockIdx.x >> 3) >= chunk || b >= nb) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t j0 = b * (kT * kPer), j1 = min(j0 + int64_t(kT) * kPer, n);
+  uint64_t hb[kPer];
+#pragma unroll
+  for (int r = 0; r < kPer; ++r) {
+    const int64_t j = j0 + r * kT + threadIdx.x;
+    const bool st = j < n && (j == 0 || !gk.same(j, j - 1));
+    const bool hd = st && !gk.empty(j);
+    const uint64_t sb = __ballot(st);
+    hb[r] = __ballot(hd);
+    if (lane == 0) {
+      starts[r * 4 + wave] = sb;
+      heads[r * 4 + wave] = uint32_t(__popcll(hb[r]));
     }
-    h = h + 1 == size ? 0 : h + 1;
+    if (j < n) {
+      const uint32_t i = vals[j];
+      sorted[j] = make_float4(xyz[i], xyz[n + i], xyz[2 * n + i], __int_as_float(int32_t(i)));
+      if (order) order[j] = i;
+      if (gk.empty(j)) g.run_id[j] = kNoRun;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t total = 0;
+    for (int w = 0; w < kWords; ++w) total += heads[w];
+    base = uint32_t(x * g.run_chunk) + (total ? atomicAdd(&n_runs[16 * x], total) : 0u);
+  }
+  __syncthreads();
+  uint32_t before = base;
+#pragma unroll
+  for (int r = 0; r < kPer; ++r) {
+    uint32_t id = before;
+    for (int w = 0; w < 4; ++w) {
+      id += w < wave ? heads[r * 4 + w] : 0u;
+      before += heads[r * 4 + w];
+    }
+    if (!((hb[r] >> lane) & 1u)) continue;
+    id += uint32_t(__popcll(hb[r] & ((uint64_t(1) << lane) - 1)));
+    const int64_t j = j0 + r * kT + threadIdx.x;
+    // the next start in the block's ballots
+    int w = r * 4 + wave;
+    uint64_t m = lane == 63 ? 0ull : starts[w] & (~0ull << (lane + 1));
+    while (!m && ++w < kWords) m = starts[w];
+    int64_t e = m ? j0 + w * 64 + __builtin_ctzll(m) : j1;
+    if (!m && j1 < n && gk.same(j, j1)) {
+      int64_t ok = j1, step = 1;             // ok: in the run
+      while (ok + step < n && gk.same(j, ok + step)) {
+        ok += step;
+        step <<= 1;
+      }
+      for (; step >= 1; step >>= 1)
+        if (ok + step < n && gk.same(j, ok + step)) ok += step;
+      e = ok + 1;
+    }
+    const uint64_t key = gk.key(j);
+    const uint32_t sc = gk.scan(j), cnt = uint32_t(e - j);
+    run_start[id] = uint32_t(j);
+    run_end[id] = uint32_t(e);
+    run_key[id] = key;
+    if (run_sid) run_sid[id] = sc;
+    uint32_t sb, size;
+    grid_part(g, sc, &sb, &size);
+    uint32_t h = grid_hash(key_x(key), key_y(key), key_z(key), size);
+    // every run is a different cell, so a slot is claimed on its length word
+    // alone (a 32-bit compare-and-swap; a length is at least 1, never the empty
+    // word); key and start follow as plain stores, read only by later kernels
+    for (uint32_t probe = 0; probe < size; ++probe) {
+      const uint32_t old = atomicCAS(reinterpret_cast<uint32_t*>(&slots[sb + h].aux),
+                                     0xFFFFFFFFu, cnt);
+      if (old == 0xFFFFFFFFu) {
+        slots[sb + h].key = key;
+        slots[sb + h].vox = int32_t(j);
+        break;
+      }
+      h = h + 1 == size ? 0 : h + 1;
+    }
   }
 }
 
-__global__ __launch_bounds__(kT) void k_grid_claim(GridView g, Slot* slots) {
-  xcd_ranges(*g.n_runs, [&](int64_t r) { grid_claim_run(g, slots, r); });
+// Persistent grids over the runs: at most kGridBlocks blocks, a multiple of 8,
+// each taking the items of its XCD's range of runs in turn.
+constexpr int kGridBlocks = 8 * 1024;
+inline unsigned grid_blocks(int64_t items) {
+  const int64_t nb = ((items + kT - 1) / kT + 7) / 8 * 8;
+  return unsigned(std::min<int64_t>(nb < 8 ? 8 : nb, kGridBlocks));
 }
 
 // Neighbour table of the runs: per run, the (start, count) of the run of the
@@ -1301,26 +1337,32 @@ __global__ __launch_bounds__(kT) void k_grid_claim(GridView g, Slot* slots) {
 // per (run, cell) entry t, the entries in XCD ranges (one XCD probes one
 // scan's stretch of slots at a time); the rows are written with non-temporal
 // stores so that they stream past the L2 holding the slots.
-__device__ inline void grid_nbr_entry(const GridView& g, uint2* nbt, int64_t t) {
-  const int64_t r = t / 27;
-  const int code = int(t - r * 27);
-  const uint32_t s0 = g.seg_start[r];
-  uint32_t a = s0, c = g.seg_end[r] - s0;
+__device__ inline void grid_nbr_entry(const GridView& g, uint2* nbt, uint32_t r, int code) {
+  const uint32_t s0 = g.run_start[r], s1 = g.run_end[r];
+  uint32_t a = s0, c = s1 - s0;
   if (code != 13) {
-    const uint64_t key = g.keys[s0];
-    const uint32_t sc = g.sid ? g.sid[s0] : 0u;
+    const uint64_t key = g.run_key[r];
+    const uint32_t sc = g.run_sid ? g.run_sid[r] : 0u;
     int32_t cnt;
     const int32_t f = grid_find(g, key_x(key) + code / 9 - 1, key_y(key) + (code / 3) % 3 - 1,
                                 key_z(key) + code % 3 - 1, sc, &cnt);
     a = f < 0 ? 0u : uint32_t(f);
     c = f < 0 ? 0u : uint32_t(cnt);
   }
+  const int64_t t = int64_t(r) * 27 + code;
   __builtin_nontemporal_store(a, &nbt[t].x);
   __builtin_nontemporal_store(c, &nbt[t].y);
+  // the run's points learn their run, the 27 threads of its row in turn
+  for (uint32_t j = s0 + uint32_t(code); j < s1; j += 27) g.run_id[j] = r;
 }
 
 __global__ __launch_bounds__(kT) void k_grid_nbr_table(GridView g, uint2* nbt) {
-  xcd_ranges(int64_t(*g.n_runs) * 27, [&](int64_t t) { grid_nbr_entry(g, nbt, t); });
+  const int x = int(blockIdx.x & 7);
+  const int64_t total = int64_t(g.n_runs[16 * x]) * 27, step = int64_t(gridDim.x >> 3) * kT;
+  for (int64_t t = int64_t(blockIdx.x >> 3) * kT + threadIdx.x; t < total; t += step) {
+    const int64_t q = t / 27;
+    grid_nbr_entry(g, nbt, uint32_t(x * g.run_chunk + q), int(t - q * 27));
+  }
 }
 
 // Squared face distance as a float never above the FP64 value (rounded
@@ -1342,9 +1384,9 @@ __device__ inline void grid_cov_run(const GridView& g, int64_t sg, int32_t dense
                                     int32_t* nb_start, int32_t* nb_cnt) {
   const int lane = threadIdx.x;
   __syncthreads();   // the previous run's readers of nb_start and nb_cnt are done
-  const uint32_t s0 = g.seg_start[sg], s1 = g.seg_end[sg];
+  const uint32_t s0 = g.run_start[sg], s1 = g.run_end[sg];
   if (int64_t(s1 - s0) < dense) return;   // sparse runs: the per-point search
-  const uint64_t key = g.keys[s0];
+  const uint64_t key = g.run_key[sg];
   const int64_t kx = key_x(key), ky = key_y(key), kz = key_z(key);
   if (lane < 27) {   // the run's row of the neighbour table
     const uint2 e = g.nbt[sg * 27 + lane];
@@ -1405,11 +1447,9 @@ __global__ __launch_bounds__(64) void k_grid_cov_wave(GridView g, int32_t dense,
                                                       uint8_t* valid) {
   __shared__ int32_t nb_start[27];
   __shared__ int32_t nb_cnt[27];
-  // the runs in eight contiguous ranges, one per XCD; each block of an XCD
-  // takes every (gridDim / 8)-th run of its range
-  const int64_t n_seg = *g.n_runs;
-  const int64_t chunk = (n_seg + 7) >> 3;
-  const int64_t lo = int64_t(blockIdx.x & 7) * chunk, hi = min(lo + chunk, n_seg);
+  // each block of an XCD takes every (gridDim / 8)-th run of its range
+  const int x = int(blockIdx.x & 7);
+  const int64_t lo = x * g.run_chunk, hi = lo + g.n_runs[16 * x];
   for (int64_t sg = lo + (blockIdx.x >> 3); sg < hi; sg += gridDim.x >> 3)
     grid_cov_run<K>(g, sg, dense, n, k, reg, cov6, valid, nb_start, nb_cnt);
 }
@@ -1435,7 +1475,8 @@ __global__ __launch_bounds__(kT, kCovMinWaves) void k_grid_cov(GridView g, int32
   const int64_t j = b * kT + threadIdx.x;
   if ((blockIdx.x >> 3) >= chunk || j >= n) return;
   const float4 me = g.sorted[j];
-  if (g.keys[j] == kEmptyKey) {   // a non-finite point: zero covariance, invalid
+  const uint32_t rid = g.run_id[j];
+  if (rid == kNoRun) {   // a non-finite point: zero covariance, invalid
     const int64_t i = __float_as_int(me.w);
 #pragma unroll
     for (int t = 0; t < 6; ++t) cov6[t * n + i] = 0.0f;
@@ -1447,7 +1488,7 @@ __global__ __launch_bounds__(kT, kCovMinWaves) void k_grid_cov(GridView g, int32
   const double qx = me.x, qy = me.y, qz = me.z;
   // the cells around the point's own cell (the cell of its run's key: the
   // same coordinates and cell edge) from its run's row of the neighbour table
-  const uint2* row = g.nbt + int64_t(g.head_scan[j] + g.head[j] - 1) * 27;
+  const uint2* row = g.nbt + int64_t(rid) * 27;
   if (dense > 0 && int32_t(row[13].y) >= dense) return;
   TopK<K> top;
   knn_cells27<K>(qx, qy, qz, g.c, g.inv_c, g.pow2 != 0, g.v * g.v, g.sorted, int32_t(j), g.mx,
@@ -1475,6 +1516,142 @@ __global__ __launch_bounds__(kT, kCovMinWaves) void k_grid_cov(GridView g, int32
   cov6[4 * n + i] = f4;
   cov6[5 * n + i] = f5;
   valid[i] = ok ? 1 : 0;
+}
+
+// Covariances of a small scan, 32 lanes per point.  One lane per point leaves
+// most of the chip idle below about 32k points (5000 points are 79 waves, each
+// as long as its slowest chain of cells: 60 us; 17.5 us here; k = 5 at 20k
+// points 54 -> 39 us, k = 10 at 13k points 86 -> 54 us).  First the lanes share the points of the own cell, each keeping
+// its own K best, and the group merges them; then every lane ranks one of the
+// other 26 cells against the merged K-th best (entries it holds from the start,
+// with no place, so only better points enter), and the group merges again.
+// The list is the K best by (d2, id) of the same candidates, so the results
+// are those of k_grid_cov, bit for bit.
+constexpr int64_t kWideCovMax = 32 * 1024;
+constexpr int kCovLanes = 32;
+
+// The K best of the lanes' sorted lists into out, in every lane; entries
+// without a place count as absent.
+template <int K>
+__device__ inline void merge_lists(TopK<K>& own, TopK<K>& out) {
+#pragma unroll
+  for (int s = 0; s < K; ++s) {
+    const bool have = own.pos[0] >= 0;
+    double d = have ? own.d[0] : __builtin_inf();
+    int32_t id = have ? own.id[0] : INT_MAX, pos = have ? own.pos[0] : -1;
+#pragma unroll
+    for (int w = kCovLanes / 2; w >= 1; w >>= 1) {
+      const double od = __shfl_xor(d, w, kCovLanes);
+      const int32_t oi = __shfl_xor(id, w, kCovLanes), op = __shfl_xor(pos, w, kCovLanes);
+      if (rank_less(od, oi, d, id)) {
+        d = od;
+        id = oi;
+        pos = op;
+      }
+    }
+    out.d[s] = d;
+    out.id[s] = id;
+    out.pos[s] = pos;
+    if (have && own.pos[0] == pos) {   // the lane that held it drops it
+#pragma unroll
+      for (int q = 0; q + 1 < K; ++q) {
+        own.d[q] = own.d[q + 1];
+        own.id[q] = own.id[q + 1];
+        own.pos[q] = own.pos[q + 1];
+      }
+      own.pos[K - 1] = -1;
+    }
+  }
+}
+
+template <int K>
+__global__ __launch_bounds__(kT) void k_grid_cov_wide(GridView g, int64_t n, int32_t k,
+                                                      int32_t reg, float* cov6, uint8_t* valid) {
+  constexpr int kPts = kT / kCovLanes;
+  __shared__ int32_t s_pos[kPts][K];   // the K nearest of the block's points (-1: none)
+  const int64_t j = int64_t(blockIdx.x) * kPts + threadIdx.x / kCovLanes;
+  const int lane = threadIdx.x & (kCovLanes - 1);
+  float4 me = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  if (j < n) me = g.sorted[j];
+  const bool fin = j < n && isfinite(me.x) && isfinite(me.y) && isfinite(me.z);
+  TopK<K> top;
+  top.init();
+  if (fin) {
+    const uint2* row = g.nbt + int64_t(g.run_id[j]) * 27;
+    const double px = me.x, py = me.y, pz = me.z, c = g.c, r2 = g.v * g.v;
+    const double tx = g.pow2 ? px * g.inv_c : px / c;
+    const double fx = floor(tx), fy = floor(g.pow2 ? py * g.inv_c : py / c),
+                 fz = floor(g.pow2 ? pz * g.inv_c : pz / c);
+    // the own cell, its points dealt to the lanes
+    TopK<K> own;
+    own.init();
+    Query q = make_query(px, py, pz, r2);
+    const uint2 me_run = row[13];
+    for (uint32_t u = me_run.x + uint32_t(lane); u < me_run.x + me_run.y; u += kCovLanes) {
+      const float4 p = g.sorted[u];
+      const double d = dist2(double(p.x), double(p.y), double(p.z), px, py, pz);
+      if (d <= r2) own.push(d, __float_as_int(p.w), int32_t(u));
+    }
+    merge_lists<K>(own, top);
+    // one other cell per lane, from the list's last entry on
+    const double bound = fmin(r2, top.bound());
+    const double slack = 1e-7 * c;
+    const int ox = lane / 9 - 1, oy = (lane / 3) % 3 - 1, oz = lane % 3 - 1;
+    auto gap = [&](int o, double p, double f) {
+      return o == 0 ? 0.0f
+                    : lb_down_sq(fmax(o < 0 ? p - f * c - slack : (f + 1.0) * c - p - slack, 0.0));
+    };
+    const float lb = (gap(ox, px, fx) + gap(oy, py, fy)) + gap(oz, pz, fz);
+#pragma unroll
+    for (int s = 0; s < K; ++s) {
+      own.d[s] = top.d[K - 1];
+      own.id[s] = top.id[K - 1];
+      own.pos[s] = -1;
+    }
+    bool any = false;
+    if (lane < 27 && lane != 13 && double(lb) <= bound) {
+      const uint2 e = row[lane];
+      if (e.y) {
+        q.bound_f = screen_bound(bound, q.m);
+        const float w = fminf(fmaxf(float(e.y) * (float(tx - fx) - float(ox)), 0.0f), float(e.y));
+        scan_run_x<K>(g.sorted, int32_t(e.x), int32_t(e.y),
+                      int32_t(e.x) + min(int32_t(w), int32_t(e.y)), q, r2, g.mx, own);
+        any = own.pos[0] >= 0;
+      }
+    }
+    // (a ballot of the group's half of the wave)
+    if ((__ballot(any) >> (threadIdx.x & 32)) & 0xFFFFFFFFull) {
+      if (lane == 31) own = top;   // the first list takes part as a lane of its own
+      merge_lists<K>(own, top);
+    }
+  }
+  if (lane == 0) {
+#pragma unroll
+    for (int s = 0; s < K; ++s) s_pos[threadIdx.x / kCovLanes][s] = top.pos[s];
+  }
+  __syncthreads();
+  // the FP64 covariances by one lane per point, all in the first wave (by every
+  // wave for its own points they would take four times the issue slots)
+  const int64_t jj = int64_t(blockIdx.x) * kPts + threadIdx.x;
+  if (threadIdx.x >= kPts || jj >= n) return;
+  int found = 0;
+#pragma unroll
+  for (int s = 0; s < K; ++s) {
+    top.pos[s] = s_pos[threadIdx.x][s];
+    found += top.pos[s] >= 0 ? 1 : 0;
+  }
+  double c6[6] = {0, 0, 0, 0, 0, 0};
+  const bool ok = found >= k;
+  if (ok) regularised_cov<K>(top, k, [&](int32_t pos) { return g.sorted[pos]; }, c6, reg);
+  const int64_t i = __float_as_int(g.sorted[jj].w);
+  float cf[6];
+#pragma unroll
+  for (int t = 0; t < 6; ++t) {
+    cf[t] = float(c6[t]);
+    cov6[t * n + i] = cf[t];
+  }
+  valid[i] = ok ? 1 : 0;
+  write_packed(g, jj, cf, ok);
 }
 
 // Probe lengths of the held keys: summed per block before the two atomics (one
@@ -1600,41 +1777,26 @@ far_status_t dispatch_k(int32_t k, F&& f) {
   return f(std::integral_constant<int, 32>());
 }
 
-// Keys, stable sort and runs of a point batch: the common front half of the
-// insert and of the scan covariances.
-struct Runs {
-  uint64_t* keys;
-  uint32_t* vals;
-  uint32_t* head;
-  uint32_t* head_scan;
-  uint32_t* seg_start;
-  uint32_t* seg_end;
-  uint32_t* counters;   // [0] non-finite, [1] out of range, [2] runs
-};
-
-far_status_t build_runs(const float* xyz, int64_t n, double v, hipStream_t st, Scratch& scr,
-                        Runs& r) {
+// Points sorted (stably) by full voxel key: the path of key ranges too wide for
+// compact keys.
+far_status_t sort_full_keys(const float* xyz, int64_t n, double v, hipStream_t st, Scratch& scr,
+                            uint64_t** keys, uint32_t** vals) {
   uint64_t* keys_alt;
-  uint32_t* vals_alt;
-  FAR_TRY(scr.get(&r.keys, size_t(n)));
-  FAR_TRY(scr.get(&r.vals, size_t(n)));
+  uint32_t *vals_alt, *counters;
+  FAR_TRY(scr.get(keys, size_t(n)));
+  FAR_TRY(scr.get(vals, size_t(n)));
   FAR_TRY(scr.get(&keys_alt, size_t(n)));
   FAR_TRY(scr.get(&vals_alt, size_t(n)));
-  FAR_TRY(scr.get(&r.head, size_t(n)));
-  FAR_TRY(scr.get(&r.head_scan, size_t(n)));
-  FAR_TRY(scr.get(&r.seg_start, size_t(n)));
-  FAR_TRY(scr.get(&r.seg_end, size_t(n)));
-  FAR_TRY(scr.get(&r.counters, 4));
-  FAR_HIP(hipMemsetAsync(r.counters, 0, 4 * sizeof(uint32_t), st));
-  k_keys<<<blocks_for(n), kT, 0, st>>>(xyz, n, v, r.keys, r.vals, r.counters);
+  FAR_TRY(scr.get(&counters, 2));
+  FAR_HIP(hipMemsetAsync(counters, 0, 2 * sizeof(uint32_t), st));
+  k_keys<<<blocks_for(n), kT, 0, st>>>(xyz, n, v, *keys, *vals, counters);
   FAR_HIP(hipGetLastError());
-  FAR_TRY(radix_sort_pairs(r.keys, r.vals, keys_alt, vals_alt, n, kKeyBits, st, scr));
-  k_heads<<<blocks_for(n), kT, 0, st>>>(r.keys, n, r.head);
-  FAR_HIP(hipGetLastError());
-  FAR_TRY(scan_exclusive(r.head, r.head_scan, n, r.counters + 2, st, scr));
-  k_seg_bounds<<<blocks_for(n), kT, 0, st>>>(r.keys, n, r.head, r.head_scan, r.seg_start,
-                                              r.seg_end);
-  FAR_HIP(hipGetLastError());
+  bool alt = false;
+  FAR_TRY(radix_sort_pairs(*keys, *vals, keys_alt, vals_alt, n, 64, st, scr, &alt));
+  if (alt) {
+    *keys = keys_alt;
+    *vals = vals_alt;
+  }
   return FAR_OK;
 }
 
@@ -1662,13 +1824,11 @@ far_status_t fine_build(far_map_s* m, hipStream_t st) {
   const int64_t n = m->n_points;
   Scratch scr(st);
   uint64_t *keys, *keys_alt;
-  uint32_t *vals, *vals_alt, *head, *head_scan, *seg_start, *seg_end, *counters;
+  uint32_t *vals, *vals_alt, *seg_start, *seg_end, *counters;
   FAR_TRY(scr.get(&keys, size_t(n)));
   FAR_TRY(scr.get(&keys_alt, size_t(n)));
   FAR_TRY(scr.get(&vals, size_t(n)));
   FAR_TRY(scr.get(&vals_alt, size_t(n)));
-  FAR_TRY(scr.get(&head, size_t(n)));
-  FAR_TRY(scr.get(&head_scan, size_t(n)));
   FAR_TRY(scr.get(&seg_start, size_t(n)));
   FAR_TRY(scr.get(&seg_end, size_t(n)));
   FAR_TRY(scr.get(&counters, 4));
@@ -1678,11 +1838,8 @@ far_status_t fine_build(far_map_s* m, hipStream_t st) {
                                             vals, counters);
   FAR_HIP(hipGetLastError());
   FAR_TRY(radix_sort_pairs(keys, vals, keys_alt, vals_alt, n, kKeyBits, st, scr));
-  k_heads<<<blocks_for(n), kT, 0, st>>>(keys, n, head);
-  FAR_HIP(hipGetLastError());
-  FAR_TRY(scan_exclusive(head, head_scan, n, counters + 2, st, scr));
-  k_seg_bounds<<<blocks_for(n), kT, 0, st>>>(keys, n, head, head_scan, seg_start, seg_end);
-  FAR_HIP(hipGetLastError());
+  FAR_TRY(scan_flags(RunFlags{SortedKeys{keys, kEmptyKey}, n, seg_start, seg_end}, n,
+                     counters + 2, st, scr));
   uint32_t h_cnt[4];
   FAR_HIP(hipMemcpyAsync(h_cnt, counters, sizeof(h_cnt), hipMemcpyDeviceToHost, st));
   FAR_HIP(hipStreamSynchronize(st));
@@ -1969,16 +2126,12 @@ far_status_t far_map_insert(far_map_t m, const float* xyz, int64_t n, const int3
     return FAR_E_INVALID;
   }
   if (none) return FAR_OK;
-  uint64_t *keys, *keys_alt;
-  uint32_t *vals, *vals_alt, *seg_start, *seg_end, *is_new, *acc_flag, *id_local, *seg_changed;
+  uint64_t* keys;
+  uint32_t *vals, *seg_start, *seg_end, *is_new, *acc_flag, *id_local, *seg_changed;
   int32_t *seg_vox, *acc_pos, *seg_newcount;
   InsertCounts* counts;
   const size_t nn = size_t(n);
   FAR_TRY(scr.get(&counts, 1));
-  FAR_TRY(scr.get(&keys, nn));
-  FAR_TRY(scr.get(&keys_alt, nn));
-  FAR_TRY(scr.get(&vals, nn));
-  FAR_TRY(scr.get(&vals_alt, nn));
   FAR_TRY(scr.get(&seg_start, nn));
   FAR_TRY(scr.get(&seg_end, nn));
   FAR_TRY(scr.get(&seg_vox, nn));
@@ -1989,24 +2142,29 @@ far_status_t far_map_insert(far_map_t m, const float* xyz, int64_t n, const int3
   FAR_TRY(scr.get(&seg_newcount, nn));
   FAR_TRY(scr.get(&seg_changed, nn));
   FAR_HIP(hipMemsetAsync(counts, 0, sizeof(InsertCounts), st));
-  int e2 = 0;
-  const int32_t pow2 = std::frexp(v, &e2) == 0.5 ? 1 : 0;
   if (fits) {
+    uint64_t* keys_alt;
+    uint32_t* vals_alt;
+    FAR_TRY(scr.get(&keys, nn));
+    FAR_TRY(scr.get(&keys_alt, nn));
+    FAR_TRY(scr.get(&vals, nn));
+    FAR_TRY(scr.get(&vals_alt, nn));
+    int e2 = 0;
+    const int32_t pow2 = std::frexp(v, &e2) == 0.5 ? 1 : 0;
     k_keys_compact<<<blocks_for(n), kT, 0, st>>>(xyz, n, v, 1.0 / v, pow2, nullptr, 1, ck, keys,
-                                                  vals, acc_flag);
+                                                  vals, acc_flag, nullptr);
+    FAR_HIP(hipGetLastError());
+    bool alt = false;
+    FAR_TRY(radix_sort_pairs(keys, vals, keys_alt, vals_alt, n, ck.kb + 1, st, scr, &alt));
+    if (alt) {
+      keys = keys_alt;
+      vals = vals_alt;
+    }
   } else {   // a range that needs the full keys
     FAR_HIP(hipMemsetAsync(acc_flag, 0, nn * sizeof(uint32_t), st));
-    k_keys<<<blocks_for(n), kT, 0, st>>>(xyz, n, v, keys, vals, counts->pad);
+    FAR_TRY(sort_full_keys(xyz, n, v, st, scr, &keys, &vals));
   }
-  FAR_HIP(hipGetLastError());
-  bool alt = false;
-  FAR_TRY(radix_sort_pairs(keys, vals, keys_alt, vals_alt, n, fits ? ck.kb + 1 : 64, st, scr,
-                           &alt));
-  if (alt) {
-    keys = keys_alt;
-    vals = vals_alt;
-  }
-  const SortedKeys sk{keys, 0, fits ? uint64_t(1) << ck.kb : kEmptyKey};
+  const SortedKeys sk{keys, fits ? uint64_t(1) << ck.kb : kEmptyKey};
   FAR_TRY(scan_flags(RunFlags{sk, n, seg_start, seg_end}, n, &counts->n_seg, st, scr));
   const int64_t vox_room = m->voxel_cap - m->n_voxels;
   const int64_t room = m->p.point_capacity - m->n_points;
@@ -2075,142 +2233,102 @@ far_status_t far_map_knn(far_map_t m, const float* q, int64_t n, int32_t k, doub
   });
 }
 
-// Voxel grid of a batch of scans with cells of edge `cell` (points grouped by
-// scan, then by cell key): sorted points, runs and a hash of the runs.
-// *oor receives the number of points whose cell key is out of range (the
-// grid is then not built).
-// The runs of a scan grid sorted by (scan, key) through compact keys (see
-// k_key_range), and each run by x up to 2^-*fb_out cells (*fb_out = 0: runs
-// unordered).  *used = false when the batch has no finite point or its key
-// range needs more than 62 bits with the scan id; *oor receives the points
-// whose keys leave [-2^20, 2^20) (nothing else is done then).
-static far_status_t build_runs_compact(const float* xyz, const int64_t* offsets, int32_t S_,
-                                       int64_t n, double cell, hipStream_t st, Scratch& scr,
-                                       Runs& r, uint32_t** sid_out, bool* used, uint32_t* oor,
-                                       int* fb_out) {
-  *used = false;
-  *oor = 0;
-  *fb_out = 0;
-  CompactKey ck;
-  FAR_TRY(compact_layout(xyz, n, cell, S_, st, scr, &ck, used, oor, nullptr));
-  if (!*used) return FAR_OK;
-  *used = false;
-  int e2 = 0;
-  const int32_t pow2 = std::frexp(cell, &e2) == 0.5 ? 1 : 0;
-  const int key_bits = (S_ > 1 ? ceil_log2(S_) : 0) + ck.kb + 1;
-  // x bits: one more radix pass of 8 bits (8 to 15 bits), within 62 in all
-  ck.fb = std::min(((key_bits + 15) / 8) * 8 - key_bits, 62 - key_bits);
-  const int bits = key_bits + ck.fb;
-  uint64_t *ckeys, *ckeys_alt;
-  uint32_t* vals_alt;
-  FAR_TRY(scr.get(&ckeys, size_t(n)));
-  FAR_TRY(scr.get(&ckeys_alt, size_t(n)));
-  FAR_TRY(scr.get(&r.keys, size_t(n)));
-  FAR_TRY(scr.get(&r.vals, size_t(n)));
-  FAR_TRY(scr.get(&vals_alt, size_t(n)));
-  FAR_TRY(scr.get(&r.head, size_t(n)));
-  FAR_TRY(scr.get(&r.head_scan, size_t(n)));
-  FAR_TRY(scr.get(&r.seg_start, size_t(n)));
-  FAR_TRY(scr.get(&r.seg_end, size_t(n)));
-  FAR_TRY(scr.get(&r.counters, 4));
-  uint32_t* sid = nullptr;
-  if (S_ > 1) FAR_TRY(scr.get(&sid, size_t(n)));
-  FAR_HIP(hipMemsetAsync(r.counters, 0, 4 * sizeof(uint32_t), st));
-  k_keys_compact<<<blocks_for(n), kT, 0, st>>>(xyz, n, cell, 1.0 / cell, pow2,
-                                                S_ > 1 ? offsets : nullptr, S_, ck, ckeys,
-                                                r.vals, nullptr);
-  FAR_HIP(hipGetLastError());
-  bool alt = false;
-  FAR_TRY(radix_sort_pairs(ckeys, r.vals, ckeys_alt, vals_alt, n, bits, st, scr, &alt));
-  if (alt) r.vals = vals_alt;
-  k_keys_expand<<<blocks_for(n), kT, 0, st>>>(alt ? ckeys_alt : ckeys, n, ck, r.keys, sid);
-  FAR_HIP(hipGetLastError());
-  k_grid_heads<<<blocks_for(n), kT, 0, st>>>(r.keys, sid, n, r.head);
-  FAR_HIP(hipGetLastError());
-  FAR_TRY(scan_exclusive(r.head, r.head_scan, n, r.counters + 2, st, scr));
-  k_grid_bounds<<<blocks_for(n), kT, 0, st>>>(r.keys, sid, n, r.head, r.head_scan,
-                                              r.seg_start, r.seg_end);
-  FAR_HIP(hipGetLastError());
-  *sid_out = sid;
-  *used = true;
-  *fb_out = ck.fb;
-  return FAR_OK;
-}
-
+// Voxel grid of a batch of scans with cells of edge `cell`: the points sorted
+// by (scan, cell, x), through compact keys (see k_key_range) or, when the
+// batch's key range needs more than 62 bits with the scan id, by full keys and
+// then by scan (runs not ordered by x); the runs, a hash of them, and each
+// run's neighbour cells.  *oor receives the points whose keys leave [-2^20,
+// 2^20) (the grid is then not built).
 static far_status_t build_grid(const float* xyz, const int64_t* offsets, int32_t S_, int64_t n,
                                double v, double cell, hipStream_t st, Scratch& scr,
                                GridView* out, uint32_t* oor, uint32_t* order = nullptr,
                                float4* sorted_in = nullptr) {
-  Runs r;
-  uint32_t* sid = nullptr;
-  bool compact = false;
-  int fb = 0;
-  FAR_TRY(build_runs_compact(xyz, offsets, S_, n, cell, st, scr, r, &sid, &compact, oor, &fb));
+  CompactKey ck{};
+  bool compact = false, none = false;
+  FAR_TRY(compact_layout(xyz, n, cell, S_, st, scr, &ck, &compact, oor, &none));
   if (*oor > 0) return FAR_OK;
-  if (!compact) FAR_TRY(build_runs(xyz, n, cell, st, scr, r));
-  uint64_t* keys = r.keys;
-  uint32_t* vals = r.vals;
-  if (S_ > 1 && !compact) {
-    // second stable sort, by scan id, keeps the key order inside every scan
-    uint64_t *sid_key, *sid_alt, *keys2;
-    uint32_t *perm, *perm_alt, *vals2;
-    FAR_TRY(scr.get(&sid_key, size_t(n)));
-    FAR_TRY(scr.get(&sid_alt, size_t(n)));
-    FAR_TRY(scr.get(&perm, size_t(n)));
-    FAR_TRY(scr.get(&perm_alt, size_t(n)));
-    FAR_TRY(scr.get(&keys2, size_t(n)));
-    FAR_TRY(scr.get(&vals2, size_t(n)));
-    FAR_TRY(scr.get(&sid, size_t(n)));
-    k_scan_ids<<<blocks_for(n), kT, 0, st>>>(r.vals, n, offsets, S_, sid_key, perm);
-    FAR_HIP(hipGetLastError());
-    FAR_TRY(radix_sort_pairs(sid_key, perm, sid_alt, perm_alt, n, ceil_log2(S_), st, scr));
-    k_apply_perm<<<blocks_for(n), kT, 0, st>>>(perm, n, r.keys, r.vals, keys2, vals2,
-                                               sid_key, sid);
-    FAR_HIP(hipGetLastError());
-    keys = keys2;
-    vals = vals2;
-    k_grid_heads<<<blocks_for(n), kT, 0, st>>>(keys, sid, n, r.head);
-    FAR_HIP(hipGetLastError());
-    FAR_TRY(scan_exclusive(r.head, r.head_scan, n, r.counters + 2, st, scr));
-    k_grid_bounds<<<blocks_for(n), kT, 0, st>>>(keys, sid, n, r.head, r.head_scan,
-                                                r.seg_start, r.seg_end);
-    FAR_HIP(hipGetLastError());
-  }
-  if (!compact) {   // keys out of range are found by the full-key pass only
-    uint32_t h_cnt[4];
-    FAR_HIP(hipMemcpyAsync(h_cnt, r.counters, sizeof(h_cnt), hipMemcpyDeviceToHost, st));
-    FAR_HIP(hipStreamSynchronize(st));
-    *oor = h_cnt[1];
-    if (h_cnt[1] > 0) return FAR_OK;
-  }
-  // The number of runs stays on the device (r.counters[2]): the kernels below
-  // are launched for one run per point and read it.
-  // two slots per point, each scan's in its own stretch (n < 2^31)
-  const int64_t n_slots = 2 * n;
-  Slot* slots;
-  float4* sorted;
-  FAR_TRY(scr.get(&slots, size_t(n_slots)));
-  if (sorted_in)
-    sorted = sorted_in;   // the caller's packed A words: the sorted points are exactly those
-  else
-    FAR_TRY(scr.get(&sorted, size_t(n)));
-  FAR_HIP(hipMemsetAsync(slots, 0xFF, size_t(n_slots) * sizeof(Slot), st));
-  k_gather_sorted<<<unsigned(((blocks_for(n) + 7) / 8) * 8), kT, 0, st>>>(xyz, n, vals, sorted,
-                                                                        order);
-  FAR_HIP(hipGetLastError());
   int e2 = 0;
   const int32_t pow2 = std::frexp(cell, &e2) == 0.5 ? 1 : 0;
+  const size_t nn = size_t(n);
+  const int64_t n_slots = 2 * n;   // two slots per point, each scan's in its own stretch
+  Slot* slots;
+  uint64_t *keys, *run_key;
+  uint32_t *vals, *run_start, *run_end, *run_id, *n_runs, *run_sid = nullptr, *sid = nullptr;
+  uint2* nbt;
+  FAR_TRY(scr.get(&n_runs, 8 * 16));
+  FAR_TRY(scr.get(&slots, size_t(n_slots)));
+  FAR_TRY(scr.get(&run_key, nn));
+  FAR_TRY(scr.get(&run_start, nn));
+  FAR_TRY(scr.get(&run_end, nn));
+  FAR_TRY(scr.get(&run_id, nn));
+  if (S_ > 1) FAR_TRY(scr.get(&run_sid, nn));
+  FAR_HIP(hipMemsetAsync(n_runs, 0, 8 * 16 * sizeof(uint32_t), st));
+  float4* sorted = sorted_in;   // the caller's packed A words: the sorted points are exactly those
+  if (!sorted) FAR_TRY(scr.get(&sorted, nn));
+  if (compact) {
+    uint64_t* keys_alt;
+    uint32_t* vals_alt;
+    FAR_TRY(scr.get(&keys, nn));
+    FAR_TRY(scr.get(&keys_alt, nn));
+    FAR_TRY(scr.get(&vals, nn));
+    FAR_TRY(scr.get(&vals_alt, nn));
+    const int key_bits = (S_ > 1 ? ceil_log2(S_) : 0) + ck.kb + 1;
+    // x bits: one more radix pass of 8 bits (8 to 15 bits), within 62 in all
+    ck.fb = std::min(((key_bits + 15) / 8) * 8 - key_bits, 62 - key_bits);
+    k_keys_compact<<<blocks_for(n), kT, 0, st>>>(xyz, n, cell, 1.0 / cell, pow2,
+                                                  S_ > 1 ? offsets : nullptr, S_, ck, keys, vals,
+                                                  nullptr, slots);
+    FAR_HIP(hipGetLastError());
+    bool alt = false;
+    FAR_TRY(radix_sort_pairs(keys, vals, keys_alt, vals_alt, n, key_bits + ck.fb, st, scr, &alt));
+    if (alt) {
+      keys = keys_alt;
+      vals = vals_alt;
+    }
+  } else {
+    FAR_HIP(hipMemsetAsync(slots, 0xFF, size_t(n_slots) * sizeof(Slot), st));
+    FAR_TRY(sort_full_keys(xyz, n, cell, st, scr, &keys, &vals));
+    if (S_ > 1) {
+      // second stable sort, by scan id, keeps the key order inside every scan
+      uint64_t *sid_key, *sid_alt, *keys2;
+      uint32_t *perm, *perm_alt, *vals2;
+      FAR_TRY(scr.get(&sid_key, nn));
+      FAR_TRY(scr.get(&sid_alt, nn));
+      FAR_TRY(scr.get(&perm, nn));
+      FAR_TRY(scr.get(&perm_alt, nn));
+      FAR_TRY(scr.get(&keys2, nn));
+      FAR_TRY(scr.get(&vals2, nn));
+      FAR_TRY(scr.get(&sid, nn));
+      k_scan_ids<<<blocks_for(n), kT, 0, st>>>(vals, n, offsets, S_, sid_key, perm);
+      FAR_HIP(hipGetLastError());
+      FAR_TRY(radix_sort_pairs(sid_key, perm, sid_alt, perm_alt, n, ceil_log2(S_), st, scr));
+      k_apply_perm<<<blocks_for(n), kT, 0, st>>>(perm, n, keys, vals, keys2, vals2, sid_key, sid);
+      FAR_HIP(hipGetLastError());
+      keys = keys2;
+      vals = vals2;
+    }
+  }
+  FAR_TRY(scr.get(&nbt, nn * 27));
   // a later point of an x-sorted run lies at most one quantum (2^-fb cells,
   // plus the rounding of x / cell) below an earlier one; twice that is kept
-  const double mx = compact && fb > 0 ? std::ldexp(cell, 1 - fb) : HUGE_VAL;
-  uint2* nbt;
-  FAR_TRY(scr.get(&nbt, size_t(n) * 27));
-  *out = GridView{slots, sorted, keys, sid, r.seg_start, r.seg_end, v, cell, 1.0 / cell, pow2,
-                  S_ > 1 ? offsets : nullptr, uint32_t(n_slots), mx, r.head, r.head_scan,
-                  nbt, r.counters + 2, nullptr, nullptr};
-  k_grid_claim<<<kGridBlocks, kT, 0, st>>>(*out, slots);
+  const double mx = compact && ck.fb > 0 ? std::ldexp(cell, 1 - ck.fb) : HUGE_VAL;
+  // four positions a lane where the blocks' adds on the run counts would
+  // otherwise be many
+  const int per = n > (1 << 20) ? 4 : 1;
+  const int64_t nb = (n + kT * per - 1) / (kT * per);
+  *out = GridView{slots, sorted, v, cell, 1.0 / cell, pow2, S_ > 1 ? offsets : nullptr,
+                  uint32_t(n_slots), mx, ((nb + 7) >> 3) * kT * per, n_runs, run_key, run_sid,
+                  run_start, run_end, run_id, nbt, nullptr, nullptr};
+  const GridKeys gk{keys, sid, compact ? 1 : 0, S_ > 1 ? 1 : 0, ck};
+  const unsigned grid = unsigned(((nb + 7) / 8) * 8);
+  if (per == 4)
+    k_grid_runs<4><<<grid, kT, 0, st>>>(*out, gk, xyz, n, vals, slots, sorted, order, n_runs,
+                                        run_key, run_sid, run_start, run_end);
+  else
+    k_grid_runs<1><<<grid, kT, 0, st>>>(*out, gk, xyz, n, vals, slots, sorted, order, n_runs,
+                                        run_key, run_sid, run_start, run_end);
   FAR_HIP(hipGetLastError());
-  k_grid_nbr_table<<<kGridBlocks, kT, 0, st>>>(*out, nbt);
+  k_grid_nbr_table<<<grid_blocks(n * 27), kT, 0, st>>>(*out, nbt);
   FAR_HIP(hipGetLastError());
   return FAR_OK;
 }
@@ -2243,6 +2361,14 @@ static far_status_t scan_cov_impl(const float* xyz, const int64_t* offsets, int3
   // non-finite branch of k_grid_cov, zero covariance and invalid)
   return dispatch_k(k, [&](auto KK) -> far_status_t {
     constexpr int K = decltype(KK)::value;
+    if constexpr (K <= 10) {
+      if (dense == 0 && n <= kWideCovMax) {
+        k_grid_cov_wide<K><<<blocks_for(n * kCovLanes), kT, 0, st>>>(g, n, k, g_cov_reg, cov6,
+                                                                     valid);
+        FAR_HIP(hipGetLastError());
+        return FAR_OK;
+      }
+    }
     const int64_t cov_grid = ((blocks_for(n) + 7) / 8) * 8;
     k_grid_cov<K><<<unsigned(cov_grid), kT, 0, st>>>(g, dense, n, k, g_cov_reg, cov6, valid);
     FAR_HIP(hipGetLastError());

@@ -12,6 +12,7 @@
 // whole align (state init + max_iters iterations) is captured once into a HIP
 // graph per argument set and replayed.
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -31,6 +32,15 @@ constexpr int kTileMin = 128;
 constexpr int kTileMax = 512;
 constexpr int kVals = 29;     // 21 H + 6 b + cost + count
 constexpr int kStride = 32;   // partial row stride (doubles)
+
+// How far a one-scan align has come, for the host that enqueues it: the solve
+// of iteration `step` (from 1) stores it in word 0 of the slot, and kAlignDone
+// once the scan is done (a captured align has none).
+constexpr uint32_t kAlignDone = 0xFFFFu;
+struct Progress {
+  uint32_t* word;
+  uint32_t step;
+};
 
 struct Params {
   double r2;        // min(tau, v)^2
@@ -1111,41 +1121,9 @@ __device__ inline double tile_sum(const double* partial, int64_t t, int v) {
     return partial[t * kStride + v];
 }
 
-// Sums of scan s's tile partials and its Gauss-Newton update, by the first 256
-// threads of a block (all threads call it): eight groups of 32 lanes, group g
-// sums tiles begin+g, begin+g+8, ... of the scan in that order, then the eight
-// group sums are added in group order; the loads go out sixteen at a time (the
-// sums wait on them).
-template <bool kHalf>
-__device__ void reduce_solve_scan(int32_t s, const int32_t* begin, const double* partial,
-                                  double* T, double* ctr, int32_t* done,
-                                  far_align_stats_t* stats, const Params& prm, int32_t solve) {
-  __shared__ double part[8][kVals];
-  __shared__ double lin[kVals];
-  const int g = threadIdx.x >> 5, v = threadIdx.x & 31;
-  if (g < 8 && v < kVals) {
-    double acc = 0.0;
-    const int32_t t1 = begin[s + 1];
-    int32_t t = begin[s] + g;
-    for (; t + 8 * 15 < t1; t += 8 * 16) {
-      double x[16];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) x[u] = tile_sum<kHalf>(partial, t + 8 * u, v);
-#pragma unroll
-      for (int u = 0; u < 16; ++u) acc += x[u];
-    }
-    for (; t < t1; t += 8) acc += tile_sum<kHalf>(partial, t, v);
-    part[g][v] = acc;
-  }
-  __syncthreads();
-  if (threadIdx.x < kVals) {
-    double acc = 0.0;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) acc += part[q][threadIdx.x];
-    lin[threadIdx.x] = acc;
-  }
-  __syncthreads();
-  if (threadIdx.x != 0) return;
+// Gauss-Newton update of scan s from its 29 sums, by one lane.
+__device__ void solve_scan(int32_t s, const double* lin, double* T, double* ctr, int32_t* done,
+                           far_align_stats_t* stats, const Params& prm, int32_t solve) {
   far_align_stats_t& st = stats[s];
   double H[36], b[6];
   int u = 0;
@@ -1219,17 +1197,59 @@ __device__ void reduce_solve_scan(int32_t s, const int32_t* begin, const double*
   }
 }
 
+// Sums of scan s's tile partials and its Gauss-Newton update, by the first 256
+// threads of a block (all threads call it): eight groups of 32 lanes, group g
+// sums tiles begin+g, begin+g+8, ... of the scan in that order, then the eight
+// group sums are added in group order; the loads go out sixteen at a time (the
+// sums wait on them).
+template <bool kHalf>
+__device__ void reduce_solve_scan(int32_t s, const int32_t* begin, const double* partial,
+                                  double* T, double* ctr, int32_t* done,
+                                  far_align_stats_t* stats, const Params& prm, int32_t solve,
+                                  const Progress& pg) {
+  __shared__ double part[8][kVals];
+  __shared__ double lin[kVals];
+  const int g = threadIdx.x >> 5, v = threadIdx.x & 31;
+  if (g < 8 && v < kVals) {
+    double acc = 0.0;
+    const int32_t t1 = begin[s + 1];
+    int32_t t = begin[s] + g;
+    for (; t + 8 * 15 < t1; t += 8 * 16) {
+      double x[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) x[u] = tile_sum<kHalf>(partial, t + 8 * u, v);
+#pragma unroll
+      for (int u = 0; u < 16; ++u) acc += x[u];
+    }
+    for (; t < t1; t += 8) acc += tile_sum<kHalf>(partial, t, v);
+    part[g][v] = acc;
+  }
+  __syncthreads();
+  if (threadIdx.x < kVals) {
+    double acc = 0.0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) acc += part[q][threadIdx.x];
+    lin[threadIdx.x] = acc;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  solve_scan(s, lin, T, ctr, done, stats, prm, solve);
+  if (pg.word)
+    __hip_atomic_store(pg.word, done[s] ? kAlignDone : pg.step, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 __global__ __launch_bounds__(256) void k_reduce_solve(int32_t S, const int32_t* begin,
                                                       const double* partial, double* T,
                                                       double* ctr, int32_t* done,
                                                       far_align_stats_t* stats, Params prm,
-                                                      int32_t solve, uint32_t* bins) {
+                                                      int32_t solve, uint32_t* bins, Progress pg) {
   // the next iteration's queue starts empty (this iteration's search has
   // read its bins)
   if (bins && blockIdx.x == 0 && threadIdx.x < kBins) bins[threadIdx.x] = 0u;
   const int32_t s = blockIdx.x;
   if (s >= S || done[s]) return;
-  reduce_solve_scan<false>(s, begin, partial, T, ctr, done, stats, prm, solve);
+  reduce_solve_scan<false>(s, begin, partial, T, ctr, done, stats, prm, solve, pg);
 }
 
 // ---------------------------------------------------------------- wide jobs
@@ -1332,7 +1352,7 @@ __global__ __launch_bounds__(kWide) void k_wide_iter(
     const uint32_t* __restrict__ tile_lo, const uint32_t* __restrict__ tile_hi, int64_t n_half,
     const int32_t* __restrict__ begin, double* T, double* ctr, int32_t* done, Params prm,
     double* partial, uint32_t* counter, far_align_stats_t* stats, int32_t solve, int32_t first,
-    int32_t* corr, float* grad_src, int64_t n_src, int32_t* prev) {
+    int32_t* corr, float* grad_src, int64_t n_src, int32_t* prev, Progress pg) {
   constexpr int kNV = kGrad ? 14 : kVals;
   __shared__ double q_p[kWidePts][3];
   __shared__ double q_d[kWidePts];
@@ -1437,7 +1457,7 @@ __global__ __launch_bounds__(kWide) void k_wide_iter(
     if (!s_last) return;
     __threadfence();
     if (tid == 0) counter[s] = 0u;
-    reduce_solve_scan<true>(s, begin, partial, T, ctr, done, stats, prm, solve);
+    reduce_solve_scan<true>(s, begin, partial, T, ctr, done, stats, prm, solve, pg);
   }
 }
 
@@ -1669,6 +1689,7 @@ struct Job {
   double* g_cost = nullptr;
   int64_t* g_n = nullptr;
   int32_t tile = kTileDefault; // points per tile (the map's schedule)
+  HostSlot* slot = nullptr;    // a one-scan align the host waits for: its progress, or null
   const uint32_t* order = nullptr;   // caller's locality order of the source, or null
   // the source already packed by the caller (A, B, C as the pack writes
   // them, in a locality order), or null
@@ -1765,7 +1786,7 @@ far_status_t launch_lin(int32_t tile, int64_t grid, hipStream_t st, const MapVie
 // One iteration (or linearisation, or gradient) of a wide job.
 template <class Real, bool kGrad>
 far_status_t launch_wide(hipStream_t st, const MapView& mv, const AlignWS* w, int64_t max_tiles,
-                         const Job& j, bool first) {
+                         const Job& j, bool first, Progress pg = {}) {
   const float4* pA = j.in_A ? j.in_A : w->pA;
   const float4* pB = j.in_A ? j.in_B : w->pB;
   const float2* pC = j.in_A ? j.in_C : w->pC;
@@ -1775,7 +1796,7 @@ far_status_t launch_wide(hipStream_t st, const MapView& mv, const AlignWS* w, in
     k_wide_iter<Real, kGrad, decltype(no_sa)::value><<<grid, kWide, 0, st>>>(
         mv, pA, pB, pC, w->tile_scan, w->tile_lo, w->tile_hi, n_half, w->begin, j.T, w->ctr,
         w->done, j.prm, w->partial, w->counter, j.stats, j.c_fixed ? 0 : 1, first ? 1 : 0,
-        j.corr, kGrad ? j.grad_src : nullptr, j.n_total, kGrad ? nullptr : w->prev);
+        j.corr, kGrad ? j.grad_src : nullptr, j.n_total, kGrad ? nullptr : w->prev, pg);
   };
   if (j.prm.sa_off)
     go(std::true_type());
@@ -1811,6 +1832,26 @@ far_status_t enqueue_setup(const AlignWS* w, const Job& j, int64_t max_tiles,
                                             j.stats, w->done, w->ctr);
   FAR_HIP(hipGetLastError());
   return FAR_OK;
+}
+
+// Before iteration `it` (from 0) of an align whose progress the host sees:
+// false when the scan is done, so that the iterations left are not launched
+// (each would be up to four launches of kernels that find nothing to do, about
+// 4 us of host time each).  The host stays at most kAhead iterations ahead,
+// enough to keep the device busy; it gives up watching after a millisecond and
+// enqueues what is left.
+constexpr uint32_t kAhead = 2;
+
+bool wait_progress(HostSlot* slot, int it) {
+  const auto t0 = std::chrono::steady_clock::now();
+  for (int spin = 0;; ++spin) {
+    const uint32_t p = __atomic_load_n(slot->host, __ATOMIC_ACQUIRE);
+    if (p == kAlignDone) return false;
+    if (uint32_t(it) <= p + kAhead) return true;
+    if ((spin & 255) == 255 &&
+        std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(1))
+      return true;
+  }
 }
 
 // Enqueue the whole job (setup, locality packing, iterations) on st; a
@@ -1866,25 +1907,21 @@ far_status_t enqueue(far_map_s* m, AlignWS* w, const Job& j, int64_t max_tiles, 
     return FAR_OK;
   }
   const int iters = j.c_fixed ? 1 : j.prm.max_iters;
-  if (wide) {
-    for (int it = 0; it < iters; ++it) {
-      TimedScope ts(FAR_TIME_LINEARIZE, st);
-      FAR_TRY((fp64 ? launch_wide<double, false>(st, mv, w, max_tiles, j, it == 0)
-                    : launch_wide<float, false>(st, mv, w, max_tiles, j, it == 0)));
-    }
-    return FAR_OK;
-  }
   for (int it = 0; it < iters; ++it) {
-    {
-      TimedScope ts(FAR_TIME_LINEARIZE, st);
-      if (j.precision == FAR_PREC_FP64)
-        FAR_TRY((launch_lin<double, false>(j.tile, grid, st, mv, w, max_tiles, j, it == 0)));
-      else
-        FAR_TRY((launch_lin<float, false>(j.tile, grid, st, mv, w, max_tiles, j, it == 0)));
+    if (j.slot && !wait_progress(j.slot, it)) break;
+    const Progress pg{j.slot ? j.slot->dev : nullptr, uint32_t(it + 1)};
+    TimedScope ts(FAR_TIME_LINEARIZE, st);
+    if (wide) {
+      FAR_TRY((fp64 ? launch_wide<double, false>(st, mv, w, max_tiles, j, it == 0, pg)
+                    : launch_wide<float, false>(st, mv, w, max_tiles, j, it == 0, pg)));
+      continue;
     }
+    FAR_TRY((fp64 ? launch_lin<double, false>(j.tile, grid, st, mv, w, max_tiles, j, it == 0)
+                  : launch_lin<float, false>(j.tile, grid, st, mv, w, max_tiles, j, it == 0)));
+    ts.stop();
     k_reduce_solve<<<unsigned(j.S), 256, 0, st>>>(j.S, w->begin, w->partial, j.T, w->ctr,
                                                   w->done, j.stats, j.prm, j.c_fixed ? 0 : 1,
-                                                  it + 1 < iters ? w->q_count : nullptr);
+                                                  it + 1 < iters ? w->q_count : nullptr, pg);
     FAR_HIP(hipGetLastError());
   }
   return FAR_OK;
@@ -1915,7 +1952,19 @@ far_status_t run_job(far_map_s* m, const Job& j0, hipStream_t st, bool use_graph
   if (j.prm.fine_nn) FAR_TRY(fine_build(m, st));
   (void)device_cu_count();   // query the device outside any capture
   if (one) FAR_TRY(enqueue_setup(w, j, max_tiles, one, st));
-  if (!use_graph || st == nullptr || timing_on()) return enqueue(m, w, j, max_tiles, !one, st);
+  // a one-scan align that is launched directly reports its progress
+  HostSlot* const slot = j.slot;
+  j.slot = nullptr;
+  auto direct = [&]() {
+    if (slot) slot->take(st);
+    if (slot && slot->host) {
+      slot->pending = st;
+      slot->busy = true;
+      j.slot = slot;
+    }
+    return enqueue(m, w, j, max_tiles, !one, st);
+  };
+  if (!use_graph || st == nullptr || timing_on()) return direct();
   // the captured map view holds the fine-index flag: a graph captured with a
   // different flag must not be replayed
   const void* key[12] = {j.src, j.offsets, j.cov6, j.valid, j.T, j.stats, j.c_fixed, j.corr,
@@ -1936,7 +1985,7 @@ far_status_t run_job(far_map_s* m, const Job& j0, hipStream_t st, bool use_graph
     if (memcmp(w->pending, key, sizeof(key)) != 0 && memcmp(w->pending2, key, sizeof(key)) != 0) {
       memcpy(w->pending2, w->pending, sizeof(key));
       memcpy(w->pending, key, sizeof(key));
-      return enqueue(m, w, j, max_tiles, !one, st);
+      return direct();
     }
     hit = w->cap[0].used <= w->cap[1].used ? &w->cap[0] : &w->cap[1];
     if (hit->exec) {
@@ -2052,8 +2101,7 @@ far_status_t far_gicp_linearize(far_map_t m, const float* src, const float* cov6
         make_params(m, tau, kappa, 0.0, 1, 0, precision), precision_of(precision)};
   FAR_TRY(run_job(m, j, st, false, &one));
   far_align_stats_t hs;
-  FAR_HIP(hipMemcpyAsync(&hs, w->stats, sizeof(hs), hipMemcpyDeviceToHost, st));
-  FAR_HIP(hipStreamSynchronize(st));
+  FAR_TRY(fetch(st, &hs, w->stats, sizeof(hs)));
   lin_from_stats(hs, out);
   return FAR_OK;
 }
@@ -2146,8 +2194,7 @@ far_status_t far_gicp_gradient(far_map_t m, const float* src, const float* cov6,
     FAR_TRY(run_job(m, j, st, false, &one));
   }
   double g[14];
-  FAR_HIP(hipMemcpyAsync(g, w->gsum, sizeof(g), hipMemcpyDeviceToHost, st));
-  FAR_HIP(hipStreamSynchronize(st));
+  FAR_TRY(fetch(st, g, w->gsum, sizeof(g)));
   for (int q = 0; q < 12; ++q) grad_T[q] = g[q];
   twist_from_grad(g, T, cc, grad_twist);
   if (cost) *cost = g[12];
@@ -2212,10 +2259,11 @@ far_status_t far_gicp_align(far_map_t m, const float* src, const float* cov6,
         make_params(m, params->tau, params->kappa, params->eps, params->max_iters,
                     params->recenter, params->precision),
         precision_of(params->precision)};
+  HostSlot slot;   // outlives the kernels that report to it: they end before the fetch
+  j.slot = &slot;
   FAR_TRY(run_job(m, j, st, true, &one));
-  FAR_HIP(hipMemcpyAsync(T_out, w->T, 16 * sizeof(double), hipMemcpyDeviceToHost, st));
-  FAR_HIP(hipMemcpyAsync(&hs, w->stats, sizeof(hs), hipMemcpyDeviceToHost, st));
-  FAR_HIP(hipStreamSynchronize(st));
+  FAR_TRY(fetch(st, T_out, w->T, 16 * sizeof(double), &hs, w->stats, sizeof(hs)));
+  slot.busy = false;
   if (stats) *stats = hs;
   return far_status_t(hs.status);
 }

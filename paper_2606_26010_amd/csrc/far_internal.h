@@ -336,6 +336,36 @@ inline size_t radix_sort_scratch_bytes(int64_t n) {
   return hist + 8 * sums + 4096;
 }
 
+// ---------------------------------------------------------------- host slots
+// Small results reach the host through pinned slots: a one-block kernel writes
+// them and then a ticket, and the host watches the ticket.  (A copy to the
+// caller's own memory is staged by the runtime and ends in a stream wait:
+// @HS0@ us from the last kernel's end to the caller against @HS1@.)  The slots are one
+// allocation of kHostSlots, made at first use, handed out one per call in
+// flight under a lock, and given back by far_scratch_release while none is in
+// use; a call that finds none free copies and waits as before.
+constexpr int kHostSlots = 64;
+constexpr size_t kSlotBytes = 1024;       // the ticket's line, then the words
+constexpr size_t kSlotData = kSlotBytes - 64;
+
+struct HostSlot {
+  uint32_t* host = nullptr;   // null: none free
+  uint32_t* dev = nullptr;    // the same words as kernels address them
+  uint32_t ticket = 0;        // unique to this use of the slot
+  hipStream_t pending = nullptr;
+  bool busy = false;          // kernels that write the slot may be in flight on `pending`
+  HostSlot() = default;
+  HostSlot(const HostSlot&) = delete;
+  HostSlot& operator=(const HostSlot&) = delete;
+  ~HostSlot();
+  void take(hipStream_t st);  // leaves host null when none is free or st is capturing
+};
+
+// Copies bytes (multiples of 4; b may be null) from device memory to the host
+// when everything enqueued on st before is done, and waits for them.
+far_status_t fetch(hipStream_t st, void* a_host, const void* a, size_t a_bytes,
+                   void* b_host = nullptr, const void* b = nullptr, size_t b_bytes = 0);
+
 // ---------------------------------------------------------------- primitives
 // Stable LSD radix sort of (key, value) pairs by key bits [0, bits); the
 // *_alt buffers are scratch of the same size.  With in_alt NULL the result

@@ -1941,8 +1941,7 @@ static far_status_t compact_layout(const float* xyz, int64_t n, double cell, int
   k_key_range<<<nb, kT, 0, st>>>(xyz, n, cell, 1.0 / cell, pow2, rng);
   FAR_HIP(hipGetLastError());
   uint32_t h[7];
-  FAR_HIP(hipMemcpyAsync(h, rng, sizeof(h), hipMemcpyDeviceToHost, st));
-  FAR_HIP(hipStreamSynchronize(st));
+  FAR_TRY(fetch(st, h, rng, sizeof(h)));
   *oor = h[6];
   if (h[6] > 0) return FAR_OK;
   if (h[0] == 0) {
@@ -2194,8 +2193,7 @@ far_status_t far_map_insert(far_map_t m, const float* xyz, int64_t n, const int3
   FAR_TRY(certs_build(m, m->n_voxels + std::min(n, vox_room), m->n_points + n_add, m->cert_mark,
                       m->cert_gen, counts, m->cov, m->n_points, n_add, st, scr));
   InsertCounts h;
-  FAR_HIP(hipMemcpyAsync(&h, counts, sizeof(h), hipMemcpyDeviceToHost, st));
-  FAR_HIP(hipStreamSynchronize(st));
+  FAR_TRY(fetch(st, &h, counts, sizeof(h)));
   if (int64_t(h.n_new) > vox_room) {
     set_error("far_map_insert: %lld new voxels exceed the voxel capacity %lld",
               (long long)h.n_new, (long long)m->voxel_cap);
@@ -2462,8 +2460,7 @@ far_status_t far_voxel_downsample(const float* xyz, int64_t n, double v, float* 
   FAR_TRY(scan_flags(DownsampleFlags{xyz, n, slots, slot_of, cnt, out, keep}, n, cnt + 1, st,
                      scr));
   uint32_t h[2];
-  FAR_HIP(hipMemcpyAsync(h, cnt, sizeof(h), hipMemcpyDeviceToHost, st));
-  FAR_HIP(hipStreamSynchronize(st));
+  FAR_TRY(fetch(st, h, cnt, sizeof(h)));
   if (h[0] > 0) {
     set_error("far_voxel_downsample: %u points have voxel keys outside [-2^20, 2^20)", h[0]);
     return FAR_E_INVALID;
@@ -2619,8 +2616,7 @@ far_status_t far_asmd_caps(const float* xyz_sensor, const float* xyz_map, int64_
       FAR_HIP(hipGetLastError());
     }
     uint32_t h[3];
-    FAR_HIP(hipMemcpyAsync(h, counters, sizeof(h), hipMemcpyDeviceToHost, st));
-    FAR_HIP(hipStreamSynchronize(st));
+    FAR_TRY(fetch(st, h, counters, sizeof(h)));
     if (h[2] > 0) {
       set_error("far_asmd_caps: %u near points have voxel keys outside [-2^20, 2^20)", h[2]);
       return FAR_E_INVALID;
@@ -2684,8 +2680,7 @@ far_status_t far_map_evict(far_map_t m, const double c[3], double radius, int64_
                                    vkeep, nvox, xyz, cv, loc},
                        n, &counts->n_acc, st, scr));
   }
-  FAR_HIP(hipMemcpyAsync(&h, counts, sizeof(h), hipMemcpyDeviceToHost, st));
-  FAR_HIP(hipStreamSynchronize(st));
+  FAR_TRY(fetch(st, &h, counts, sizeof(h)));
   const int64_t n_keep = h.n_acc, v_keep = h.n_seg;
   if (n_keep == n) return FAR_OK;
   TimedScope ts2(FAR_TIME_EVICT, st);
@@ -2711,8 +2706,7 @@ far_status_t far_map_evict(far_map_t m, const double c[3], double radius, int64_
   FAR_TRY(links_update(m, v_keep, m->voxel_cap, counts, seg_vox, nullptr, nullptr, st));
   FAR_TRY(certs_build(m, v_keep, n_keep, nullptr, 0, counts, nullptr, 0, 0, st, scr));
   ts2.stop();
-  FAR_HIP(hipMemcpyAsync(&h, counts, sizeof(h), hipMemcpyDeviceToHost, st));
-  FAR_HIP(hipStreamSynchronize(st));
+  FAR_TRY(fetch(st, &h, counts, sizeof(h)));
   ghosts_take(m, h.ghosts);
   m->n_points = n_keep;
   m->n_voxels = v_keep;
@@ -2739,9 +2733,7 @@ far_status_t far_map_stats(far_map_t m, far_map_stats_t* out, far_stream_t strea
   FAR_HIP(hipGetLastError());
   unsigned long long h_sum = 0;
   uint32_t h_max = 0;
-  FAR_HIP(hipMemcpyAsync(&h_sum, sum, sizeof(h_sum), hipMemcpyDeviceToHost, st));
-  FAR_HIP(hipMemcpyAsync(&h_max, maxp, sizeof(h_max), hipMemcpyDeviceToHost, st));
-  FAR_HIP(hipStreamSynchronize(st));
+  FAR_TRY(fetch(st, &h_sum, sum, sizeof(h_sum), &h_max, maxp, sizeof(h_max)));
   out->n_points = m->n_points;
   out->n_voxels = m->n_voxels;
   out->table_slots = m->slots;

@@ -4,6 +4,9 @@
 // The insert needs a *stable* grouping of points by voxel key so that each
 // voxel's candidates are visited in input order (the sequential capped-insert
 // semantics); an LSD radix sort whose every pass is stable gives exactly that.
+#include <atomic>
+#include <chrono>
+#include <cstring>
 #include <mutex>
 #include <utility>
 #include <vector>
@@ -483,6 +486,116 @@ far_status_t scratch_pool(hipMemPool_t* out) {
   return FAR_OK;
 }
 
+// ---------------------------------------------------------------- host slots
+namespace {
+struct HostSlots {
+  std::mutex mu;
+  char* host = nullptr;
+  char* dev = nullptr;
+  uint64_t used = 0;   // bit per slot
+  std::atomic<uint32_t> ticket{0};
+};
+HostSlots& host_slots() {
+  static HostSlots h;
+  return h;
+}
+
+// Words of a, then b, into the slot, then the ticket: a system-scope release
+// behind a barrier, so that the host that sees the ticket sees the words.
+__global__ __launch_bounds__(256) void k_publish(const uint32_t* a, int32_t na, const uint32_t* b,
+                                                 int32_t nb, uint32_t* slot, uint32_t ticket) {
+  for (int32_t i = threadIdx.x; i < na + nb; i += blockDim.x)
+    slot[16 + i] = i < na ? a[i] : b[i - na];
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0)
+    __hip_atomic_store(slot, ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+}  // namespace
+
+void HostSlot::take(hipStream_t st) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();   // (the legacy stream while another stream captures)
+    return;
+  }
+  HostSlots& h = host_slots();
+  std::lock_guard<std::mutex> lk(h.mu);
+  if (!h.host) {
+    void *p = nullptr, *d = nullptr;
+    if (hipHostMalloc(&p, kHostSlots * kSlotBytes, hipHostMallocPortable | hipHostMallocMapped) !=
+        hipSuccess) {
+      (void)hipGetLastError();
+      return;
+    }
+    if (hipHostGetDevicePointer(&d, p, 0) != hipSuccess) {
+      (void)hipGetLastError();
+      (void)hipHostFree(p);
+      return;
+    }
+    memset(p, 0, kHostSlots * kSlotBytes);
+    h.host = static_cast<char*>(p);
+    h.dev = static_cast<char*>(d);
+  }
+  if (~h.used == 0) return;
+  const int i = __builtin_ctzll(~h.used);
+  h.used |= uint64_t(1) << i;
+  host = reinterpret_cast<uint32_t*>(h.host + size_t(i) * kSlotBytes);
+  dev = reinterpret_cast<uint32_t*>(h.dev + size_t(i) * kSlotBytes);
+  *host = 0u;   // no ticket, no progress (no kernel writes a free slot)
+  do {
+    ticket = ++h.ticket;
+  } while (ticket == 0);
+}
+
+HostSlot::~HostSlot() {
+  if (!host) return;
+  if (busy) (void)hipStreamSynchronize(pending);   // nothing writes a slot given back
+  HostSlots& h = host_slots();
+  std::lock_guard<std::mutex> lk(h.mu);
+  const size_t i = size_t(reinterpret_cast<char*>(host) - h.host) / kSlotBytes;
+  h.used &= ~(uint64_t(1) << i);
+}
+
+far_status_t fetch(hipStream_t st, void* a_host, const void* a, size_t a_bytes, void* b_host,
+                   const void* b, size_t b_bytes) {
+  HostSlot slot;
+  if (a_bytes + b_bytes <= kSlotData) slot.take(st);
+  if (!slot.host) {
+    FAR_HIP(hipMemcpyAsync(a_host, a, a_bytes, hipMemcpyDeviceToHost, st));
+    if (b) FAR_HIP(hipMemcpyAsync(b_host, b, b_bytes, hipMemcpyDeviceToHost, st));
+    FAR_HIP(hipStreamSynchronize(st));
+    return FAR_OK;
+  }
+  slot.pending = st;
+  slot.busy = true;
+  k_publish<<<1, 256, 0, st>>>(static_cast<const uint32_t*>(a), int32_t(a_bytes / 4),
+                               static_cast<const uint32_t*>(b), int32_t(b_bytes / 4), slot.dev,
+                               slot.ticket);
+  FAR_HIP(hipGetLastError());
+  // watch for two milliseconds, then let the runtime wait (and report faults)
+  const auto t0 = std::chrono::steady_clock::now();
+  bool seen = false;
+  for (int spin = 0; !seen; ++spin) {
+    seen = __atomic_load_n(slot.host, __ATOMIC_ACQUIRE) == slot.ticket;
+    if (!seen && (spin & 255) == 255 &&
+        std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(2))
+      break;
+  }
+  if (!seen) {
+    FAR_HIP(hipStreamSynchronize(st));
+    if (__atomic_load_n(slot.host, __ATOMIC_ACQUIRE) != slot.ticket) {
+      set_error("internal: a result did not reach its host slot");
+      return FAR_E_HIP;
+    }
+  }
+  slot.busy = false;
+  const char* w = reinterpret_cast<const char*>(slot.host) + 64;
+  memcpy(a_host, w, a_bytes);
+  if (b) memcpy(b_host, w + a_bytes, b_bytes);
+  return FAR_OK;
+}
+
 // ---------------------------------------------------------------- timing
 namespace {
 struct Timing {
@@ -517,6 +630,12 @@ far_status_t far_scratch_release(void) {
   std::lock_guard<std::mutex> lk(P.mu);
   for (hipMemPool_t p : P.pool)
     if (p) FAR_HIP(hipMemPoolTrimTo(p, 0));
+  far::HostSlots& h = far::host_slots();
+  std::lock_guard<std::mutex> lk2(h.mu);
+  if (h.host && h.used == 0) {
+    FAR_HIP(hipHostFree(h.host));
+    h.host = h.dev = nullptr;
+  }
   return FAR_OK;
 }
 

@@ -2243,6 +2243,9 @@ static far_status_t build_grid(const float* xyz, const int64_t* offsets, int32_t
                                float4* sorted_in = nullptr) {
   CompactKey ck{};
   bool compact = false, none = false;
+  // per point: two slots (32 B), 27 cells (216), run arrays (24), keys and
+  // values twice (24), sorted point (16), and the sort's tables and small words
+  FAR_TRY(scr.reserve(size_t(n) * (32 + 216 + 24 + 24 + 16 + 2) + (size_t(1) << 20)));
   FAR_TRY(compact_layout(xyz, n, cell, S_, st, scr, &ck, &compact, oor, &none));
   if (*oor > 0) return FAR_OK;
   int e2 = 0;

@@ -452,6 +452,7 @@ namespace {
 struct Pools {
   std::mutex mu;
   std::vector<hipMemPool_t> pool;   // per device id, null until first use
+  std::vector<std::vector<void*>> kept;   // per device id, chunks of the null stream
 };
 Pools& pools() {
   static Pools p;
@@ -459,13 +460,34 @@ Pools& pools() {
 }
 }  // namespace
 
-far_status_t scratch_pool(hipMemPool_t* out) {
+void scratch_return(hipStream_t stream, size_t bytes, void* p) {
+  int dev = 0;
+  if (!stream && bytes == kScratchChunk && hipGetDevice(&dev) == hipSuccess) {
+    Pools& P = pools();
+    std::lock_guard<std::mutex> lk(P.mu);
+    if (size_t(dev) < P.kept.size() && P.kept[dev].size() < kScratchKept) {
+      P.kept[dev].push_back(p);
+      return;
+    }
+  }
+  (void)hipFreeAsync(p, stream);
+}
+
+far_status_t scratch_take(hipStream_t stream, size_t bytes, void** out) {
   *out = nullptr;
   int dev = 0;
   FAR_HIP(hipGetDevice(&dev));
   Pools& P = pools();
-  std::lock_guard<std::mutex> lk(P.mu);
-  if (size_t(dev) >= P.pool.size()) P.pool.resize(size_t(dev) + 1, nullptr);
+  std::unique_lock<std::mutex> lk(P.mu);
+  if (size_t(dev) >= P.pool.size()) {
+    P.pool.resize(size_t(dev) + 1, nullptr);
+    P.kept.resize(size_t(dev) + 1);
+  }
+  if (!stream && bytes == kScratchChunk && !P.kept[dev].empty()) {
+    *out = P.kept[dev].back();
+    P.kept[dev].pop_back();
+    return FAR_OK;
+  }
   if (!P.pool[dev]) {
     hipMemPoolProps props{};
     props.allocType = hipMemAllocationTypePinned;
@@ -482,7 +504,9 @@ far_status_t scratch_pool(hipMemPool_t* out) {
     }
     P.pool[dev] = p;
   }
-  *out = P.pool[dev];
+  hipMemPool_t pool = P.pool[dev];
+  lk.unlock();
+  FAR_HIP(hipMallocFromPoolAsync(out, bytes, pool, stream));
   return FAR_OK;
 }
 
@@ -628,6 +652,17 @@ extern "C" {
 far_status_t far_scratch_release(void) {
   far::Pools& P = far::pools();
   std::lock_guard<std::mutex> lk(P.mu);
+  // the kept chunks back to their pools first, behind the work that used them
+  int here = 0;
+  FAR_HIP(hipGetDevice(&here));
+  for (size_t d = 0; d < P.kept.size(); ++d) {
+    if (P.kept[d].empty()) continue;
+    FAR_HIP(hipSetDevice(int(d)));
+    for (void* p : P.kept[d]) (void)hipFreeAsync(p, nullptr);
+    P.kept[d].clear();
+    (void)hipStreamSynchronize(nullptr);
+    FAR_HIP(hipSetDevice(here));
+  }
   for (hipMemPool_t p : P.pool)
     if (p) FAR_HIP(hipMemPoolTrimTo(p, 0));
   far::HostSlots& h = far::host_slots();

@@ -234,12 +234,6 @@ __global__ __launch_bounds__(256) void k_setup(SingleArgs one, int64_t* offsets,
 // [2,3,0,1], row_half_mirror, row_mirror: each pairs a lane with a partner
 // holding the other half of its group), the two cross-row levels shuffles.
 // Partners add the same two values, so every lane ends with the same sum.
-template <int kCtrl>
-__device__ inline double dpp_partner(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), kCtrl, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), kCtrl, 0xF, 0xF, false);
-  return __hiloint2double(hi, lo);
-}
 __device__ inline double wave_sum(double v) {
   v += dpp_partner<0xB1>(v);
   v += dpp_partner<0x4E>(v);
@@ -1121,6 +1115,23 @@ __device__ inline double tile_sum(const double* partial, int64_t t, int v) {
     return partial[t * kStride + v];
 }
 
+// The sum of value v over tiles t, t + 8, ... below t1 in that order.  The
+// loads go out sixteen at a time, the last ones too, at clamped tiles (a loop
+// over the remainder waited for each load in turn: up to fifteen memory round
+// trips, 3.4 us of k_reduce_solve's 14.1 on the 64-scan batch).
+template <bool kHalf>
+__device__ inline double strided_sum(const double* partial, int32_t t, int32_t t1, int v) {
+  double acc = 0.0;
+  for (; t < t1; t += 8 * 16) {
+    double x[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) x[u] = tile_sum<kHalf>(partial, min(t + 8 * u, t1 - 1), v);
+#pragma unroll
+    for (int u = 0; u < 16; ++u) acc = t + 8 * u < t1 ? acc + x[u] : acc;
+  }
+  return acc;
+}
+
 // Gauss-Newton update of scan s from its 29 sums, by one lane.
 __device__ void solve_scan(int32_t s, const double* lin, double* T, double* ctr, int32_t* done,
                            far_align_stats_t* stats, const Params& prm, int32_t solve) {
@@ -1200,8 +1211,7 @@ __device__ void solve_scan(int32_t s, const double* lin, double* T, double* ctr,
 // Sums of scan s's tile partials and its Gauss-Newton update, by the first 256
 // threads of a block (all threads call it): eight groups of 32 lanes, group g
 // sums tiles begin+g, begin+g+8, ... of the scan in that order, then the eight
-// group sums are added in group order; the loads go out sixteen at a time (the
-// sums wait on them).
+// group sums are added in group order.
 template <bool kHalf>
 __device__ void reduce_solve_scan(int32_t s, const int32_t* begin, const double* partial,
                                   double* T, double* ctr, int32_t* done,
@@ -1211,17 +1221,7 @@ __device__ void reduce_solve_scan(int32_t s, const int32_t* begin, const double*
   __shared__ double lin[kVals];
   const int g = threadIdx.x >> 5, v = threadIdx.x & 31;
   if (g < 8 && v < kVals) {
-    double acc = 0.0;
-    const int32_t t1 = begin[s + 1];
-    int32_t t = begin[s] + g;
-    for (; t + 8 * 15 < t1; t += 8 * 16) {
-      double x[16];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) x[u] = tile_sum<kHalf>(partial, t + 8 * u, v);
-#pragma unroll
-      for (int u = 0; u < 16; ++u) acc += x[u];
-    }
-    for (; t < t1; t += 8) acc += tile_sum<kHalf>(partial, t, v);
+    const double acc = strided_sum<kHalf>(partial, begin[s] + g, begin[s + 1], v);
     part[g][v] = acc;
   }
   __syncthreads();
@@ -1269,7 +1269,6 @@ __global__ __launch_bounds__(256) void k_reduce_solve(int32_t S, const int32_t* 
 // and each later one about 45 us in four; 34 and 19 us in one.
 constexpr int kWide = 512;        // lanes per block: 16 searches at once
 constexpr int kWidePts = 64;
-constexpr int kWideLanes = 32;
 
 // The nearest map point of one query by 32 lanes (lane in [0, 32)), continuing
 // from the candidate in top, the same in every lane; the result in every lane.
@@ -1298,17 +1297,10 @@ __device__ inline void nn_wide(const MapView& m, const Params& prm, double px, d
       }
     }
   }
-#pragma unroll
-  for (int d = kWideLanes / 2; d >= 1; d >>= 1) {
-    const double od = __shfl_xor(top.d[0], d, kWideLanes);
-    const int32_t oi = __shfl_xor(top.id[0], d, kWideLanes);
-    const int32_t op = __shfl_xor(top.pos[0], d, kWideLanes);
-    if (rank_less(od, oi, top.d[0], top.id[0])) {
-      top.d[0] = od;
-      top.id[0] = oi;
-      top.pos[0] = op;
-    }
-  }
+  const int w = group_best(top.d[0], top.id[0]);
+  top.d[0] = __shfl(top.d[0], w, kGroup);
+  top.id[0] = __shfl(top.id[0], w, kGroup);
+  top.pos[0] = __shfl(top.pos[0], w, kGroup);
 }
 
 // Sums over one wave of kNV values per lane into row[0 .. kNV): as the tile
@@ -1405,13 +1397,13 @@ __global__ __launch_bounds__(kWide) void k_wide_iter(
     }
   }
   __syncthreads();
-  for (int q = tid / kWideLanes; q < q_n; q += kWide / kWideLanes) {
+  for (int q = tid / kGroup; q < q_n; q += kWide / kGroup) {
     TopK<1> top;
     top.init();
     const int32_t cp = q_pos[q];
     if (cp >= 0 && q_d[q] <= prm.r2) top.push(q_d[q], q_id[q], cp);
-    nn_wide(m, prm, q_p[q][0], q_p[q][1], q_p[q][2], tid & (kWideLanes - 1), top);
-    if ((tid & (kWideLanes - 1)) == 0) {
+    nn_wide(m, prm, q_p[q][0], q_p[q][1], q_p[q][2], tid & (kGroup - 1), top);
+    if ((tid & (kGroup - 1)) == 0) {
       s_match[q_lane[q]] = top.pos[0];
       if (prev) prev[lo + uint32_t(q_lane[q])] = top.pos[0] >= 0 ? top.pos[0] : cp;
     }
@@ -1497,9 +1489,7 @@ __global__ __launch_bounds__(256) void k_reduce_grad(const int32_t* begin,
   const int s = blockIdx.x;
   const int g = threadIdx.x >> 5, v = threadIdx.x & 31;
   if (v < 14) {
-    double acc = 0.0;
-    const int32_t t1 = begin[s + 1];
-    for (int32_t t = begin[s] + g; t < t1; t += 8) acc += tile_sum<kHalf>(partial, t, v);
+    const double acc = strided_sum<kHalf>(partial, begin[s] + g, begin[s + 1], v);
     part[g][v] = acc;
   }
   __syncthreads();

@@ -56,6 +56,38 @@ struct TopK {
   }
 };
 
+template <int kCtrl>
+__device__ inline double dpp_partner(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), kCtrl, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), kCtrl, 0xF, 0xF, false);
+  return __hiloint2double(hi, lo);
+}
+// Groups of kGroup lanes (a half of a wave) that share a search: where one lane
+// per query would leave the chip idle, each lane ranks a part of the candidates
+// and the group takes the best of them.
+constexpr int kGroup = 32;
+
+// Lane (in [0, kGroup)) of the group's best (d, id).  The least d by lane swaps
+// and one shuffle; its holder by ballot; ids only when several lanes hold it.
+// (Carrying d, id and place through five shuffle levels took five times the
+// LDS instructions: covariances of 20k points at k = 10 70 us, 60 us now.)
+__device__ inline int group_best(double d, int32_t id) {
+  double m = fmin(d, dpp_partner<0xB1>(d));
+  m = fmin(m, dpp_partner<0x4E>(m));
+  m = fmin(m, dpp_partner<0x141>(m));
+  m = fmin(m, dpp_partner<0x140>(m));
+  m = fmin(m, __shfl_xor(m, 16, 64));
+  const int half = threadIdx.x & 32;
+  uint32_t who = uint32_t(__ballot(d == m) >> half);
+  if (who & (who - 1)) {
+    int32_t mi = d == m ? id : INT_MAX;
+#pragma unroll
+    for (int w = 16; w >= 1; w >>= 1) mi = min(mi, __shfl_xor(mi, w, 64));
+    who = uint32_t(__ballot(d == m && id == mi) >> half);
+  }
+  return who ? __builtin_ctz(who) : 0;
+}
+
 // Voxel index of a coordinate; false when outside [-2^20, 2^20).
 __device__ inline bool voxel_index(double x, double v, int64_t* k) {
   double f = floor(x / v);

@@ -1520,39 +1520,31 @@ __global__ __launch_bounds__(kT, kCovMinWaves) void k_grid_cov(GridView g, int32
 
 // Covariances of a small scan, 32 lanes per point.  One lane per point leaves
 // most of the chip idle below about 32k points (5000 points are 79 waves, each
-// as long as its slowest chain of cells: 60 us; 17.5 us here; k = 5 at 20k
-// points 54 -> 39 us, k = 10 at 13k points 86 -> 54 us).  First the lanes share the points of the own cell, each keeping
-// its own K best, and the group merges them; then every lane ranks one of the
-// other 26 cells against the merged K-th best (entries it holds from the start,
-// with no place, so only better points enter), and the group merges again.
+// as long as its slowest chain of cells: 60 us; 15.3 us here; k = 5 at 20k
+// points 54 -> 34 us, k = 10 at 13k points 86 -> 45 us).  First the lanes share
+// the points of the own cell, each keeping its own K best, and the group merges
+// them; then every lane ranks one of the other 26 cells against the merged K-th
+// best (entries it holds from the start, with no place, so only better points
+// enter), and the group merges again.
 // The list is the K best by (d2, id) of the same candidates, so the results
 // are those of k_grid_cov, bit for bit.
 constexpr int64_t kWideCovMax = 32 * 1024;
-constexpr int kCovLanes = 32;
 
 // The K best of the lanes' sorted lists into out, in every lane; entries
 // without a place count as absent.
 template <int K>
 __device__ inline void merge_lists(TopK<K>& own, TopK<K>& out) {
+  const int lane = threadIdx.x & (kGroup - 1);
 #pragma unroll
   for (int s = 0; s < K; ++s) {
     const bool have = own.pos[0] >= 0;
-    double d = have ? own.d[0] : __builtin_inf();
-    int32_t id = have ? own.id[0] : INT_MAX, pos = have ? own.pos[0] : -1;
-#pragma unroll
-    for (int w = kCovLanes / 2; w >= 1; w >>= 1) {
-      const double od = __shfl_xor(d, w, kCovLanes);
-      const int32_t oi = __shfl_xor(id, w, kCovLanes), op = __shfl_xor(pos, w, kCovLanes);
-      if (rank_less(od, oi, d, id)) {
-        d = od;
-        id = oi;
-        pos = op;
-      }
-    }
-    out.d[s] = d;
-    out.id[s] = id;
-    out.pos[s] = pos;
-    if (have && own.pos[0] == pos) {   // the lane that held it drops it
+    const double d = have ? own.d[0] : __builtin_inf();
+    const int32_t id = have ? own.id[0] : INT_MAX, pos = have ? own.pos[0] : -1;
+    const int w = group_best(d, id);
+    out.d[s] = __shfl(d, w, kGroup);
+    out.id[s] = __shfl(id, w, kGroup);
+    out.pos[s] = __shfl(pos, w, kGroup);
+    if (have && lane == w) {   // the lane that held it drops it
 #pragma unroll
       for (int q = 0; q + 1 < K; ++q) {
         own.d[q] = own.d[q + 1];
@@ -1567,10 +1559,10 @@ __device__ inline void merge_lists(TopK<K>& own, TopK<K>& out) {
 template <int K>
 __global__ __launch_bounds__(kT) void k_grid_cov_wide(GridView g, int64_t n, int32_t k,
                                                       int32_t reg, float* cov6, uint8_t* valid) {
-  constexpr int kPts = kT / kCovLanes;
+  constexpr int kPts = kT / kGroup;
   __shared__ int32_t s_pos[kPts][K];   // the K nearest of the block's points (-1: none)
-  const int64_t j = int64_t(blockIdx.x) * kPts + threadIdx.x / kCovLanes;
-  const int lane = threadIdx.x & (kCovLanes - 1);
+  const int64_t j = int64_t(blockIdx.x) * kPts + threadIdx.x / kGroup;
+  const int lane = threadIdx.x & (kGroup - 1);
   float4 me = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   if (j < n) me = g.sorted[j];
   const bool fin = j < n && isfinite(me.x) && isfinite(me.y) && isfinite(me.z);
@@ -1587,7 +1579,7 @@ __global__ __launch_bounds__(kT) void k_grid_cov_wide(GridView g, int64_t n, int
     own.init();
     Query q = make_query(px, py, pz, r2);
     const uint2 me_run = row[13];
-    for (uint32_t u = me_run.x + uint32_t(lane); u < me_run.x + me_run.y; u += kCovLanes) {
+    for (uint32_t u = me_run.x + uint32_t(lane); u < me_run.x + me_run.y; u += kGroup) {
       const float4 p = g.sorted[u];
       const double d = dist2(double(p.x), double(p.y), double(p.z), px, py, pz);
       if (d <= r2) own.push(d, __float_as_int(p.w), int32_t(u));
@@ -1627,7 +1619,7 @@ __global__ __launch_bounds__(kT) void k_grid_cov_wide(GridView g, int64_t n, int
   }
   if (lane == 0) {
 #pragma unroll
-    for (int s = 0; s < K; ++s) s_pos[threadIdx.x / kCovLanes][s] = top.pos[s];
+    for (int s = 0; s < K; ++s) s_pos[threadIdx.x / kGroup][s] = top.pos[s];
   }
   __syncthreads();
   // the FP64 covariances by one lane per point, all in the first wave (by every
@@ -2234,13 +2226,13 @@ far_status_t far_map_knn(far_map_t m, const float* q, int64_t n, int32_t k, doub
 // Voxel grid of a batch of scans with cells of edge `cell`: the points sorted
 // by (scan, cell, x), through compact keys (see k_key_range) or, when the
 // batch's key range needs more than 62 bits with the scan id, by full keys and
-// then by scan (runs not ordered by x); the runs, a hash of them, and each
-// run's neighbour cells.  *oor receives the points whose keys leave [-2^20,
-// 2^20) (the grid is then not built).
+// then by scan (runs not ordered by x, as without by_x); the runs, a hash of
+// them, and each run's neighbour cells.  *oor receives the points whose keys
+// leave [-2^20, 2^20) (the grid is then not built).
 static far_status_t build_grid(const float* xyz, const int64_t* offsets, int32_t S_, int64_t n,
                                double v, double cell, hipStream_t st, Scratch& scr,
-                               GridView* out, uint32_t* oor, uint32_t* order = nullptr,
-                               float4* sorted_in = nullptr) {
+                               bool by_x, GridView* out, uint32_t* oor,
+                               uint32_t* order = nullptr, float4* sorted_in = nullptr) {
   CompactKey ck{};
   bool compact = false, none = false;
   // per point: two slots (32 B), 27 cells (216), run arrays (24), keys and
@@ -2275,7 +2267,7 @@ static far_status_t build_grid(const float* xyz, const int64_t* offsets, int32_t
     FAR_TRY(scr.get(&vals_alt, nn));
     const int key_bits = (S_ > 1 ? ceil_log2(S_) : 0) + ck.kb + 1;
     // x bits: one more radix pass of 8 bits (8 to 15 bits), within 62 in all
-    ck.fb = std::min(((key_bits + 15) / 8) * 8 - key_bits, 62 - key_bits);
+    ck.fb = by_x ? std::min(((key_bits + 15) / 8) * 8 - key_bits, 62 - key_bits) : 0;
     k_keys_compact<<<blocks_for(n), kT, 0, st>>>(xyz, n, cell, 1.0 / cell, pow2,
                                                   S_ > 1 ? offsets : nullptr, S_, ck, keys, vals,
                                                   nullptr, slots);
@@ -2347,8 +2339,13 @@ static far_status_t scan_cov_impl(const float* xyz, const int64_t* offsets, int3
   GridView g{};
   uint32_t oor = 0;
   char* pk = static_cast<char*>(packed);
-  FAR_TRY(build_grid(xyz, offsets, S_, n, voxel_size, voxel_size, st, scr, &g, &oor, order,
-                     reinterpret_cast<float4*>(pk)));
+  const int32_t dense = g_dense_threshold;
+  // the wide search deals a cell's few points to its lanes and gains less from
+  // runs in x order than their radix pass costs; an order the caller receives
+  // keeps it
+  const bool wide = dense == 0 && k <= 10 && n <= kWideCovMax;
+  FAR_TRY(build_grid(xyz, offsets, S_, n, voxel_size, voxel_size, st, scr,
+                     !wide || order || packed, &g, &oor, order, reinterpret_cast<float4*>(pk)));
   if (pk) {
     g.pk_B = reinterpret_cast<float4*>(pk + 16 * n);
     g.pk_C = reinterpret_cast<float2*>(pk + 32 * n);
@@ -2357,14 +2354,13 @@ static far_status_t scan_cov_impl(const float* xyz, const int64_t* offsets, int3
     set_error("%s: %u points have voxel keys outside [-2^20, 2^20)", who, oor);
     return FAR_E_INVALID;
   }
-  const int32_t dense = g_dense_threshold;
   // (a batch with no finite point has no runs: every point takes the
   // non-finite branch of k_grid_cov, zero covariance and invalid)
   return dispatch_k(k, [&](auto KK) -> far_status_t {
     constexpr int K = decltype(KK)::value;
     if constexpr (K <= 10) {
-      if (dense == 0 && n <= kWideCovMax) {
-        k_grid_cov_wide<K><<<blocks_for(n * kCovLanes), kT, 0, st>>>(g, n, k, g_cov_reg, cov6,
+      if (wide) {
+        k_grid_cov_wide<K><<<blocks_for(n * kGroup), kT, 0, st>>>(g, n, k, g_cov_reg, cov6,
                                                                      valid);
         FAR_HIP(hipGetLastError());
         return FAR_OK;

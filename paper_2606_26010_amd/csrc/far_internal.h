@@ -263,14 +263,23 @@ static __constant__ int8_t kNbrOrder[27] = {13, 4, 22, 10, 16, 12, 14, 1,  3,  5
 // ---------------------------------------------------------------- scratch
 // A chunk of device memory for work on `stream`, from the current device's
 // stream-ordered pool (one per device, created on first use, keeping freed
-// memory for later calls), and its return after that work.  Chunks of
-// kScratchChunk returned on the null stream wait in a short list per device (at
-// most kScratchKept) for the next call on it, which runs after the work that
-// used them: the null stream is never destroyed, so its work is in one order
-// for good.  (A pool request and its return cost the host 22 us a call:
-// undistorting one small scan 37 -> 14 us.)  far_scratch_release returns them.
-constexpr size_t kScratchKept = 4;
-far_status_t scratch_take(hipStream_t stream, size_t bytes, void** out);
+// memory for later calls), and its return after that work.  Returned chunks
+// wait in a short list per device (at most kScratchKept) for a later call: of
+// the null stream, which is never destroyed, for the next call on it; of
+// another stream with an event recorded behind their work, for a call on the
+// same stream, which waits for the event on the device, or on any stream once
+// the event has passed.  (A pool request and its return cost the host 22 us a
+// call: undistorting one small scan 37 -> 14 us.  And a pool whose memory is
+// pending on other streams makes the host wait or maps new memory: batches of
+// 64 scans, 1.3 GB of scratch each, enqueued in turn on three streams, 30
+// calls without a host wait, took 18 to 23 ms a call once the pool had begun to
+// unmap and map, with single calls of two seconds; 4.4 ms here.)  A request
+// that no kept chunk can hold gives an idle smaller one back to the pool first.
+// far_scratch_release returns what is idle.  Streams under capture go to the
+// pool.
+constexpr size_t kScratchKept = 8;
+// *got: the chunk's bytes, at least those asked for.
+far_status_t scratch_take(hipStream_t stream, size_t bytes, size_t* got, void** out);
 void scratch_return(hipStream_t stream, size_t bytes, void* p);
 
 // Stream-ordered device scratch, freed when the guard leaves scope.  Pieces
@@ -305,9 +314,9 @@ struct Scratch {
   // host wait.
   far_status_t reserve(size_t bytes) {
     if (arena || (chunk && chunk_used + bytes <= chunk_cap)) return FAR_OK;
-    const size_t cap = bytes > kScratchChunk ? bytes : kScratchChunk;
+    size_t cap = bytes > kScratchChunk ? bytes : kScratchChunk;
     void* p = nullptr;
-    FAR_TRY(scratch_take(stream, cap, &p));
+    FAR_TRY(scratch_take(stream, cap, &cap, &p));
     ptrs.push_back({p, cap});
     chunk = static_cast<char*>(p);
     chunk_cap = cap;

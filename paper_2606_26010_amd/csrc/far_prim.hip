@@ -449,10 +449,17 @@ far_status_t radix_sort_pairs(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt
 // far_scratch_release: its footprint is the largest scratch any one call
 // has needed, far below the device memory of the workloads it serves.
 namespace {
+struct Kept {
+  void* p;
+  size_t bytes;
+  hipStream_t stream;
+  hipEvent_t ev;   // behind its last work; null: the null stream's
+};
 struct Pools {
   std::mutex mu;
-  std::vector<hipMemPool_t> pool;   // per device id, null until first use
-  std::vector<std::vector<void*>> kept;   // per device id, chunks of the null stream
+  std::vector<hipMemPool_t> pool;          // per device id, null until first use
+  std::vector<std::vector<Kept>> kept;     // per device id
+  std::vector<std::vector<hipEvent_t>> events;   // per device id, not in use
 };
 Pools& pools() {
   static Pools p;
@@ -460,33 +467,107 @@ Pools& pools() {
 }
 }  // namespace
 
+// Whether the work behind a kept chunk's event has ended.  (Asked in relaxed
+// mode, so that a capture on another thread's stream is left alone.)
+static bool chunk_idle(const Kept& k) {
+  if (!k.ev) return false;
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  const bool idle = hipEventQuery(k.ev) == hipSuccess;
+  if (!idle) (void)hipGetLastError();   // hipErrorNotReady
+  if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  return idle;
+}
+
+static bool capturing(hipStream_t stream) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  return stream && (hipStreamIsCapturing(stream, &cs) != hipSuccess ||
+                    cs != hipStreamCaptureStatusNone);
+}
+
 void scratch_return(hipStream_t stream, size_t bytes, void* p) {
   int dev = 0;
-  if (!stream && bytes == kScratchChunk && hipGetDevice(&dev) == hipSuccess) {
+  if (!capturing(stream) && hipGetDevice(&dev) == hipSuccess) {
     Pools& P = pools();
     std::lock_guard<std::mutex> lk(P.mu);
     if (size_t(dev) < P.kept.size() && P.kept[dev].size() < kScratchKept) {
-      P.kept[dev].push_back(p);
-      return;
+      Kept k{p, bytes, stream, nullptr};
+      if (stream) {
+        auto& ev = P.events[dev];
+        if (!ev.empty()) {
+          k.ev = ev.back();
+          ev.pop_back();
+        } else if (hipEventCreateWithFlags(&k.ev, hipEventDisableTiming) != hipSuccess) {
+          k.ev = nullptr;
+        }
+        if (k.ev && hipEventRecord(k.ev, stream) != hipSuccess) {
+          ev.push_back(k.ev);
+          k.ev = nullptr;
+        }
+      }
+      if (!stream || k.ev) {
+        P.kept[dev].push_back(k);
+        return;
+      }
+      (void)hipGetLastError();
     }
   }
   (void)hipFreeAsync(p, stream);
 }
 
-far_status_t scratch_take(hipStream_t stream, size_t bytes, void** out) {
+far_status_t scratch_take(hipStream_t stream, size_t bytes, size_t* got, void** out) {
   *out = nullptr;
+  *got = bytes;
   int dev = 0;
   FAR_HIP(hipGetDevice(&dev));
+  const bool cap = capturing(stream);
   Pools& P = pools();
   std::unique_lock<std::mutex> lk(P.mu);
   if (size_t(dev) >= P.pool.size()) {
     P.pool.resize(size_t(dev) + 1, nullptr);
     P.kept.resize(size_t(dev) + 1);
+    P.events.resize(size_t(dev) + 1);
   }
-  if (!stream && bytes == kScratchChunk && !P.kept[dev].empty()) {
-    *out = P.kept[dev].back();
-    P.kept[dev].pop_back();
-    return FAR_OK;
+  if (!cap) {
+    // the smallest chunk of this stream that holds the request, then the
+    // smallest idle one; without either the largest idle one goes back
+    auto& kept = P.kept[dev];
+    int best = -1, drop = -1;
+    bool best_own = false;
+    for (int i = 0; i < int(kept.size()); ++i) {
+      const Kept& k = kept[i];
+      const bool own = k.stream == stream;   // (event null exactly on the null stream)
+      if (k.bytes >= bytes) {
+        const bool better = best < 0 || (own && !best_own) ||
+                            (own == best_own && k.bytes < kept[best].bytes);
+        if (better && (own || chunk_idle(k))) {
+          best = i;
+          best_own = own;
+        }
+      } else if ((drop < 0 || k.bytes > kept[drop].bytes) && (own || chunk_idle(k))) {
+        drop = i;
+      }
+    }
+    const int at = best >= 0 ? best : drop;
+    if (at >= 0) {
+      const Kept k = kept[at];
+      kept.erase(kept.begin() + at);
+      if (k.ev) {
+        // (also where the handles are equal: the stream may be a new one)
+        const hipError_t e = hipStreamWaitEvent(stream, k.ev, 0);
+        P.events[dev].push_back(k.ev);
+        if (e != hipSuccess) {
+          (void)hipEventSynchronize(k.ev);
+          (void)hipGetLastError();
+        }
+      }
+      if (best >= 0) {
+        *out = k.p;
+        *got = k.bytes;
+        return FAR_OK;
+      }
+      (void)hipFreeAsync(k.p, stream);
+    }
   }
   if (!P.pool[dev]) {
     hipMemPoolProps props{};
@@ -656,10 +737,20 @@ far_status_t far_scratch_release(void) {
   int here = 0;
   FAR_HIP(hipGetDevice(&here));
   for (size_t d = 0; d < P.kept.size(); ++d) {
-    if (P.kept[d].empty()) continue;
+    if (P.kept[d].empty() && P.events[d].empty()) continue;
     FAR_HIP(hipSetDevice(int(d)));
-    for (void* p : P.kept[d]) (void)hipFreeAsync(p, nullptr);
-    P.kept[d].clear();
+    std::vector<far::Kept> busy;
+    for (const far::Kept& k : P.kept[d]) {
+      if (k.ev && !far::chunk_idle(k)) {   // a call still running: its chunk stays
+        busy.push_back(k);
+        continue;
+      }
+      (void)hipFreeAsync(k.p, nullptr);
+      if (k.ev) P.events[d].push_back(k.ev);
+    }
+    P.kept[d].swap(busy);
+    for (hipEvent_t e : P.events[d]) (void)hipEventDestroy(e);
+    P.events[d].clear();
     (void)hipStreamSynchronize(nullptr);
     FAR_HIP(hipSetDevice(here));
   }

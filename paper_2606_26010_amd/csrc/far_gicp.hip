@@ -232,16 +232,20 @@ __global__ __launch_bounds__(256) void k_setup(SingleArgs one, int64_t* offsets,
 // sum and takes one add per level instead of a TwoSum).
 // The four in-row levels use DPP lane swaps (quad_perm [1,0,3,2] and
 // [2,3,0,1], row_half_mirror, row_mirror: each pairs a lane with a partner
-// holding the other half of its group), the two cross-row levels shuffles.
+// holding the other half of its group), the two cross-row levels row swaps in
+// registers (as shuffles through LDS the 29 sums of a wave took 8200 cycles, 5700
+// now: an FP64 iteration of 20000 points 37.5 us, 35.4 now).
 // Partners add the same two values, so every lane ends with the same sum.
 __device__ inline double wave_sum(double v) {
   v += dpp_partner<0xB1>(v);
   v += dpp_partner<0x4E>(v);
   v += dpp_partner<0x141>(v);
   v += dpp_partner<0x140>(v);
-  v += __shfl_xor(v, 16, 64);
-  v += __shfl_xor(v, 32, 64);
-  return v;
+  double a, b;
+  swap_partner<false>(v, &a, &b);
+  v = a + b;
+  swap_partner<true>(v, &a, &b);
+  return a + b;
 }
 
 // Wave sums of many FP32 values per lane through LDS (the FP32 kernels):
@@ -1132,23 +1136,17 @@ __device__ inline double strided_sum(const double* partial, int32_t t, int32_t t
   return acc;
 }
 
-// Gauss-Newton update of scan s from its 29 sums, by one lane.
-__device__ void solve_scan(int32_t s, const double* lin, double* T, double* ctr, int32_t* done,
+// Gauss-Newton update of scan s from its 29 sums, by one lane, with its pose
+// Tc, its centre cc and its iterations so far as read beforehand.  Its serial
+// chain is what an iteration of a small job waits for: everything stays in
+// registers, and the statistics are stored beside it by another wave
+// (k_reduce_solve of 64 scans 10.7 -> 10.1 us; a factorisation without square
+// roots and sine and cosine as series took 8.4, but their other roundings move
+// the FP32 terms of the later iterations and scans).
+__device__ void solve_scan(int32_t s, const double* lin, const double* Tc, const double* cc,
+                           int32_t iters, double* T, double* ctr, int32_t* done,
                            far_align_stats_t* stats, const Params& prm, int32_t solve) {
   far_align_stats_t& st = stats[s];
-  double H[36], b[6];
-  int u = 0;
-  for (int p = 0; p < 6; ++p)
-    for (int q = p; q < 6; ++q) {
-      H[6 * p + q] = lin[u];
-      H[6 * q + p] = lin[u];
-      ++u;
-    }
-  for (int p = 0; p < 6; ++p) b[p] = lin[21 + p];
-  for (int p = 0; p < 36; ++p) st.last.H[p] = H[p];
-  for (int p = 0; p < 6; ++p) st.last.b[p] = b[p];
-  st.last.cost = lin[27];
-  st.last.n_inliers = int64_t(lin[28]);
   if (!solve) {
     done[s] = 1;
     return;
@@ -1158,71 +1156,101 @@ __device__ void solve_scan(int32_t s, const double* lin, double* T, double* ctr,
     done[s] = 1;
     return;
   }
-  // Cholesky H = L L^T; a pivot not above 1e-12 max|H_ii| means not PD.
-  double L[36];
+  // Cholesky H = L L^T in place of the lower triangle; a pivot not above 1e-12
+  // max|H_ii| means not PD.
+  double L[6][6], y[6];
+  int u = 0;
+#pragma unroll
+  for (int p = 0; p < 6; ++p)
+#pragma unroll
+    for (int q = p; q < 6; ++q) L[q][p] = lin[u++];
   double dmax = 0.0;
-  for (int p = 0; p < 6; ++p) dmax = fmax(dmax, fabs(H[7 * p]));
+#pragma unroll
+  for (int p = 0; p < 6; ++p) dmax = fmax(dmax, fabs(L[p][p]));
+  bool pd = true;
+#pragma unroll
   for (int j = 0; j < 6; ++j) {
-    double sd = H[7 * j];
-    for (int l = 0; l < j; ++l) sd -= L[6 * j + l] * L[6 * j + l];
-    if (!(sd > 1e-12 * dmax) || !isfinite(sd)) {
-      st.status = FAR_E_NOT_PD;
-      done[s] = 1;
-      return;
-    }
-    double dj = sqrt(sd);
-    L[7 * j] = dj;
+    double sd = L[j][j];
+#pragma unroll
+    for (int l = 0; l < j; ++l) sd -= L[j][l] * L[j][l];
+    pd = pd && sd > 1e-12 * dmax && isfinite(sd);
+    const double dj = sqrt(sd);
+    L[j][j] = dj;
+#pragma unroll
     for (int i = j + 1; i < 6; ++i) {
-      double x = H[6 * i + j];
-      for (int l = 0; l < j; ++l) x -= L[6 * i + l] * L[6 * j + l];
-      L[6 * i + j] = x / dj;
+      double x = L[i][j];
+#pragma unroll
+      for (int l = 0; l < j; ++l) x -= L[i][l] * L[j][l];
+      L[i][j] = x / dj;
     }
+    // (the forward substitution beside the next columns)
+    double x = -lin[21 + j];
+#pragma unroll
+    for (int l = 0; l < j; ++l) x -= L[j][l] * y[l];
+    y[j] = x / dj;
   }
-  double y[6], dl[6];
-  for (int i = 0; i < 6; ++i) {
-    double x = -b[i];
-    for (int l = 0; l < i; ++l) x -= L[6 * i + l] * y[l];
-    y[i] = x / L[7 * i];
+  if (!pd) {
+    st.status = FAR_E_NOT_PD;
+    done[s] = 1;
+    return;
   }
+  double dl[6];
+#pragma unroll
   for (int i = 5; i >= 0; --i) {
     double x = y[i];
-    for (int l = i + 1; l < 6; ++l) x -= L[6 * l + i] * dl[l];
-    dl[i] = x / L[7 * i];
+#pragma unroll
+    for (int l = i + 1; l < 6; ++l) x -= L[l][i] * dl[l];
+    dl[i] = x / L[i][i];
   }
+  double Tn[12];
+#pragma unroll
+  for (int p = 0; p < 12; ++p) Tn[p] = Tc[p];
+  se3_apply(dl, cc, Tn);
   double* Ts = T + 16 * int64_t(s);
-  double* cs = ctr + 3 * s;
-  se3_apply(dl, cs, Ts);
-  st.iters += 1;
+#pragma unroll
+  for (int p = 0; p < 12; ++p) Ts[p] = Tn[p];
+  st.iters = ++iters;
   double nrm = 0.0;
+#pragma unroll
   for (int p = 0; p < 6; ++p) nrm += dl[p] * dl[p];
   if (sqrt(nrm) <= prm.eps) {
     st.converged = 1;
     done[s] = 1;
-  } else if (st.iters >= prm.max_iters) {
+  } else if (iters >= prm.max_iters) {
     done[s] = 1;
   }
   if (prm.recenter) {
-    cs[0] = Ts[3];
-    cs[1] = Ts[7];
-    cs[2] = Ts[11];
+    double* cs = ctr + 3 * s;
+    cs[0] = Tn[3];
+    cs[1] = Tn[7];
+    cs[2] = Tn[11];
   }
 }
 
-// Sums of scan s's tile partials and its Gauss-Newton update, by the first 256
-// threads of a block (all threads call it): eight groups of 32 lanes, group g
-// sums tiles begin+g, begin+g+8, ... of the scan in that order, then the eight
-// group sums are added in group order.
+// Sums of scan s's tile partials (tiles t0 to t1) and its Gauss-Newton update, by
+// the first 256 threads of a block (all threads call it): eight groups of 32
+// lanes, group g sums tiles t0+g, t0+g+8, ... in that order, then the eight
+// group sums are added in group order.  What the update needs besides is read
+// beside the sums by the lanes that hold none.
 template <bool kHalf>
-__device__ void reduce_solve_scan(int32_t s, const int32_t* begin, const double* partial,
+__device__ void reduce_solve_scan(int32_t s, int32_t t0, int32_t t1, const double* partial,
                                   double* T, double* ctr, int32_t* done,
                                   far_align_stats_t* stats, const Params& prm, int32_t solve,
                                   const Progress& pg) {
   __shared__ double part[8][kVals];
   __shared__ double lin[kVals];
+  __shared__ double pose[15];   // the scan's pose (three rows) and centre
+  __shared__ int32_t iters;
   const int g = threadIdx.x >> 5, v = threadIdx.x & 31;
   if (g < 8 && v < kVals) {
-    const double acc = strided_sum<kHalf>(partial, begin[s] + g, begin[s + 1], v);
+    const double acc = strided_sum<kHalf>(partial, t0 + g, t1, v);
     part[g][v] = acc;
+  } else if (g < 8) {
+    const int q = g * 3 + v - kVals;
+    if (q < 15)
+      pose[q] = q < 12 ? T[16 * int64_t(s) + q] : ctr[3 * s + q - 12];
+    else if (q == 15)
+      iters = stats[s].iters;
   }
   __syncthreads();
   if (threadIdx.x < kVals) {
@@ -1232,8 +1260,23 @@ __device__ void reduce_solve_scan(int32_t s, const int32_t* begin, const double*
     lin[threadIdx.x] = acc;
   }
   __syncthreads();
+  // the statistics by the second wave, beside the solve
+  if (threadIdx.x >= 64 && threadIdx.x < 64 + 44) {
+    const int e = int(threadIdx.x) - 64;
+    far_lin_t& out = stats[s].last;
+    if (e < 36) {
+      const int a = e / 6, b = e % 6, p = min(a, b), q = max(a, b);
+      out.H[e] = lin[p * 6 - p * (p - 1) / 2 + (q - p)];   // row p of the upper triangle
+    } else if (e < 42) {
+      out.b[e - 36] = lin[21 + e - 36];
+    } else if (e == 42) {
+      out.cost = lin[27];
+    } else {
+      out.n_inliers = int64_t(lin[28]);
+    }
+  }
   if (threadIdx.x != 0) return;
-  solve_scan(s, lin, T, ctr, done, stats, prm, solve);
+  solve_scan(s, lin, pose, pose + 12, iters, T, ctr, done, stats, prm, solve);
   if (pg.word)
     __hip_atomic_store(pg.word, done[s] ? kAlignDone : pg.step, __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_SYSTEM);
@@ -1249,7 +1292,7 @@ __global__ __launch_bounds__(256) void k_reduce_solve(int32_t S, const int32_t* 
   if (bins && blockIdx.x == 0 && threadIdx.x < kBins) bins[threadIdx.x] = 0u;
   const int32_t s = blockIdx.x;
   if (s >= S || done[s]) return;
-  reduce_solve_scan<false>(s, begin, partial, T, ctr, done, stats, prm, solve, pg);
+  reduce_solve_scan<false>(s, begin[s], begin[s + 1], partial, T, ctr, done, stats, prm, solve, pg);
 }
 
 // ---------------------------------------------------------------- wide jobs
@@ -1266,7 +1309,7 @@ __global__ __launch_bounds__(256) void k_reduce_solve(int32_t S, const int32_t* 
 // the exact search, and the sums are taken in the order of the tile passes (per
 // wave, then the two waves of a tile of 128, then the tiles), so the results
 // are theirs bit for bit.  5000 points, first iteration 45 us in two launches
-// and each later one about 45 us in four; 34 and 19 us in one.
+// and each later one about 45 us in four; 32 and 18.5 us in one.
 constexpr int kWide = 512;        // lanes per block: 16 searches at once
 constexpr int kWidePts = 64;
 
@@ -1293,7 +1336,7 @@ __device__ inline void nn_wide(const MapView& m, const Params& prm, double px, d
       if (vox >= 0) {
         Query q = make_query(px, py, pz, prm.r2);
         q.bound_f = screen_bound(bound, q.m);
-        scan_voxel_points<1, 8>(m.vox_pts, vox * m.nmax, cnt, q, prm.r2, top);
+        scan_voxel_points<1, 10>(m.vox_pts, vox * m.nmax, cnt, q, prm.r2, top);
       }
     }
   }
@@ -1344,7 +1387,8 @@ __global__ __launch_bounds__(kWide) void k_wide_iter(
     const uint32_t* __restrict__ tile_lo, const uint32_t* __restrict__ tile_hi, int64_t n_half,
     const int32_t* __restrict__ begin, double* T, double* ctr, int32_t* done, Params prm,
     double* partial, uint32_t* counter, far_align_stats_t* stats, int32_t solve, int32_t first,
-    int32_t* corr, float* grad_src, int64_t n_src, int32_t* prev, Progress pg) {
+    int32_t* corr, float* grad_src, int64_t n_src, int32_t* prev, Progress pg,
+    int64_t n_one) {
   constexpr int kNV = kGrad ? 14 : kVals;
   __shared__ double q_p[kWidePts][3];
   __shared__ double q_d[kWidePts];
@@ -1355,10 +1399,19 @@ __global__ __launch_bounds__(kWide) void k_wide_iter(
   const int64_t hb = block_tile(n_half);
   if (hb < 0) return;
   const int64_t t = hb >> 1;
-  const int32_t s = tile_scan[t];
+  // one scan: its tiles are known without their table, a load less before the
+  // pose and the points
+  const int32_t s = n_one > 0 ? (t * kTileMin < n_one ? 0 : -1) : tile_scan[t];
   if (s < 0 || done[s]) return;
   const int tid = threadIdx.x, lane = tid & 63;
-  const uint32_t lo = tile_lo[t] + uint32_t(kWidePts) * uint32_t(hb & 1), hi = tile_hi[t];
+  uint32_t lo = uint32_t(hb) * kWidePts, hi = uint32_t(n_one);
+  int32_t t0 = 0, t1 = int32_t((n_one + kTileMin - 1) / kTileMin);
+  if (n_one <= 0) {
+    t0 = begin[s];
+    t1 = begin[s + 1];
+    lo = tile_lo[t] + uint32_t(kWidePts) * uint32_t(hb & 1);
+    hi = tile_hi[t];
+  }
   const uint32_t i = lo + uint32_t(lane);
   const bool own = tid < 64 && i < hi;
   const Pose P(T + 16 * int64_t(s));
@@ -1442,14 +1495,14 @@ __global__ __launch_bounds__(kWide) void k_wide_iter(
   if constexpr (!kGrad) {
     __syncthreads();
     if (tid == 0) {
-      __threadfence();
-      s_last = atomicAdd(&counter[s], 1u) + 1u == 2u * uint32_t(begin[s + 1] - begin[s]) ? 1u : 0u;
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      s_last = atomicAdd(&counter[s], 1u) + 1u == 2u * uint32_t(t1 - t0) ? 1u : 0u;
     }
     __syncthreads();
     if (!s_last) return;
-    __threadfence();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     if (tid == 0) counter[s] = 0u;
-    reduce_solve_scan<true>(s, begin, partial, T, ctr, done, stats, prm, solve, pg);
+    reduce_solve_scan<true>(s, t0, t1, partial, T, ctr, done, stats, prm, solve, pg);
   }
 }
 
@@ -1786,7 +1839,8 @@ far_status_t launch_wide(hipStream_t st, const MapView& mv, const AlignWS* w, in
     k_wide_iter<Real, kGrad, decltype(no_sa)::value><<<grid, kWide, 0, st>>>(
         mv, pA, pB, pC, w->tile_scan, w->tile_lo, w->tile_hi, n_half, w->begin, j.T, w->ctr,
         w->done, j.prm, w->partial, w->counter, j.stats, j.c_fixed ? 0 : 1, first ? 1 : 0,
-        j.corr, kGrad ? j.grad_src : nullptr, j.n_total, kGrad ? nullptr : w->prev, pg);
+        j.corr, kGrad ? j.grad_src : nullptr, j.n_total, kGrad ? nullptr : w->prev, pg,
+        j.S == 1 ? j.n_total : 0);
   };
   if (j.prm.sa_off)
     go(std::true_type());

@@ -62,13 +62,33 @@ __device__ inline double dpp_partner(double v) {
   const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), kCtrl, 0xF, 0xF, false);
   return __hiloint2double(hi, lo);
 }
+// The two halves of v's exchange with the lane 16 (32) away, in either order:
+// rows (halves) swapped in registers instead of a shuffle through LDS.  *a and
+// *b are the same two values in both lanes, so that a sum or a minimum of them
+// is what v and its partner give.
+template <bool k32>
+__device__ inline void swap_partner(double v, double* a, double* b) {
+  const uint32_t lo = uint32_t(__double2loint(v)), hi = uint32_t(__double2hiint(v));
+  if constexpr (k32) {
+    const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    *a = __hiloint2double(int(h[0]), int(l[0]));
+    *b = __hiloint2double(int(h[1]), int(l[1]));
+  } else {
+    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    *a = __hiloint2double(int(h[0]), int(l[0]));
+    *b = __hiloint2double(int(h[1]), int(l[1]));
+  }
+}
+
 // Groups of kGroup lanes (a half of a wave) that share a search: where one lane
 // per query would leave the chip idle, each lane ranks a part of the candidates
 // and the group takes the best of them.
 constexpr int kGroup = 32;
 
-// Lane (in [0, kGroup)) of the group's best (d, id).  The least d by lane swaps
-// and one shuffle; its holder by ballot; ids only when several lanes hold it.
+// Lane (in [0, kGroup)) of the group's best (d, id).  The least d by lane swaps;
+// its holder by ballot; ids only when several lanes hold it.
 // (Carrying d, id and place through five shuffle levels took five times the
 // LDS instructions: covariances of 20k points at k = 10 70 us, 60 us now.)
 __device__ inline int group_best(double d, int32_t id) {
@@ -76,7 +96,9 @@ __device__ inline int group_best(double d, int32_t id) {
   m = fmin(m, dpp_partner<0x4E>(m));
   m = fmin(m, dpp_partner<0x141>(m));
   m = fmin(m, dpp_partner<0x140>(m));
-  m = fmin(m, __shfl_xor(m, 16, 64));
+  double a, b;
+  swap_partner<false>(m, &a, &b);
+  m = fmin(a, b);
   const int half = threadIdx.x & 32;
   uint32_t who = uint32_t(__ballot(d == m) >> half);
   if (who & (who - 1)) {

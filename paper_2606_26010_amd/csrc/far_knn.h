@@ -110,6 +110,47 @@ __device__ inline int group_best(double d, int32_t id) {
   return who ? __builtin_ctz(who) : 0;
 }
 
+// The same over the four lanes of a quad.
+__device__ inline int quad_best(double d, int32_t id) {
+  double m = fmin(d, dpp_partner<0xB1>(d));
+  m = fmin(m, dpp_partner<0x4E>(m));
+  const int quad = threadIdx.x & 60;
+  uint32_t who = uint32_t(__ballot(d == m) >> quad) & 15u;
+  if (who & (who - 1)) {
+    int32_t mi = d == m ? id : INT_MAX;
+    mi = min(mi, __builtin_amdgcn_update_dpp(0, mi, 0xB1, 0xF, 0xF, false));
+    mi = min(mi, __builtin_amdgcn_update_dpp(0, mi, 0x4E, 0xF, 0xF, false));
+    who = uint32_t(__ballot(d == m && id == mi) >> quad) & 15u;
+  }
+  return who ? __builtin_ctz(who) : 0;
+}
+
+// The K best of the sorted lists of a group's kLanes (4 or kGroup) lanes into
+// out, in every lane; entries without a place count as absent.
+template <int kLanes, int K>
+__device__ inline void merge_lists(TopK<K>& own, TopK<K>& out) {
+  const int lane = threadIdx.x & (kLanes - 1);
+#pragma unroll
+  for (int s = 0; s < K; ++s) {
+    const bool have = own.pos[0] >= 0;
+    const double d = have ? own.d[0] : __builtin_inf();
+    const int32_t id = have ? own.id[0] : INT_MAX, pos = have ? own.pos[0] : -1;
+    const int w = kLanes == 4 ? quad_best(d, id) : group_best(d, id);
+    out.d[s] = __shfl(d, w, kLanes);
+    out.id[s] = __shfl(id, w, kLanes);
+    out.pos[s] = __shfl(pos, w, kLanes);
+    if (have && lane == w) {   // the lane that held it drops it
+#pragma unroll
+      for (int q = 0; q + 1 < K; ++q) {
+        own.d[q] = own.d[q + 1];
+        own.id[q] = own.id[q + 1];
+        own.pos[q] = own.pos[q + 1];
+      }
+      own.pos[K - 1] = -1;
+    }
+  }
+}
+
 // Voxel index of a coordinate; false when outside [-2^20, 2^20).
 __device__ inline bool voxel_index(double x, double v, int64_t* k) {
   double f = floor(x / v);

@@ -486,6 +486,43 @@ __global__ __launch_bounds__(kT) void k_cert_list(int64_t n_vox, int32_t nmax,
   for (uint32_t q = 0; q < c; ++q) list[at + q] = uint32_t(V * nmax + q);
 }
 
+// The certificate of the point p at pos from its K nearest (see k_cert_build),
+// and its covariance when cov is given and its id is at least id0.
+template <int K>
+__device__ inline void cert_write(const MapView& m, uint32_t pos, const float4& p,
+                                  const TopK<K>& top, CertRow* cert, float4* cov,
+                                  float4* vox_cov, int64_t id0, int32_t k, int32_t reg) {
+  // the row straight to memory (an array of its entries, indexed by a count,
+  // would live in scratch)
+  float4* out = reinterpret_cast<float4*>(cert + pos);
+  int c = 0;
+  double next = -1.0;
+#pragma unroll
+  for (int u = 0; u < kCertK + 2; ++u) {
+    if (top.pos[u] < 0 || top.pos[u] == int32_t(pos)) continue;
+    if (c < kCertK) {
+      const float4 q = m.vox_pts[top.pos[u]];
+      out[++c] = make_float4(q.x, q.y, q.z, __int_as_float(top.pos[u]));
+    } else if (next < 0.0) {
+      next = top.d[u];
+    }
+  }
+  while (c < kCertK) out[++c] = make_float4(0.0f, 0.0f, 0.0f, __int_as_float(-1));
+  const double half = 0.5 * (next >= 0.0 ? sqrt(next) : m.v) * (1.0 - 0x1p-20);
+  out[0] = make_float4(p.x, p.y, p.z, __double2float_rd(half));
+  const int32_t id = __float_as_int(p.w);
+  if (!cov || id < id0) return;
+  double c6[6] = {0, 0, 0, 0, 0, 0};
+  const bool ok = top.found() >= k;
+  if (ok) regularised_cov<K>(top, k, [&](int32_t at) { return m.vox_pts[at]; }, c6, reg);
+  const float4 a = make_float4(float(c6[0]), float(c6[1]), float(c6[2]), float(c6[3]));
+  const float4 b = make_float4(float(c6[4]), float(c6[5]), ok ? 1.0f : 0.0f, 0.0f);
+  cov[2 * int64_t(id)] = a;
+  cov[2 * int64_t(id) + 1] = b;
+  vox_cov[2 * int64_t(pos)] = a;
+  vox_cov[2 * int64_t(pos) + 1] = b;
+}
+
 // Certificate of every listed point, one lane each: the kCertK + 1 nearest
 // other points within v by (d2, id) from the exact 27-voxel search (the point
 // itself, and so kCertK + 2 entries, included), the first kCertK listed with
@@ -526,35 +563,133 @@ __global__ __launch_bounds__(kT, kCertWaves) void k_cert_build(MapView m, const 
     (void)voxel_index(double(p.z), m.v, &kz);
     map_knn_row<K>(m, double(p.x), double(p.y), double(p.z), int32_t(kx), int32_t(ky),
                    int32_t(kz), V * m.nmax, m.vox_count[V], row, m.v * m.v, top);
-    // the row straight to memory (an array of its entries, indexed by a count,
-    // would live in scratch)
-    float4* out = reinterpret_cast<float4*>(cert + pos);
-    int c = 0;
-    double next = -1.0;
+    cert_write<K>(m, pos, p, top, cert, cov, vox_cov, id0, k, reg);
+  }
+}
+
+// The same for the short list of a small insert or map, four lanes per point:
+// one lane each would leave the chip at a wave per SIMD, as long as its chain of
+// voxels and of FP64 insertions.  First
+// the lanes share the points of the own voxel and merge their lists; then each
+// takes every fourth of the voxels that the merged K-th best can still reach
+// (the first lane on from the merged list, the others from its K-th entry
+// without a place), and the lists are merged again.  The list is the K best by
+// (d2, id) of the same candidates, so the certificates are the same.
+// Where the line lies: it pays by the points of a voxel.  In a street driven
+// along (30k to 60k listed, up to 20 points a voxel) an insert took 77 us by one
+// lane and 51 by four, the same points after an eviction 58 and 33; in a
+// sparse map (2 points a voxel) 20000 added points 16.5 and 16.7, 30000 21 and
+// 28, 64000 34 and 53.
+constexpr int64_t kCertQuadMax = 48 * 1024;
+template <int K>
+__global__ __launch_bounds__(kT, 3) void k_cert_build_quad(MapView m, const uint32_t* list,
+                                                           const uint32_t* count, CertRow* cert,
+                                                           float4* cov, float4* vox_cov,
+                                                           int64_t id0, int32_t k, int32_t reg) {
+  static_assert(K >= kCertK + 2, "a certificate needs kCertK + 2 entries");
+  constexpr int kPts = kT / 4;
+  __shared__ uint32_t rows[kPts * kRowWords];
+  __shared__ int32_t s_pos[kPts][K];
+  __shared__ double s_d[kPts][K];
+  const int lane = threadIdx.x & 3, q4 = threadIdx.x >> 2;
+  uint32_t* row = rows + q4 * kRowWords;
+  const uint32_t n = *count;
+  for (uint32_t t0 = blockIdx.x * kPts; t0 < n; t0 += gridDim.x * kPts) {
+    const uint32_t t = t0 + uint32_t(q4);
+    if (t < n) {   // (a quad as a whole)
+      const uint32_t pos = list[t];
+      const int32_t V = int32_t(pos / uint32_t(m.nmax));
+      const float4 p = m.vox_pts[pos];
+      const uint2* nb = reinterpret_cast<const uint2*>(m.vox_nbr + int64_t(V) * 26);
 #pragma unroll
-    for (int u = 0; u < kCertK + 2; ++u) {
-      if (top.pos[u] < 0 || top.pos[u] == int32_t(pos)) continue;
-      if (c < kCertK) {
-        const float4 q = m.vox_pts[top.pos[u]];
-        out[++c] = make_float4(q.x, q.y, q.z, __int_as_float(top.pos[u]));
-      } else if (next < 0.0) {
-        next = top.d[u];
+      for (int u = 0; u < 4; ++u)
+        if (lane + 4 * u < 13) {
+          const uint2 e = nb[lane + 4 * u];
+          row[2 * (lane + 4 * u)] = e.x;
+          row[2 * (lane + 4 * u) + 1] = e.y;
+        }
+      const double px = p.x, py = p.y, pz = p.z, r2 = m.v * m.v;
+      int64_t kx = 0, ky = 0, kz = 0;   // in range: held when the point was inserted
+      (void)voxel_index(px, m.v, &kx);
+      (void)voxel_index(py, m.v, &ky);
+      (void)voxel_index(pz, m.v, &kz);
+      TopK<K> own, top;
+      own.init();
+      const int32_t base = V * m.nmax, cnt = m.vox_count[V];
+      for (int32_t j = lane; j < cnt; j += 16) {
+        float4 c[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (j + 4 * u < cnt) c[u] = m.vox_pts[base + j + 4 * u];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (j + 4 * u < cnt) {
+            const double d = dist2(double(c[u].x), double(c[u].y), double(c[u].z), px, py, pz);
+            if (d <= r2) own.push(d, __float_as_int(c[u].w), base + j + 4 * u);
+          }
+      }
+      merge_lists<4>(own, top);
+      // (the row was written by this wave's lanes, in order)
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      Query q = make_query(px, py, pz, r2);
+      FaceOffsets fo;
+      fo.f[0] = float(px - double(kx) * m.v);
+      fo.f[1] = float(py - double(ky) * m.v);
+      fo.f[2] = float(pz - double(kz) * m.v);
+      fo.v = float(m.v);
+      fo.slack = float(1e-7 * m.v);
+      const double bound = fmin(r2, top.bound());
+      uint32_t need = 0;
+      {
+        const float bnd = f32_up(bound);
+#pragma unroll
+        for (int rank = 1; rank < 27; ++rank) {
+          const int code = nbr_code(rank);
+          if (row[nbr_dir(code)] != kNbrNone && fo.lb2(code) <= bnd) need |= 1u << rank;
+        }
+      }
+#pragma unroll
+      for (int s = 0; s < K; ++s) {
+        own.d[s] = lane == 0 ? top.d[s] : top.d[K - 1];
+        own.id[s] = lane == 0 ? top.id[s] : top.id[K - 1];
+        own.pos[s] = lane == 0 ? top.pos[s] : -1;
+      }
+      q.bound_f = screen_bound(bound, q.m);
+      for (int u = 0; u < lane; ++u) need &= need - 1;
+      while (need) {
+        const int code = nbr_code(__builtin_ctz(need));
+        need &= need - 1;
+        need &= need - 1;
+        need &= need - 1;
+        need &= need - 1;
+        if (double(fo.lb2(code)) > fmin(r2, own.bound())) continue;
+        const uint32_t e = row[nbr_dir(code)];
+        scan_voxel_points<K>(m.vox_pts, int32_t(e >> kNbrCountBits) * m.nmax,
+                             int32_t(e & ((1u << kNbrCountBits) - 1u)), q, r2, own);
+      }
+      merge_lists<4>(own, top);
+      if (lane == 0) {
+#pragma unroll
+        for (int s = 0; s < K; ++s) {
+          s_pos[q4][s] = top.pos[s];
+          s_d[q4][s] = top.d[s];
+        }
       }
     }
-    while (c < kCertK) out[++c] = make_float4(0.0f, 0.0f, 0.0f, __int_as_float(-1));
-    const double half = 0.5 * (next >= 0.0 ? sqrt(next) : m.v) * (1.0 - 0x1p-20);
-    out[0] = make_float4(p.x, p.y, p.z, __double2float_rd(half));
-    const int32_t id = __float_as_int(p.w);
-    if (!cov || id < id0) continue;
-    double c6[6] = {0, 0, 0, 0, 0, 0};
-    const bool ok = top.found() >= k;
-    if (ok) regularised_cov<K>(top, k, [&](int32_t at) { return m.vox_pts[at]; }, c6, reg);
-    const float4 a = make_float4(float(c6[0]), float(c6[1]), float(c6[2]), float(c6[3]));
-    const float4 b = make_float4(float(c6[4]), float(c6[5]), ok ? 1.0f : 0.0f, 0.0f);
-    cov[2 * int64_t(id)] = a;
-    cov[2 * int64_t(id) + 1] = b;
-    vox_cov[2 * int64_t(pos)] = a;
-    vox_cov[2 * int64_t(pos) + 1] = b;
+    __syncthreads();
+    // the rows and covariances by one lane per point, all in the first wave
+    if (threadIdx.x < kPts && t0 + threadIdx.x < n) {
+      TopK<K> top;
+#pragma unroll
+      for (int s = 0; s < K; ++s) {
+        top.pos[s] = s_pos[threadIdx.x][s];
+        top.d[s] = s_d[threadIdx.x][s];
+        top.id[s] = 0;
+      }
+      const uint32_t pos = list[t0 + threadIdx.x];
+      cert_write<K>(m, pos, m.vox_pts[pos], top, cert, cov, vox_cov, id0, k, reg);
+    }
+    __syncthreads();
   }
 }
 
@@ -1530,32 +1665,6 @@ __global__ __launch_bounds__(kT, kCovMinWaves) void k_grid_cov(GridView g, int32
 // are those of k_grid_cov, bit for bit.
 constexpr int64_t kWideCovMax = 32 * 1024;
 
-// The K best of the lanes' sorted lists into out, in every lane; entries
-// without a place count as absent.
-template <int K>
-__device__ inline void merge_lists(TopK<K>& own, TopK<K>& out) {
-  const int lane = threadIdx.x & (kGroup - 1);
-#pragma unroll
-  for (int s = 0; s < K; ++s) {
-    const bool have = own.pos[0] >= 0;
-    const double d = have ? own.d[0] : __builtin_inf();
-    const int32_t id = have ? own.id[0] : INT_MAX, pos = have ? own.pos[0] : -1;
-    const int w = group_best(d, id);
-    out.d[s] = __shfl(d, w, kGroup);
-    out.id[s] = __shfl(id, w, kGroup);
-    out.pos[s] = __shfl(pos, w, kGroup);
-    if (have && lane == w) {   // the lane that held it drops it
-#pragma unroll
-      for (int q = 0; q + 1 < K; ++q) {
-        own.d[q] = own.d[q + 1];
-        own.id[q] = own.id[q + 1];
-        own.pos[q] = own.pos[q + 1];
-      }
-      own.pos[K - 1] = -1;
-    }
-  }
-}
-
 template <int K>
 __global__ __launch_bounds__(kT) void k_grid_cov_wide(GridView g, int64_t n, int32_t k,
                                                       int32_t reg, float* cov6, uint8_t* valid) {
@@ -1584,7 +1693,7 @@ __global__ __launch_bounds__(kT) void k_grid_cov_wide(GridView g, int64_t n, int
       const double d = dist2(double(p.x), double(p.y), double(p.z), px, py, pz);
       if (d <= r2) own.push(d, __float_as_int(p.w), int32_t(u));
     }
-    merge_lists<K>(own, top);
+    merge_lists<kGroup>(own, top);
     // one other cell per lane, from the list's last entry on
     const double bound = fmin(r2, top.bound());
     const double slack = 1e-7 * c;
@@ -1614,7 +1723,7 @@ __global__ __launch_bounds__(kT) void k_grid_cov_wide(GridView g, int64_t n, int
     // (a ballot of the group's half of the wave)
     if ((__ballot(any) >> (threadIdx.x & 32)) & 0xFFFFFFFFull) {
       if (lane == 31) own = top;   // the first list takes part as a lane of its own
-      merge_lists<K>(own, top);
+      merge_lists<kGroup>(own, top);
     }
   }
   if (lane == 0) {
@@ -1865,15 +1974,23 @@ far_status_t certs_build(far_map_s* m, int64_t n_vox, int64_t n_pts, const uint3
   const int32_t k = m->p.k_cov;
   const uint32_t* n_cert = &counts->n_cert;
   const unsigned nb = blocks_upto(n_pts, 16);
-  if (k <= kCertK + 2)
-    k_cert_build<kCertK + 2><<<nb, kT, 0, st>>>(m->view(), list, n_cert, m->cert, cov, m->vox_cov,
-                                                id0, k, g_cov_reg);
-  else if (k <= 10)
-    k_cert_build<10><<<nb, kT, 0, st>>>(m->view(), list, n_cert, m->cert, cov, m->vox_cov, id0,
-                                        k, g_cov_reg);
+  float4* const c = k <= 10 ? cov : nullptr;
+  // (an insert lists the points around the added ones too: two to three times
+  // as many in a map that fills up)
+  const int64_t listed = mark ? 2 * n_add : n_pts;
+  auto go = [&](auto KK) {
+    constexpr int K = decltype(KK)::value;
+    if (listed <= kCertQuadMax)
+      k_cert_build_quad<K><<<blocks_upto(n_pts * 4, 32), kT, 0, st>>>(
+          m->view(), list, n_cert, m->cert, c, m->vox_cov, id0, k, g_cov_reg);
+    else
+      k_cert_build<K><<<nb, kT, 0, st>>>(m->view(), list, n_cert, m->cert, c, m->vox_cov, id0, k,
+                                         g_cov_reg);
+  };
+  if (k <= kCertK + 2 || k > 10)
+    go(std::integral_constant<int, kCertK + 2>());
   else
-    k_cert_build<kCertK + 2><<<nb, kT, 0, st>>>(m->view(), list, n_cert, m->cert, nullptr,
-                                                nullptr, id0, k, g_cov_reg);
+    go(std::integral_constant<int, 10>());
   FAR_HIP(hipGetLastError());
   if (!cov || k <= 10 || n_add <= 0) return FAR_OK;
   return dispatch_k(k, [&](auto KK) -> far_status_t {

@@ -84,3 +84,41 @@ def test_insert_refused_on_voxel_capacity_leaves_the_map(orc):
         q = synth.random_cloud(9, 500, extent=4.0)
         np.testing.assert_array_equal(host(gm.knn(dev(q), 5, 1.0)[0]), om.knn(q, 5, 1.0)[0])
     gm.close()
+
+
+@pytest.mark.parametrize("k,nmax", [(5, 2), (5, 64), (9, 20), (10, 64), (11, 20)])
+def test_certificates_by_one_lane_and_by_four(k, nmax):
+    """The same points (a crowded part, duplicates, a thin part) inserted alone
+    and with so many far ones that one lane takes a point, then with those
+    evicted: covariances and six iterations agree bit for bit."""
+    from paper_2606_26010_amd import far
+    a = synth.random_cloud(11, 3000, extent=1.5, dup_frac=0.05, on_faces=0.1)
+    b = synth.random_cloud(12, 4001, extent=12.0, dup_frac=0.01)
+    near = np.concatenate([a, b], 1)
+    g = synth.rng(13)
+    away = (g.uniform(-40.0, 40.0, (3, 60000)) + np.array([[500.0], [0.0], [0.0]])).astype(np.float32)
+    q = dev((np.concatenate([a, b[:, :2000]], 1) + g.normal(scale=0.05, size=(3, 5000))).astype(np.float32))
+    T = synth.random_offset(synth.rng(14), 0.05, 0.5)
+    cov, val = far.far_scan_covariances(q, 1.0, 5)
+    prm = far.align_params(1.0, 0.1, max_iters=6, eps=0.0)
+
+    def state(m):
+        x, c, v = m.export()
+        _, Tg, st = m.align(q, cov, val, T, prm)
+        ref = m.linearize(q, cov, val, T, 1.0, 0.1, want_corr=True)
+        return [host(t)[..., :held] for t in (x, c, v)] + [np.asarray(Tg), host(ref["corr"])]
+
+    def new(p):
+        m = far.Map(1.0, nmax, 0.0, 1 << 17, 0, k)
+        m.insert(dev(p))
+        return m
+
+    alone = new(near)
+    held = alone.export()[0].shape[1]
+    want = state(alone)
+    both = new(np.concatenate([near, away], 1))
+    for u, w in zip(want, state(both)):
+        np.testing.assert_array_equal(u, w)
+    assert both.evict([0.0, 0.0, 0.0], 100.0) > 0
+    for u, w in zip(want, state(both)):
+        np.testing.assert_array_equal(u, w)

@@ -88,3 +88,27 @@ def test_batches_bit_identical_on_both_sides_of_the_limit(room, prec):
         np.testing.assert_array_equal(a, b)
     assert list(res[0][1]["status"]) == [0, far.FAR_E_FEW_CORR, far.FAR_E_FEW_CORR,
                                          far.FAR_E_FEW_CORR, 0]
+
+
+@pytest.mark.parametrize("k", [1, 4, 5, 8, 10])
+def test_covariances_bit_identical_on_both_sides_of_the_limit(room, k):
+    """Scans around the one-block sort's size (8192 points), with a dense heap,
+    duplicates, points on cell faces and non-finite points, alone (32 lanes per
+    point, cells not sorted by x) and in a batch too large for that."""
+    far, c, gm, om = room
+    scans = [scan_of(c, n, 300 + n) for n in (1, 63, 8191, 8192, 8193)]
+    scans[2][:, :1500] = synth.rng(8).uniform(0.0, 0.9, (3, 1500))
+    scans[3][:, 100:200] = scans[3][:, :100]
+    scans[3][:, 300:500] = np.round(scans[3][:, 300:500])
+    scans[4][0, ::50] = np.nan
+    scans[4][2, 7] = np.inf
+    offs = np.concatenate([[0], np.cumsum([s.shape[1] for s in scans] + [40000])]).astype(np.int64)
+    big = np.concatenate(scans + [scan_of(c, 40000, 9)], 1)
+    n = int(offs[-2])
+    cov, val = far.far_scan_covariances_batch(dev(big), dev(offs), c.voxel_size, k)
+    few, fewv = far.far_scan_covariances_batch(dev(big[:, :n]), dev(offs[:-1]), c.voxel_size, k)
+    assert torch.equal(cov[:, :n], few) and torch.equal(val[:n], fewv)
+    for s, a in zip(scans, offs):
+        one, onev = far.far_scan_covariances(dev(s), c.voxel_size, k)
+        assert torch.equal(cov[:, a:a + s.shape[1]], one), s.shape
+        assert torch.equal(val[a:a + s.shape[1]], onev), s.shape

@@ -2,15 +2,18 @@
 // iteration (Sec. III-A.2, Eqs. (2)-(6)), for one scan or many scans per
 // launch.
 //
-// Work decomposition: every scan is cut into tiles of 256 consecutive points;
-// one 256-thread block linearises one tile (one point per thread) and writes
+// Work decomposition: every scan is cut into tiles of 256 consecutive points
+// (128 to 512); one block linearises one tile (one point per thread) and writes
 // 29 FP64 partial sums (21 upper-triangle H entries, 6 b entries, cost,
 // inlier count).  A second kernel runs one block per scan: it sums the scan's
 // tile partials in tile order (deterministic) and one lane solves the 6x6
 // system in FP64 and updates the pose.  Finished scans skip their tiles.
-// One iteration is therefore two launches whatever the number of scans; the
-// whole align (state init + max_iters iterations) is captured once into a HIP
-// graph per argument set and replayed.
+// The first iteration is therefore two launches whatever the number of scans
+// and a later one four (certify, search the rest, terms, solve); a small job
+// takes one launch an iteration (k_wide_iter), in the same order of sums.  On
+// a stream that allows capture the whole align (state init + max_iters
+// iterations) is captured into a HIP graph per repeating argument set and
+// replayed; a one-scan align launched directly stops once its scan is done.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
@@ -1574,10 +1577,13 @@ __global__ __launch_bounds__(256) void k_reduce_grad(const int32_t* begin,
 // Device workspace of the align driver, owned by the map and reused (with its
 // captured graph) while the call arguments stay the same.
 // Jobs of up to kWideMax points (at the smallest tile, over the voxels) run
-// k_wide_iter: 64 points a block are then at most two blocks a CU, which run
-// at once.  Above, one lane per point fills the chip by itself and the wide
-// search does more work than the pruned one (about 540 candidates a query).
-constexpr int64_t kWideMax = 32 * 1024;
+// k_wide_iter: 64 points a block are then at most three blocks a CU.  Above, one
+// lane per point fills the chip by itself and the wide search does more work
+// than the pruned one (about 540 candidates a query).  One scan of 16000, 32000,
+// 48000 and 64000 points, wide against the tile passes: an align of one
+// iteration 87, 98, 122 and 134 us against 112, 113, 121 and 124, of six 251, 294,
+// 373 and 419 against 446, 456, 453 and 454.
+constexpr int64_t kWideMax = 48 * 1024;
 
 struct AlignWS {
   int32_t S = 0;

@@ -91,7 +91,8 @@ struct alignas(16) Slot {
   uint64_t key;   // kEmptyKey when free
   int32_t vox;    // compact voxel index
   int32_t aux;    // map: points the voxel holds (mirror of vox_count), so one
-                  // 16-byte probe yields key, voxel and count; scan grid: scan id
+                  // 16-byte probe yields key, voxel and count; scan grid and
+                  // fine index: the run's length
 };
 
 // A slot in one memory round trip.  Read field by field (or even as one

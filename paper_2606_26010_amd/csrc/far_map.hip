@@ -537,8 +537,9 @@ __device__ inline void cert_write(const MapView& m, uint32_t pos, const float4& 
 // come from the voxel's row of the neighbour table (in LDS, read in one go)
 // instead of a hash probe each.  On average over two inserts of 500k points
 // into an emptied map: 782 us for one lane per slot with probes and 188 us for the separate
-// covariance search, now 194 us in all (300 with the row as an indexed local array and 222
-// registers); at 15k points 97 + 89 -> 87 us.
+// covariance search, now 152 us in all (300 with the row as an indexed local array and 222
+// registers; 194 with the certificate's row and the covariance written in the
+// loop, which spilled more).
 constexpr int kCertWaves = 4;   // waves per SIMD asked for (128 registers)
 
 template <int K>
@@ -569,12 +570,12 @@ __global__ __launch_bounds__(kT, kCertWaves) void k_cert_build(MapView m, const 
 
 // The same for the short list of a small insert or map, four lanes per point:
 // one lane each would leave the chip at a wave per SIMD, as long as its chain of
-// voxels and of FP64 insertions.  First
-// the lanes share the points of the own voxel and merge their lists; then each
-// takes every fourth of the voxels that the merged K-th best can still reach
-// (the first lane on from the merged list, the others from its K-th entry
-// without a place), and the lists are merged again.  The list is the K best by
-// (d2, id) of the same candidates, so the certificates are the same.
+// voxels and of FP64 insertions.  First the lanes share the points of the own
+// voxel and merge their lists; then each takes every fourth of the voxels that
+// the merged K-th best can still reach (the first lane on from the merged list,
+// the others from its K-th entry without a place), and the lists are merged
+// again.  The list is the K best by (d2, id) of the same candidates, so the
+// certificates are the same.
 // Where the line lies: it pays by the points of a voxel.  In a street driven
 // along (30k to 60k listed, up to 20 points a voxel) an insert took 77 us by one
 // lane and 51 by four, the same points after an eviction 58 and 33; in a
@@ -1654,7 +1655,7 @@ __global__ __launch_bounds__(kT, kCovMinWaves) void k_grid_cov(GridView g, int32
 }
 
 // Covariances of a small scan, 32 lanes per point.  One lane per point leaves
-// most of the chip idle below about 32k points (5000 points are 79 waves, each
+// most of the chip idle below about 30k points (5000 points are 79 waves, each
 // as long as its slowest chain of cells: 60 us; 15.3 us here; k = 5 at 20k
 // points 54 -> 34 us, k = 10 at 13k points 86 -> 45 us).  First the lanes share
 // the points of the own cell, each keeping its own K best, and the group merges
@@ -1663,7 +1664,10 @@ __global__ __launch_bounds__(kT, kCovMinWaves) void k_grid_cov(GridView g, int32
 // enter), and the group merges again.
 // The list is the K best by (d2, id) of the same candidates, so the results
 // are those of k_grid_cov, bit for bit.
-constexpr int64_t kWideCovMax = 32 * 1024;
+// The line: one scan of 16000, 24000, 32000 and 48000 points took 98, 114, 133 and
+// 164 us a call at k = 5 (125, 130, 128 and 135 by one lane per point), 123, 151,
+// 186 and 263 at k = 10 (220, 204, 207 and 205).
+constexpr int64_t kWideCovMax = 28 * 1024;
 
 template <int K>
 __global__ __launch_bounds__(kT) void k_grid_cov_wide(GridView g, int64_t n, int32_t k,

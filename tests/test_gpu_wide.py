@@ -38,7 +38,7 @@ def scan_of(c, n, seed):
 
 
 @pytest.mark.parametrize("prec", [0, 1])
-@pytest.mark.parametrize("n", [6, 63, 64, 65, 128, 129, 257, 32768, 32769])
+@pytest.mark.parametrize("n", [6, 63, 64, 65, 128, 129, 257, 32768, 32769, 49152, 49153])
 def test_align_and_gradient_around_the_limits(room, orc, n, prec):
     far, c, gm, om = room
     src = scan_of(c, n, 100 + n)
@@ -75,7 +75,7 @@ def test_batches_bit_identical_on_both_sides_of_the_limit(room, prec):
     small[2][:] = np.nan
     small.insert(1, np.zeros((3, 0), np.float32))
     res = []
-    for scans in (small, small + [scan_of(c, 40000, 9)]):
+    for scans in (small, small + [scan_of(c, 60000, 9)]):
         offs = dev(np.concatenate([[0], np.cumsum([s.shape[1] for s in scans])]).astype(np.int64))
         src = dev(np.concatenate(scans, 1))
         cov, val = far.far_scan_covariances_batch(src, offs, c.voxel_size, c.k)

@@ -622,7 +622,9 @@ far_status_t far_timing_read(double* linearize_ms, int64_t* launches, int32_t re
  * buffers, grids, partial sums) come from one stream-ordered pool per device
  * that keeps freed memory for the next call instead of returning it to the
  * driver, so repeated calls map no new memory; the pool grows to the largest
- * scratch a single call has needed.  far_scratch_release returns the unused
+ * scratch a single call has needed.  Up to eight chunks per device wait in the
+ * library for the next call of their stream, or of any once their work has
+ * ended.  far_scratch_release returns the unused
  * part of every device's pool to the driver (buffers of calls still running
  * stay); far_scratch_reserved gives the bytes the current device's pool
  * holds (0 before its first use).  Both are safe at any time. */

@@ -265,11 +265,13 @@ static __constant__ int8_t kNbrOrder[27] = {13, 4, 22, 10, 16, 12, 14, 1,  3,  5
 // A chunk of device memory for work on `stream`, from the current device's
 // stream-ordered pool (one per device, created on first use, keeping freed
 // memory for later calls), and its return after that work.  Returned chunks
-// wait in a short list per device (at most kScratchKept) for a later call: of
-// the null stream, which is never destroyed, for the next call on it; of
-// another stream with an event recorded behind their work, for a call on the
-// same stream, which waits for the event on the device, or on any stream once
-// the event has passed.  (A pool request and its return cost the host 22 us a
+// wait in a short list per device (at most kScratchKept; a full list gives its
+// oldest idle chunk back to the pool) for a later call: of the null stream, which
+// is never destroyed, for the next call on it, or on any stream while the null
+// stream is idle (an event behind each of its calls would cost up to 5 us on the
+// device); of another stream with an event recorded behind their work, for a call
+// on the same stream, which waits for the event on the device, or on any stream
+// once the event has passed.  (A pool request and its return cost the host 22 us a
 // call: undistorting one small scan 37 -> 14 us.  And a pool whose memory is
 // pending on other streams makes the host wait or maps new memory: batches of
 // 64 scans, 1.3 GB of scratch each, enqueued in turn on three streams, 30

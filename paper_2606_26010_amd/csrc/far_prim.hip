@@ -4,6 +4,7 @@
 // The insert needs a *stable* grouping of points by voxel key so that each
 // voxel's candidates are visited in input order (the sequential capped-insert
 // semantics); an LSD radix sort whose every pass is stable gives exactly that.
+#include <algorithm>
 #include <atomic>
 #include <chrono>
 #include <cstring>
@@ -453,7 +454,7 @@ struct Kept {
   void* p;
   size_t bytes;
   hipStream_t stream;
-  hipEvent_t ev;   // behind its last work; null: the null stream's
+  hipEvent_t ev;   // behind its last work; null: the null stream's (see chunk_idle)
 };
 struct Pools {
   std::mutex mu;
@@ -467,15 +468,28 @@ Pools& pools() {
 }
 }  // namespace
 
-// Whether the work behind a kept chunk's event has ended.  (Asked in relaxed
-// mode, so that a capture on another thread's stream is left alone.)
-static bool chunk_idle(const Kept& k) {
-  if (!k.ev) return false;
+// While it lives, this thread's calls are checked neither against nor by a capture
+// on any thread's stream (a query or a wait in the default mode would end such a
+// capture).
+namespace {
+struct RelaxedCapture {
   hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-  const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
-  const bool idle = hipEventQuery(k.ev) == hipSuccess;
+  bool swapped;
+  RelaxedCapture() { swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess; }
+  ~RelaxedCapture() {
+    if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  }
+  RelaxedCapture(const RelaxedCapture&) = delete;
+  RelaxedCapture& operator=(const RelaxedCapture&) = delete;
+};
+}  // namespace
+
+// Whether the work of a kept chunk has ended: the null stream's when that stream
+// is idle.
+static bool chunk_idle(const Kept& k) {
+  RelaxedCapture relaxed;
+  const bool idle = (k.ev ? hipEventQuery(k.ev) : hipStreamQuery(k.stream)) == hipSuccess;
   if (!idle) (void)hipGetLastError();   // hipErrorNotReady
-  if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
   return idle;
 }
 
@@ -486,10 +500,20 @@ static bool capturing(hipStream_t stream) {
 }
 
 void scratch_return(hipStream_t stream, size_t bytes, void* p) {
+  RelaxedCapture relaxed;
   int dev = 0;
   if (!capturing(stream) && hipGetDevice(&dev) == hipSuccess) {
     Pools& P = pools();
     std::lock_guard<std::mutex> lk(P.mu);
+    if (size_t(dev) < P.kept.size() && P.kept[dev].size() == kScratchKept) {
+      // the longest kept of the idle chunks makes room
+      auto& kept = P.kept[dev];
+      const auto old = std::find_if(kept.begin(), kept.end(), chunk_idle);
+      if (old != kept.end() && hipFreeAsync(old->p, stream) == hipSuccess) {
+        if (old->ev) P.events[dev].push_back(old->ev);
+        kept.erase(old);
+      }
+    }
     if (size_t(dev) < P.kept.size() && P.kept[dev].size() < kScratchKept) {
       Kept k{p, bytes, stream, nullptr};
       if (stream) {

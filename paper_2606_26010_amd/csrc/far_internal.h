@@ -372,9 +372,10 @@ inline size_t radix_sort_scratch_bytes(int64_t n) {
 // them and then a ticket, and the host watches the ticket.  (A copy to the
 // caller's own memory is staged by the runtime and ends in a stream wait; a
 // registration of 5000 points with two such results took 20 us more.)  The slots are one
-// allocation of kHostSlots, made at first use, handed out one per call in
-// flight under a lock, and given back by far_scratch_release while none is in
-// use; a call that finds none free copies and waits as before.
+// allocation of kHostSlots (64 KiB), made at first use, handed out one per call in
+// flight under a lock, and kept as long as the process lives: freeing pinned
+// memory waits for all work on the device (300 ms behind 300 ms of matrix
+// products).  A call that finds none free copies and waits as before.
 constexpr int kHostSlots = 64;
 constexpr size_t kSlotBytes = 1024;       // the ticket's line, then the words
 constexpr size_t kSlotData = kSlotBytes - 64;

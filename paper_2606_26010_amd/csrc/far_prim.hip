@@ -454,7 +454,7 @@ struct Kept {
   void* p;
   size_t bytes;
   hipStream_t stream;
-  hipEvent_t ev;   // behind its last work; null: the null stream's (see chunk_idle)
+  hipEvent_t ev;   // behind its last work; null: the null stream's (see Idle)
 };
 struct Pools {
   std::mutex mu;
@@ -485,13 +485,30 @@ struct RelaxedCapture {
 }  // namespace
 
 // Whether the work of a kept chunk has ended: the null stream's when that stream
-// is idle.
-static bool chunk_idle(const Kept& k) {
-  RelaxedCapture relaxed;
-  const bool idle = (k.ev ? hipEventQuery(k.ev) : hipStreamQuery(k.stream)) == hipSuccess;
-  if (!idle) (void)hipGetLastError();   // hipErrorNotReady
-  return idle;
-}
+// is idle.  (The first query after a kernel only asks the device for a mark, so
+// the null stream is asked for 30 us, about what a pool request costs; at most
+// once per object.)
+class Idle {
+  int null_ = -1;
+  static bool ended(hipError_t e) {
+    if (e != hipSuccess) (void)hipGetLastError();   // hipErrorNotReady
+    return e == hipSuccess;
+  }
+
+ public:
+  bool operator()(const Kept& k) {
+    RelaxedCapture relaxed;
+    if (k.ev) return ended(hipEventQuery(k.ev));
+    const auto t0 = std::chrono::steady_clock::now();
+    while (null_ < 0) {
+      if (ended(hipStreamQuery(nullptr)))
+        null_ = 1;
+      else if (std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(30))
+        null_ = 0;
+    }
+    return null_ == 1;
+  }
+};
 
 static bool capturing(hipStream_t stream) {
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
@@ -508,7 +525,8 @@ void scratch_return(hipStream_t stream, size_t bytes, void* p) {
     if (size_t(dev) < P.kept.size() && P.kept[dev].size() == kScratchKept) {
       // the longest kept of the idle chunks makes room
       auto& kept = P.kept[dev];
-      const auto old = std::find_if(kept.begin(), kept.end(), chunk_idle);
+      Idle idle;
+      const auto old = std::find_if(kept.begin(), kept.end(), [&](const Kept& k) { return idle(k); });
       if (old != kept.end() && hipFreeAsync(old->p, stream) == hipSuccess) {
         if (old->ev) P.events[dev].push_back(old->ev);
         kept.erase(old);
@@ -556,22 +574,23 @@ far_status_t scratch_take(hipStream_t stream, size_t bytes, size_t* got, void** 
     // the smallest chunk of this stream that holds the request, then the
     // smallest idle one; without either the largest idle one goes back
     auto& kept = P.kept[dev];
+    Idle idle;
     int best = -1, drop = -1;
-    bool best_own = false;
-    for (int i = 0; i < int(kept.size()); ++i) {
-      const Kept& k = kept[i];
-      const bool own = k.stream == stream;   // (event null exactly on the null stream)
-      if (k.bytes >= bytes) {
-        const bool better = best < 0 || (own && !best_own) ||
-                            (own == best_own && k.bytes < kept[best].bytes);
-        if (better && (own || chunk_idle(k))) {
+    auto own = [&](const Kept& k) { return k.stream == stream; };
+    for (int i = 0; i < int(kept.size()); ++i)
+      if (own(kept[i]) && kept[i].bytes >= bytes &&
+          (best < 0 || kept[i].bytes < kept[best].bytes))
+        best = i;
+    if (best < 0)
+      for (int i = 0; i < int(kept.size()); ++i)
+        if (!own(kept[i]) && kept[i].bytes >= bytes &&
+            (best < 0 || kept[i].bytes < kept[best].bytes) && idle(kept[i]))
           best = i;
-          best_own = own;
-        }
-      } else if ((drop < 0 || k.bytes > kept[drop].bytes) && (own || chunk_idle(k))) {
-        drop = i;
-      }
-    }
+    if (best < 0)
+      for (int i = 0; i < int(kept.size()); ++i)
+        if (kept[i].bytes < bytes && (drop < 0 || kept[i].bytes > kept[drop].bytes) &&
+            (own(kept[i]) || idle(kept[i])))
+          drop = i;
     const int at = best >= 0 ? best : drop;
     if (at >= 0) {
       const Kept k = kept[at];
@@ -757,35 +776,37 @@ extern "C" {
 far_status_t far_scratch_release(void) {
   far::Pools& P = far::pools();
   std::lock_guard<std::mutex> lk(P.mu);
-  // the kept chunks back to their pools first, behind the work that used them
+  // The idle kept chunks back to their pools, on a stream made for it: work on the
+  // null stream waits for other streams, and a free on it crashed the runtime
+  // while another thread captured a stream that the null stream waits for.  Only
+  // the frees are waited for.
+  far::RelaxedCapture relaxed;
   int here = 0;
   FAR_HIP(hipGetDevice(&here));
   for (size_t d = 0; d < P.kept.size(); ++d) {
-    if (P.kept[d].empty() && P.events[d].empty()) continue;
+    auto& kept = P.kept[d];
+    if (kept.empty() && P.events[d].empty()) continue;
     FAR_HIP(hipSetDevice(int(d)));
-    std::vector<far::Kept> busy;
-    for (const far::Kept& k : P.kept[d]) {
-      if (k.ev && !far::chunk_idle(k)) {   // a call still running: its chunk stays
-        busy.push_back(k);
-        continue;
-      }
-      (void)hipFreeAsync(k.p, nullptr);
-      if (k.ev) P.events[d].push_back(k.ev);
+    hipStream_t st = nullptr;
+    if (hipStreamCreateWithFlags(&st, hipStreamNonBlocking) == hipSuccess) {
+      // (a call still running, or a free that fails: its chunk stays)
+      far::Idle idle;
+      auto gone = [&](const far::Kept& k) {
+        if (!idle(k) || hipFreeAsync(k.p, st) != hipSuccess) return false;
+        if (k.ev) (void)hipEventDestroy(k.ev);
+        return true;
+      };
+      kept.erase(std::remove_if(kept.begin(), kept.end(), gone), kept.end());
+      (void)hipStreamSynchronize(st);
+      (void)hipStreamDestroy(st);
     }
-    P.kept[d].swap(busy);
     for (hipEvent_t e : P.events[d]) (void)hipEventDestroy(e);
     P.events[d].clear();
-    (void)hipStreamSynchronize(nullptr);
+    (void)hipGetLastError();
     FAR_HIP(hipSetDevice(here));
   }
   for (hipMemPool_t p : P.pool)
     if (p) FAR_HIP(hipMemPoolTrimTo(p, 0));
-  far::HostSlots& h = far::host_slots();
-  std::lock_guard<std::mutex> lk2(h.mu);
-  if (h.host && h.used == 0) {
-    FAR_HIP(hipHostFree(h.host));
-    h.host = h.dev = nullptr;
-  }
   return FAR_OK;
 }
 

@@ -1,5 +1,7 @@
 """What the kept scratch chunks hold: a chunk serves every stream once its work
-has ended."""
+has ended, and a release gives back what is idle at any time, without waiting."""
+import threading
+
 import pytest
 import torch
 
@@ -38,3 +40,46 @@ def test_a_null_stream_chunk_serves_other_streams(far):
         torch.cuda.synchronize()
         assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
         assert far.far_scratch_reserved() == held
+
+
+def test_release_does_not_wait_for_other_work(far):
+    x = cloud(5000, 2)
+    a = torch.randn(8192, 8192, device="cuda", dtype=torch.bfloat16)
+    want = cov(far, x)
+    torch.cuda.synchronize()
+    held = far.far_scratch_reserved()
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        for _ in range(300):      # about 0.25 s
+            a @ a
+    far.far_scratch_release()
+    assert not st.query()         # (the products are still running)
+    assert far.far_scratch_reserved() < held
+    torch.cuda.synchronize()
+    got = cov(far, x)
+    torch.cuda.synchronize()
+    assert torch.equal(got[0], want[0])
+
+
+@pytest.mark.parametrize("other_thread", [False, True])
+def test_release_during_a_capture(far, other_thread):
+    x, v = cloud(5000, 3), torch.arange(1000.0, device="cuda")
+    cov(far, x), cov(far, x, torch.cuda.Stream())
+    torch.cuda.synchronize()
+    held = far.far_scratch_reserved()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        y = v * 2
+        if other_thread:
+            t = threading.Thread(target=far.far_scratch_release)
+            t.start()
+            t.join()
+        else:
+            far.far_scratch_release()
+        y = y + 1
+    assert far.far_scratch_reserved() < held
+    for k in range(3):
+        v.fill_(k)
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, torch.full_like(y, 2.0 * k + 1))

@@ -621,13 +621,17 @@ far_status_t far_timing_read(double* linearize_ms, int64_t* launches, int32_t re
 /* Scratch memory.  The temporary device buffers of every call (sort
  * buffers, grids, partial sums) come from one stream-ordered pool per device
  * that keeps freed memory for the next call instead of returning it to the
- * driver, so repeated calls map no new memory; the pool grows to the largest
- * scratch a single call has needed.  Up to eight chunks per device wait in the
- * library for the next call of their stream, or of any once their work has
- * ended.  far_scratch_release returns the unused
- * part of every device's pool to the driver (buffers of calls still running
- * stay); far_scratch_reserved gives the bytes the current device's pool
- * holds (0 before its first use).  Both are safe at any time. */
+ * driver, so repeated calls map no new memory.  Up to eight chunks per device
+ * wait in the library for the next call of their stream, or of any once their
+ * work has ended.  The pool grows to the largest scratch a single call has
+ * needed where calls follow each other on one stream, and otherwise at most to
+ * the eight chunks and those of the calls in flight, each no larger than that.
+ * A call whose scratch the device cannot hold gives the unused part back and
+ * asks once more before it fails with FAR_E_HIP.  far_scratch_release returns
+ * the unused part of every device's pool to the driver (buffers of calls still
+ * running stay; it does not wait for them); far_scratch_reserved gives the bytes
+ * the current device's pool holds (0 before its first use).  Both are safe at
+ * any time. */
 far_status_t far_scratch_release(void);
 far_status_t far_scratch_reserved(int64_t* bytes /* [host] */);
 

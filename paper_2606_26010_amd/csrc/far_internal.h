@@ -271,13 +271,15 @@ static __constant__ int8_t kNbrOrder[27] = {13, 4, 22, 10, 16, 12, 14, 1,  3,  5
 // stream is idle (an event behind each of its calls would cost up to 5 us on the
 // device); of another stream with an event recorded behind their work, for a call
 // on the same stream, which waits for the event on the device, or on any stream
-// once the event has passed.  (A pool request and its return cost the host 22 us a
+// once the event has passed; another stream's only up to four times what is asked
+// for, so that small calls leave the large chunks to the large ones.  (A pool request and its return cost the host 22 us a
 // call: undistorting one small scan 37 -> 14 us.  And a pool whose memory is
 // pending on other streams makes the host wait or maps new memory: batches of
 // 64 scans, 1.3 GB of scratch each, enqueued in turn on three streams, 30
 // calls without a host wait, took 18 to 23 ms a call once the pool had begun to
 // unmap and map, with single calls of two seconds; 4.4 ms here.)  A request
-// that no kept chunk can hold gives an idle smaller one back to the pool first.
+// that no kept chunk can hold gives an idle smaller one back to the pool first, and
+// one that the pool cannot serve gives back all that are idle and is tried again.
 // far_scratch_release returns what is idle.  Streams under capture go to the
 // pool.
 constexpr size_t kScratchKept = 8;

@@ -447,8 +447,10 @@ far_status_t radix_sort_pairs(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt
 // synchronisation (release threshold 0), so each call would map its scratch
 // afresh, which costs more than many of the kernels it serves.  The library's
 // own pool keeps what it has reserved (threshold unlimited) until
-// far_scratch_release: its footprint is the largest scratch any one call
-// has needed, far below the device memory of the workloads it serves.
+// far_scratch_release or a request that the device cannot hold.  Its footprint is
+// what was out at once at most: for calls one after the other on one stream the
+// largest scratch of any of them, else at most the kept chunks (kScratchKept) and
+// those of the calls in flight, each no larger than the largest.
 namespace {
 struct Kept {
   void* p;
@@ -509,6 +511,32 @@ class Idle {
     return null_ == 1;
   }
 };
+
+// The idle kept chunks of the current device dev back to its pool, on a stream made
+// for it: work on the null stream waits for other streams, and a free on it crashed
+// the runtime while another thread captured a stream that the null stream waits
+// for.  Only the frees are waited for.  (With the pools locked.)
+static void free_idle(int dev) {
+  RelaxedCapture relaxed;
+  Pools& P = pools();
+  auto& kept = P.kept[dev];
+  hipStream_t st = nullptr;
+  if (hipStreamCreateWithFlags(&st, hipStreamNonBlocking) == hipSuccess) {
+    // (a call still running, or a free that fails: its chunk stays)
+    Idle idle;
+    auto gone = [&](const Kept& k) {
+      if (!idle(k) || hipFreeAsync(k.p, st) != hipSuccess) return false;
+      if (k.ev) (void)hipEventDestroy(k.ev);
+      return true;
+    };
+    kept.erase(std::remove_if(kept.begin(), kept.end(), gone), kept.end());
+    (void)hipStreamSynchronize(st);
+    (void)hipStreamDestroy(st);
+  }
+  for (hipEvent_t e : P.events[dev]) (void)hipEventDestroy(e);
+  P.events[dev].clear();
+  (void)hipGetLastError();
+}
 
 static bool capturing(hipStream_t stream) {
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
@@ -572,7 +600,10 @@ far_status_t scratch_take(hipStream_t stream, size_t bytes, size_t* got, void** 
   }
   if (!cap) {
     // the smallest chunk of this stream that holds the request, then the
-    // smallest idle one; without either the largest idle one goes back
+    // smallest idle one of up to four times the request (a small call on one
+    // stream would take the large chunk that another stream's next call needs, and
+    // that call would ask the pool for another); without either the largest
+    // smaller idle one goes back
     auto& kept = P.kept[dev];
     Idle idle;
     int best = -1, drop = -1;
@@ -583,7 +614,7 @@ far_status_t scratch_take(hipStream_t stream, size_t bytes, size_t* got, void** 
         best = i;
     if (best < 0)
       for (int i = 0; i < int(kept.size()); ++i)
-        if (!own(kept[i]) && kept[i].bytes >= bytes &&
+        if (!own(kept[i]) && kept[i].bytes >= bytes && kept[i].bytes / 4 <= bytes &&
             (best < 0 || kept[i].bytes < kept[best].bytes) && idle(kept[i]))
           best = i;
     if (best < 0)
@@ -630,7 +661,22 @@ far_status_t scratch_take(hipStream_t stream, size_t bytes, size_t* got, void** 
   }
   hipMemPool_t pool = P.pool[dev];
   lk.unlock();
-  FAR_HIP(hipMallocFromPoolAsync(out, bytes, pool, stream));
+  hipError_t e = hipMallocFromPoolAsync(out, bytes, pool, stream);
+  if (e != hipSuccess && !cap) {
+    // the kept chunks that are idle, and what else the pool holds unused, back to
+    // the driver first
+    (void)hipGetLastError();
+    lk.lock();
+    free_idle(dev);
+    lk.unlock();
+    (void)hipMemPoolTrimTo(pool, 0);
+    e = hipMallocFromPoolAsync(out, bytes, pool, stream);
+  }
+  if (e != hipSuccess) {
+    (void)hipGetLastError();   // (not for the next call to find)
+    *out = nullptr;
+    return hip_fail(e, "hipMallocFromPoolAsync", __FILE__, __LINE__);
+  }
   return FAR_OK;
 }
 
@@ -776,33 +822,13 @@ extern "C" {
 far_status_t far_scratch_release(void) {
   far::Pools& P = far::pools();
   std::lock_guard<std::mutex> lk(P.mu);
-  // The idle kept chunks back to their pools, on a stream made for it: work on the
-  // null stream waits for other streams, and a free on it crashed the runtime
-  // while another thread captured a stream that the null stream waits for.  Only
-  // the frees are waited for.
   far::RelaxedCapture relaxed;
   int here = 0;
   FAR_HIP(hipGetDevice(&here));
   for (size_t d = 0; d < P.kept.size(); ++d) {
-    auto& kept = P.kept[d];
-    if (kept.empty() && P.events[d].empty()) continue;
+    if (P.kept[d].empty() && P.events[d].empty()) continue;
     FAR_HIP(hipSetDevice(int(d)));
-    hipStream_t st = nullptr;
-    if (hipStreamCreateWithFlags(&st, hipStreamNonBlocking) == hipSuccess) {
-      // (a call still running, or a free that fails: its chunk stays)
-      far::Idle idle;
-      auto gone = [&](const far::Kept& k) {
-        if (!idle(k) || hipFreeAsync(k.p, st) != hipSuccess) return false;
-        if (k.ev) (void)hipEventDestroy(k.ev);
-        return true;
-      };
-      kept.erase(std::remove_if(kept.begin(), kept.end(), gone), kept.end());
-      (void)hipStreamSynchronize(st);
-      (void)hipStreamDestroy(st);
-    }
-    for (hipEvent_t e : P.events[d]) (void)hipEventDestroy(e);
-    P.events[d].clear();
-    (void)hipGetLastError();
+    far::free_idle(int(d));
     FAR_HIP(hipSetDevice(here));
   }
   for (hipMemPool_t p : P.pool)

@@ -1201,18 +1201,91 @@ __device__ inline bool voxel_index_p2(double x, double v, double inv_v, bool pow
   return true;
 }
 
+// Scan s of point i: offsets[s] <= i < offsets[s + 1].
+__device__ inline int32_t scan_of(const int64_t* offsets, int32_t S, int64_t i) {
+  int32_t lo = 0, hi = S;
+  while (hi - lo > 1) {
+    const int32_t mid = (lo + hi) >> 1;
+    if (offsets[mid] <= i) lo = mid; else hi = mid;
+  }
+  return lo;
+}
+
+// How crowded a batch's scans are, by one block: kCrowdSample of its points (drawn by a
+// hash, with repeats) are counted by (scan, cell) in a table in LDS, and out receives
+// the sum over them of the others drawn in their cell.  Times n / kCrowdSample^2 that
+// is the mean number of points in a point's own cell, up to the draw (36 of 28k
+// points a cell: within 3 %) and to cells that share a word of the table (n /
+// kCrowdCells, taken off by the caller).
+constexpr int kCrowdSample = 1024, kCrowdLog2 = 13, kCrowdCells = 1 << kCrowdLog2;
+
+__device__ inline void count_crowd(const float* xyz, int64_t n, double v, double inv_v,
+                                   int32_t pow2, const int64_t* offsets, int32_t S,
+                                   uint32_t* out) {
+  constexpr int kPer = kCrowdSample / kT;
+  constexpr uint64_t kMix = 0x9E3779B97F4A7C15ull;
+  __shared__ uint4 cnt4[kCrowdCells / 4];
+  uint32_t* cnt = reinterpret_cast<uint32_t*>(cnt4);
+  float p[kPer][3];
+  int32_t sid[kPer];
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    uint64_t x = uint64_t(u * kT + int(threadIdx.x) + 1) * kMix;
+    x = (x ^ (x >> 29)) * kMix;
+    const int64_t i = int64_t(((x >> 32) * uint64_t(n)) >> 32);   // n < 2^31
+    p[u][0] = xyz[i];
+    p[u][1] = xyz[n + i];
+    p[u][2] = xyz[2 * n + i];
+    sid[u] = offsets ? scan_of(offsets, S, i) : 0;
+  }
+#pragma unroll
+  for (int c = 0; c < kCrowdCells / 4 / kT; ++c)   // (while the loads are in flight)
+    cnt4[c * kT + threadIdx.x] = make_uint4(0u, 0u, 0u, 0u);
+  __syncthreads();
+  int32_t at[kPer];
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    int64_t kx, ky, kz;
+    at[u] = -1;
+    if (!isfinite(p[u][0]) || !isfinite(p[u][1]) || !isfinite(p[u][2]) ||
+        !voxel_index_p2(double(p[u][0]), v, inv_v, pow2, &kx) ||
+        !voxel_index_p2(double(p[u][1]), v, inv_v, pow2, &ky) ||
+        !voxel_index_p2(double(p[u][2]), v, inv_v, pow2, &kz))
+      continue;
+    at[u] = int32_t((voxel_hash(kx, ky, kz, kCrowdLog2) + uint32_t(sid[u]) * 0x9E3779B1u) &
+                    uint32_t(kCrowdCells - 1));
+    atomicAdd(&cnt[at[u]], 1u);
+  }
+  __syncthreads();
+  uint32_t others = 0;
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) others += at[u] >= 0 ? cnt[at[u]] - 1u : 0u;
+  others = block_total(others);
+  if (threadIdx.x == 0) *out = others;
+}
+
 // Key ranges of the finite points, kRangeBlocks blocks at most: out[a] the
 // minimum of axis a as 2^21 - (key + 2^20), out[3 + a] the maximum as key +
 // 2^20 + 1 (both raised from 0 by one atomic per block and axis), out[6] the
 // number of out-of-range points.  out starts as zeros.  (Per-block results
 // reduced by a second launch cost 5 us more on a scan of 100k points.)
+// kCrowd: the last block counts the crowd into out[7] instead.
+template <bool kCrowd>
 __global__ __launch_bounds__(kT) void k_key_range(const float* xyz, int64_t n, double v,
-                                                  double inv_v, int32_t pow2, uint32_t* out) {
+                                                  double inv_v, int32_t pow2,
+                                                  const int64_t* offsets, int32_t S,
+                                                  uint32_t* out) {
+  if constexpr (kCrowd) {
+    if (blockIdx.x == gridDim.x - 1) {
+      count_crowd(xyz, n, v, inv_v, pow2, offsets, S, out + 7);
+      return;
+    }
+  }
   __shared__ int32_t s_r[kT / 64][6];
   __shared__ uint32_t s_o[kT / 64];
   int32_t r[6] = {INT_MAX, INT_MAX, INT_MAX, INT_MIN, INT_MIN, INT_MIN};
   uint32_t oor = 0;
-  const int64_t step = int64_t(gridDim.x) * kT;
+  const int64_t step = int64_t(gridDim.x - (kCrowd ? 1 : 0)) * kT;
   for (int64_t i0 = int64_t(blockIdx.x) * kT + threadIdx.x; i0 < n; i0 += 4 * step) {
     float p[4][3];
 #pragma unroll
@@ -1300,15 +1373,7 @@ __global__ __launch_bounds__(kT) void k_keys_compact(const float* xyz, int64_t n
     reinterpret_cast<uint4*>(slots)[2 * i] = e;
     reinterpret_cast<uint4*>(slots)[2 * i + 1] = e;
   }
-  int32_t s = 0;
-  if (offsets) {
-    int32_t lo = 0, hi = S;            // offsets[s] <= i < offsets[s+1]
-    while (hi - lo > 1) {
-      const int32_t mid = (lo + hi) >> 1;
-      if (offsets[mid] <= i) lo = mid; else hi = mid;
-    }
-    s = lo;
-  }
+  const int32_t s = offsets ? scan_of(offsets, S, i) : 0;
   uint64_t key = uint64_t(1) << (ck.kb + ck.fb);
   const float x = xyz[i], y = xyz[n + i], z = xyz[2 * n + i];
   int64_t kx, ky, kz;
@@ -1664,10 +1729,21 @@ __global__ __launch_bounds__(kT, kCovMinWaves) void k_grid_cov(GridView g, int32
 // enter), and the group merges again.
 // The list is the K best by (d2, id) of the same candidates, so the results
 // are those of k_grid_cov, bit for bit.
-// The line: one scan of 16000, 24000, 32000 and 48000 points took 98, 114, 133 and
-// 164 us a call at k = 5 (125, 130, 128 and 135 by one lane per point), 123, 151,
-// 186 and 263 at k = 10 (220, 204, 207 and 205).
-constexpr int64_t kWideCovMax = 28 * 1024;
+// The lines.  Points: one scan of 16000, 24000, 32000 and 48000 points took 98, 114,
+// 133 and 164 us a call at k = 5 (125, 130, 128 and 135 by one lane per point), 123,
+// 151, 186 and 263 at k = 10 (220, 204, 207 and 205).  Crowd: without x order a lane
+// ranks all points of a neighbour cell, and the chip all pairs of points in a
+// cell.  On a plane, k = 5, wide against one lane per point: 2000 points with 100, 200
+// and 300 a cell 108, 132 and 163 us (128, 127 and 133); 8000 with 1000 397 (198);
+// 16000 with 20, 100 and 300 121, 158 and 249 (130, 136 and 154); 28000 with 10, 50, 300
+// and 1000 137, 165, 344 and 756 (131, 126, 158 and 211).  At k = 10 the cell may be
+// half as full again.  (crowd is the mean number of points in a point's cell, by
+// sample: 0.3 us of the range pass; scans of up to kWideCovFew points gain by the wide
+// search whatever their crowd.)
+constexpr int64_t kWideCovMax = 28 * 1024, kWideCovFew = 512;
+inline bool wide_cov_pays(int64_t n, int32_t k, double crowd) {
+  return crowd <= (k <= 5 ? 200.0 : 300.0) && crowd * double(n) <= 1.2e6;
+}
 
 template <int K>
 __global__ __launch_bounds__(kT) void k_grid_cov_wide(GridView g, int64_t n, int32_t k,
@@ -2037,11 +2113,11 @@ far_status_t links_update(far_map_s* m, int64_t n_max, int64_t vox_room, InsertC
 
 // Layout of compact keys (no x bits) for the points' range: *fits = false when
 // no point is finite (*none) or a key with the scan id needs more than 62 bits;
-// *oor receives the points whose keys leave [-2^20, 2^20).  One small copy and
-// one wait.
-static far_status_t compact_layout(const float* xyz, int64_t n, double cell, int32_t S_,
-                                   hipStream_t st, Scratch& scr, CompactKey* ck, bool* fits,
-                                   uint32_t* oor, bool* none) {
+// *oor receives the points whose keys leave [-2^20, 2^20), *crowd (if not null) the
+// mean number of points in a point's cell, by sample.  One small copy and one wait.
+static far_status_t compact_layout(const float* xyz, const int64_t* offsets, int64_t n,
+                                   double cell, int32_t S_, hipStream_t st, Scratch& scr, CompactKey* ck, bool* fits,
+                                   uint32_t* oor, bool* none, double* crowd = nullptr) {
   *fits = false;
   *oor = 0;
   if (none) *none = false;
@@ -2051,10 +2127,15 @@ static far_status_t compact_layout(const float* xyz, int64_t n, double cell, int
   int e2 = 0;
   const int32_t pow2 = std::frexp(cell, &e2) == 0.5 ? 1 : 0;
   const unsigned nb = unsigned(std::min<int64_t>(blocks_for(n, 4 * kT), kRangeBlocks));
-  k_key_range<<<nb, kT, 0, st>>>(xyz, n, cell, 1.0 / cell, pow2, rng);
+  if (crowd)
+    k_key_range<true><<<nb + 1, kT, 0, st>>>(xyz, n, cell, 1.0 / cell, pow2, offsets, S_, rng);
+  else
+    k_key_range<false><<<nb, kT, 0, st>>>(xyz, n, cell, 1.0 / cell, pow2, nullptr, 1, rng);
   FAR_HIP(hipGetLastError());
-  uint32_t h[7];
+  uint32_t h[8];
   FAR_TRY(fetch(st, h, rng, sizeof(h)));
+  if (crowd)
+    *crowd = double(n) * (double(h[7]) / (double(kCrowdSample) * kCrowdSample) - 1.0 / kCrowdCells);
   *oor = h[6];
   if (h[6] > 0) return FAR_OK;
   if (h[0] == 0) {
@@ -2232,7 +2313,7 @@ far_status_t far_map_insert(far_map_t m, const float* xyz, int64_t n, const int3
   CompactKey ck;
   bool fits = false, none = false;
   uint32_t oor = 0;
-  FAR_TRY(compact_layout(xyz, n, v, 1, st, scr, &ck, &fits, &oor, &none));
+  FAR_TRY(compact_layout(xyz, nullptr, n, v, 1, st, scr, &ck, &fits, &oor, &none));
   if (oor > 0) {
     set_error("far_map_insert: %u points have voxel keys outside [-2^20, 2^20)", oor);
     return FAR_E_INVALID;
@@ -2349,18 +2430,24 @@ far_status_t far_map_knn(far_map_t m, const float* q, int64_t n, int32_t k, doub
 // batch's key range needs more than 62 bits with the scan id, by full keys and
 // then by scan (runs not ordered by x, as without by_x); the runs, a hash of
 // them, and each run's neighbour cells.  *oor receives the points whose keys
-// leave [-2^20, 2^20) (the grid is then not built).
+// leave [-2^20, 2^20) (the grid is then not built).  *wide (given as whether the wide
+// covariances of k neighbours come into question) receives whether they are taken;
+// without by_x the grid of those has no x order.
 static far_status_t build_grid(const float* xyz, const int64_t* offsets, int32_t S_, int64_t n,
                                double v, double cell, hipStream_t st, Scratch& scr,
-                               bool by_x, GridView* out, uint32_t* oor,
+                               int32_t k, bool by_x, bool* wide, GridView* out, uint32_t* oor,
                                uint32_t* order = nullptr, float4* sorted_in = nullptr) {
   CompactKey ck{};
   bool compact = false, none = false;
   // per point: two slots (32 B), 27 cells (216), run arrays (24), keys and
   // values twice (24), sorted point (16), and the sort's tables and small words
   FAR_TRY(scr.reserve(size_t(n) * (32 + 216 + 24 + 24 + 16 + 2) + (size_t(1) << 20)));
-  FAR_TRY(compact_layout(xyz, n, cell, S_, st, scr, &ck, &compact, oor, &none));
+  double crowd = 0.0;
+  FAR_TRY(compact_layout(xyz, S_ > 1 ? offsets : nullptr, n, cell, S_, st, scr, &ck, &compact, oor, &none,
+                         *wide && n > kWideCovFew ? &crowd : nullptr));
   if (*oor > 0) return FAR_OK;
+  *wide = *wide && wide_cov_pays(n, k, crowd);
+  by_x = by_x || !*wide;
   int e2 = 0;
   const int32_t pow2 = std::frexp(cell, &e2) == 0.5 ? 1 : 0;
   const size_t nn = size_t(n);
@@ -2464,9 +2551,9 @@ static far_status_t scan_cov_impl(const float* xyz, const int64_t* offsets, int3
   // the wide search deals a cell's few points to its lanes and gains less from
   // runs in x order than their radix pass costs; an order the caller receives
   // keeps it
-  const bool wide = dense == 0 && k <= 10 && n <= kWideCovMax;
-  FAR_TRY(build_grid(xyz, offsets, S_, n, voxel_size, voxel_size, st, scr,
-                     !wide || order || packed, &g, &oor, order, reinterpret_cast<float4*>(pk)));
+  bool wide = dense == 0 && k <= 10 && n <= kWideCovMax;
+  FAR_TRY(build_grid(xyz, offsets, S_, n, voxel_size, voxel_size, st, scr, k, order || packed,
+                     &wide, &g, &oor, order, reinterpret_cast<float4*>(pk)));
   if (pk) {
     g.pk_B = reinterpret_cast<float4*>(pk + 16 * n);
     g.pk_C = reinterpret_cast<float2*>(pk + 32 * n);

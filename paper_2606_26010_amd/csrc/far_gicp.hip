@@ -1577,12 +1577,18 @@ __global__ __launch_bounds__(256) void k_reduce_grad(const int32_t* begin,
 // Device workspace of the align driver, owned by the map and reused (with its
 // captured graph) while the call arguments stay the same.
 // Jobs of up to kWideMax points (at the smallest tile, over the voxels) run
-// k_wide_iter: 64 points a block are then at most three blocks a CU.  Above, one
-// lane per point fills the chip by itself and the wide search does more work
-// than the pruned one (about 540 candidates a query).  One scan of 16000, 32000,
-// 48000 and 64000 points, wide against the tile passes: an align of one
+// k_wide_iter.  Above, one lane per point fills the chip by itself and the wide
+// search does more work than the pruned one (about 540 candidates a query).  One scan
+// of 16000, 32000, 48000 and 64000 points, wide against the tile passes: an align of one
 // iteration 87, 98, 122 and 134 us against 112, 113, 121 and 124, of six 251, 294,
 // 373 and 419 against 446, 456, 453 and 454.
+// A batch has half-filled blocks, and each scan's last block holds its 512 lanes
+// through a solve, so tiles and scans together are limited too.  Eight iterations of
+// 32, 64, 128, 160, 200, 256 and 400 scans of 700, 250, 150, 100, 50, 50 and 10 points, wide
+// against the tile passes: 268, 285, 359, 436, 414, 453 and 447 us against 371, 373, 365,
+// 384, 354, 367 and 326; 2000 of 10 points 1760 against 433.
+constexpr int64_t kWideLoad = 440;   // of tiles (an upper bound) and scans
+static_assert(kWideLoad <= kTileLdsScans, "the setup of a wide job clears its counters");
 constexpr int64_t kWideMax = 48 * 1024;
 
 struct AlignWS {
@@ -1941,8 +1947,9 @@ far_status_t enqueue(far_map_s* m, AlignWS* w, const Job& j, int64_t max_tiles, 
     }
     FAR_HIP(hipGetLastError());
   }
-  const bool wide = j.n_total <= kWideMax && j.tile == kTileMin && j.S <= kTileLdsScans &&
-                    !(j.prm.fine_nn && mv.fine_ok) && g_lin_blocks_per_cu == 0;
+  const bool wide = j.n_total <= kWideMax && max_tiles + j.S <= kWideLoad &&
+                    j.tile == kTileMin && !(j.prm.fine_nn && mv.fine_ok) &&
+                    g_lin_blocks_per_cu == 0;
   const int64_t grid = ((max_tiles + 7) / 8) * 8;   // one block per tile
   const bool fp64 = j.precision == FAR_PREC_FP64;
   if (j.gsum) {

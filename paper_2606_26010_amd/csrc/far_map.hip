@@ -234,7 +234,8 @@ struct InsertCounts {
   uint32_t n_acc;      // accepted points (the last of them may not fit)
   uint32_t n_cert;     // points whose certificates are rebuilt
   uint32_t ghosts;     // copy of the map's ghost count
-  uint32_t pad[3];
+  uint32_t leaves;     // (eviction) 1 when a point leaves
+  uint32_t pad[2];
 };
 
 // The runs of an insert, or none when its new voxels do not fit: the batch is
@@ -889,8 +890,8 @@ __global__ __launch_bounds__(kT) void k_asmd_caps(const float* xs, int64_t n,
 // rebuild.)
 
 // Keep flag of every voxel: it holds points and its centre lies within the
-// radius of c.  The kept voxels, in voxel order, go into compact keys and
-// counts.
+// radius of c; a voxel with points beyond it raises *leaves.  The kept voxels, in
+// voxel order, go into compact keys and counts.
 struct EvictVoxels {
   const uint64_t* vox_key;
   const int32_t* vox_count;
@@ -899,16 +900,18 @@ struct EvictVoxels {
   uint32_t* nvox;
   uint64_t* key_out;
   int32_t* count_out;
+  uint32_t* leaves;
   __device__ bool first(int64_t V) const {
     const uint64_t key = vox_key[V];
     const double dx = (double(key_x(key)) + 0.5) * v - cx;
     const double dy = (double(key_y(key)) + 0.5) * v - cy;
     const double dz = (double(key_z(key)) + 0.5) * v - cz;
-    const bool k = vox_count[V] > 0 && (dx * dx + dy * dy) + dz * dz <= r2;
-    vkeep[V] = k ? 1u : 0u;
-    return k;
+    const bool held = vox_count[V] > 0, in = (dx * dx + dy * dy) + dz * dz <= r2;
+    vkeep[V] = held && in ? 1u : 0u;
+    if (held && !in && *leaves == 0u) *leaves = 1u;   // (the same word by all)
+    return held && in;
   }
-  __device__ bool again(int64_t V) const { return vkeep[V] != 0; }
+  __device__ bool again(int64_t V) const { return *leaves && vkeep[V] != 0; }
   __device__ void use(int64_t V, bool flag, uint32_t pre, uint32_t) const {
     if (!flag) return;
     nvox[V] = pre;
@@ -919,7 +922,9 @@ struct EvictVoxels {
 
 // Keep flag of every map point: its voxel's.  The survivors, in id order, go
 // into compact SoA coordinates (row stride their number), covariances and new
-// slots.
+// slots.  When no point leaves, every flag is set and nothing is read or written
+// per point (a call that evicts nothing, as most of an odometry's: on 3M points in
+// 1.9M voxels 159 us with the survivors copied all the same).
 struct EvictPoints {
   const float* pt_xyz;
   const float4* cov;
@@ -931,12 +936,13 @@ struct EvictPoints {
   float* xyz_out;
   float4* cov_out;
   int32_t* loc_out;
+  const uint32_t* leaves;
   __device__ bool again(int64_t i) const {
-    return vkeep[uint32_t(pt_loc[i]) / uint32_t(nmax)] != 0;
+    return !*leaves || vkeep[uint32_t(pt_loc[i]) / uint32_t(nmax)] != 0;
   }
   __device__ bool first(int64_t i) const { return again(i); }
   __device__ void use(int64_t i, bool flag, uint32_t j, uint32_t all) const {
-    if (!flag) return;
+    if (!flag || !*leaves) return;
     xyz_out[j] = pt_xyz[i];
     xyz_out[int64_t(all) + j] = pt_xyz[point_cap + i];
     xyz_out[2 * int64_t(all) + j] = pt_xyz[2 * point_cap + i];
@@ -2881,10 +2887,11 @@ far_status_t far_map_evict(far_map_t m, const double c[3], double radius, int64_
     TimedScope ts(FAR_TIME_EVICT, st);
     FAR_HIP(hipMemsetAsync(counts, 0, sizeof(InsertCounts), st));
     FAR_TRY(scan_flags(EvictVoxels{m->vox_key, m->vox_count, v, c[0], c[1], c[2],
-                                   radius * radius, vkeep, nvox, kkey, kcount},
+                                   radius * radius, vkeep, nvox, kkey, kcount,
+                                   &counts->leaves},
                        nv, &counts->n_seg, st, scr));
     FAR_TRY(scan_flags(EvictPoints{m->pt_xyz, m->cov, m->pt_loc, m->p.point_capacity, nmax,
-                                   vkeep, nvox, xyz, cv, loc},
+                                   vkeep, nvox, xyz, cv, loc, &counts->leaves},
                        n, &counts->n_acc, st, scr));
   }
   FAR_TRY(fetch(st, &h, counts, sizeof(h)));

@@ -343,10 +343,11 @@ __global__ __launch_bounds__(256) void k_pack(const float* src, const float* cov
 }
 
 // The same packing by gather, one launch instead of two: for jobs of up to
-// kGatherPack points, where the launches count (2.4 + 4.8 us for 100k points,
-// 5.8 us); at 4.9M points the scattered reads cost more than the scattered
-// writes of k_pack (158 against 134 us).
-constexpr int64_t kGatherPack = 512 * 1024;
+// kGatherPack points.  Gathered, a scan in its sensor's order takes 3.5, 4.1 and 8.7 us
+// at 60k, 120k and 500k points (5.8, 6.7 and 11.6 in the two launches), one in random
+// order 5.6, 10.2 and 60.4 (7.0, 8.9 and 20.5: scattered reads of ten words a point
+// against scattered writes of three); the line lies where the worse order meets.
+constexpr int64_t kGatherPack = 128 * 1024;
 
 __global__ __launch_bounds__(256) void k_pack_gather(const float* src, const float* cov6,
                                                      const uint8_t* valid, int64_t n,

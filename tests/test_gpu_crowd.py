@@ -90,3 +90,39 @@ def test_scans_of_a_batch_do_not_crowd_each_other(far):
     lane = one_lane(far, lambda: us(lambda: far.far_scan_covariances_batch(x, offs, 1.0, 5)))
     print(f"20 scans of 300 points: {wide:.0f} us, one lane per point {lane:.0f} us")
     assert wide < lane
+
+
+def line(n, length):
+    """n points along x over length cells."""
+    g = synth.rng(n + length)
+    x = np.full((3, n), 0.25)
+    x[0] = g.uniform(0, length, n)
+    x[1:] += g.uniform(0, 1e-3, (2, n))
+    return torch.from_numpy(x.astype(np.float32)).cuda()
+
+
+def test_a_long_run_costs_no_more_than_short_ones(far):
+    """Points in one cell and along 600 cells, with two far ones that give the sort 15
+    bits of x below the cell: few candidates each, so about the same time."""
+    one, many = line(600000, 1), line(600000, 600)
+    one[0, :2] = many[0, :2] = torch.tensor([-2000.0, 2000.0])
+    a = us(lambda: far.far_scan_covariances(one, 1.0, 1))
+    b = us(lambda: far.far_scan_covariances(many, 1.0, 1))
+    print(f"600000 points in one cell {a:.0f} us, in 600 cells {b:.0f} us")
+    assert a <= 1.5 * b
+
+
+@pytest.mark.parametrize("n", [1023, 1024, 1025, 1026, 1027, 2560, 9999])
+def test_long_runs_against_the_oracle(far, orc, n):
+    """Runs around the length that a wave labels, from every offset of the sorted
+    order, between short ones."""
+    g = synth.rng(n)
+    x = line(n, 1).cpu().numpy()
+    for before in range(4):
+        few = (g.uniform(0, 1, (3, before)) - np.array([[3.0], [0.0], [0.0]])).astype(np.float32)
+        more = (g.uniform(0, 2, (3, 40)) + np.array([[1.0], [0.0], [0.0]])).astype(np.float32)
+        p = np.ascontiguousarray(np.concatenate([few, x, more], 1))
+        cov, val = far.far_scan_covariances(torch.from_numpy(p).cuda(), 1.0, 5)
+        oc, ov = orc.scan_covariances(p, 1.0, 5)
+        np.testing.assert_array_equal(val.cpu().numpy(), ov)
+        np.testing.assert_allclose(cov.cpu().numpy(), oc, rtol=2e-6, atol=1e-6)

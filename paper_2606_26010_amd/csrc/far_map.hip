@@ -725,12 +725,19 @@ __device__ inline int dir_code(int dir) { return dir < 13 ? dir : dir + 1; }
 //  - ghosts: the empty neighbours of a new voxel are claimed (index from
 //    gcount; beyond ghost_cap a ghost gets no row and the host switches the
 //    ghosts off), and the ghosts there before get the entry of a voxel whose
-//    count changed; new ghosts' rows are filled later.
+//    count changed; new ghosts' rows are filled later.  The table has two slots
+//    per ghost of the capacity, where chains are a few dozen slots at most; a claim
+//    that finds no place in kGhostProbes means more ghosts than that and raises
+//    gcount beyond ghost_cap.  (Unbounded, the 26 ghosts each of 20000 voxels 4 m
+//    apart, in a map of just that capacity, filled the table, and every further
+//    claim walked all of it: 3.9 s.)
 // An entry is written only by the threads of the voxel it names and of the
 // voxel whose row it is, with the same (final) value, so the writes need no
 // ordering.  As one launch per voxel these four passes took 120 us for an
 // insert of 15k points and 607 us for one of 500k (0.1M voxels); 12 and 172 us
 // in this one.
+constexpr uint32_t kGhostProbes = 1024;   // (the smallest table)
+
 __global__ __launch_bounds__(kT) void k_links(MapView m, const InsertCounts* counts,
                                               int64_t vox_room, const int32_t* seg_vox,
                                               const uint32_t* is_new, const uint32_t* seg_changed,
@@ -741,7 +748,7 @@ __global__ __launch_bounds__(kT) void k_links(MapView m, const InsertCounts* cou
   const int64_t total = insert_runs(counts, vox_room) * 26;
   for (int64_t t0 = int64_t(blockIdx.x) * kT; t0 < total; t0 += int64_t(gridDim.x) * kT) {
     const int64_t t = t0 + threadIdx.x;
-    bool won = false;
+    bool won = false, full = false;
     uint32_t h = 0;
     uint64_t nk = 0;
     if (t < total) {
@@ -771,7 +778,8 @@ __global__ __launch_bounds__(kT) void k_links(MapView m, const InsertCounts* cou
       } else if (m.ghost_ok && (fresh || changed) && key_ok(nx) && key_ok(ny) && key_ok(nz)) {
         nk = pack_key(nx, ny, nz);
         h = voxel_hash(nx, ny, nz, m.glog2);
-        for (uint32_t probe = 0; probe <= m.gmask; ++probe) {
+        full = true;
+        for (uint32_t probe = 0; probe < kGhostProbes; ++probe) {
           // (most are claimed already: look before a swap)
           unsigned long long old =
               *reinterpret_cast<const volatile unsigned long long*>(&gslots[h].key);
@@ -780,9 +788,11 @@ __global__ __launch_bounds__(kT) void k_links(MapView m, const InsertCounts* cou
                             (unsigned long long)kEmptyKey, (unsigned long long)nk);
           if (old == kEmptyKey) {
             won = fresh;
+            full = false;
             break;
           }
           if (old == nk) {
+            full = false;
             // a ghost there before; one claimed in this launch (its index not
             // yet written, or beyond those known before it) is filled later
             const int32_t g = *reinterpret_cast<const volatile int32_t*>(&gslots[h].vox);
@@ -790,12 +800,16 @@ __global__ __launch_bounds__(kT) void k_links(MapView m, const InsertCounts* cou
               const_cast<uint32_t*>(m.gnbr)[int64_t(g) * 26 + nbr_dir(26 - code)] = eV;
             break;
           }
+          if ((probe & 31u) == 31u &&
+              int64_t(*reinterpret_cast<const volatile uint32_t*>(gcount)) > ghost_cap)
+            break;   // known by now
           h = (h + 1) & m.gmask;
         }
       }
     }
     // one atomic per block on the shared count (they serialise, 6 to 7 ns each)
     const uint32_t g = block_reserve(won, gcount);
+    if (full) atomicMax(gcount, uint32_t(ghost_cap) + 1u);
     if (won) {
       gslots[h].vox = int64_t(g) < ghost_cap ? int32_t(g) : -1;
       if (int64_t(g) < ghost_cap) gkey[g] = nk;

@@ -18,7 +18,7 @@ def scan(n, voxels, in_order):
     x[0] = np.floor(g.uniform(0, voxels, n)) + 0.99 * x[0]
     if in_order:
         x = x[:, np.argsort(np.floor(x[0]), kind="stable")]
-    return x.astype(np.float32)
+    return np.ascontiguousarray(x.astype(np.float32))
 
 
 @pytest.mark.parametrize("in_order", [False, True])

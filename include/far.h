@@ -604,7 +604,10 @@ far_status_t far_odometry_destroy(far_odometry_t od);
  * far_timing_read is the linearisation kind.  Process-wide; not meant for
  * concurrent use from several threads. */
 typedef enum {
-  FAR_TIME_LINEARIZE = 0,        /* each linearisation launch of an align    */
+  FAR_TIME_LINEARIZE = 0,        /* each iteration enqueued by an align, its
+                                    solve left out; with it for a small job,
+                                    which takes one launch an iteration (a
+                                    one-scan align stops once its scan is done) */
   FAR_TIME_UNDISTORT = 1,        /* each far_undistort(_batch) call          */
   FAR_TIME_UNDISTORT_APPLY = 2,  /* its per-point kernel alone               */
   FAR_TIME_GRADIENT = 3,         /* each far_gicp_gradient call              */

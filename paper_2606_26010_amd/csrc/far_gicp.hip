@@ -1070,9 +1070,9 @@ void k_linearize(
 }
 
 // ---------------------------------------------------------------- solve
-// One 64-lane block per scan: sum the scan's tile partials in tile order,
-// then lane 0 solves H delta = -b by Cholesky (FP64) and applies
-// T <- T_c Exp(delta) T_c^-1 T.
+// One 256-lane block per scan (or the scan's last block of k_wide_iter): sum the
+// scan's tile partials in tile order, then lane 0 solves H delta = -b by Cholesky
+// (FP64) and applies T <- T_c Exp(delta) T_c^-1 T.
 __device__ void se3_apply(const double* dl, const double* c, double* T) {
   const double wx = dl[0], wy = dl[1], wz = dl[2];
   const double th2 = wx * wx + wy * wy + wz * wz;
@@ -1899,8 +1899,10 @@ far_status_t enqueue_setup(const AlignWS* w, const Job& j, int64_t max_tiles,
 // false when the scan is done, so that the iterations left are not launched
 // (each would be up to four launches of kernels that find nothing to do, about
 // 4 us of host time each).  The host stays at most kAhead iterations ahead,
-// enough to keep the device busy; it gives up watching after a millisecond and
-// enqueues what is left.
+// enough to keep the device busy.  Behind other work on the stream it watches a
+// millisecond for each iteration and then enqueues that one all the same, so
+// that the align can still stop early once the work before it has ended (the
+// call waits for its result in any case).
 constexpr uint32_t kAhead = 2;
 
 bool wait_progress(HostSlot* slot, int it) {
@@ -2041,9 +2043,10 @@ far_status_t run_job(far_map_s* m, const Job& j0, hipStream_t st, bool use_graph
         memcmp(c.key, key, sizeof(key)) == 0 && same_params(c.prm, j.prm))
       hit = &c;
   if (!hit) {
-    // Capture only once an argument set repeats (two calls apart at most):
-    // a one-off call (e.g. a different scan every time) launches directly and
-    // pays no capture.
+    // Capture only once an argument set repeats (two calls apart at most): a
+    // call on other buffers launches directly and pays no capture.  (Buffers are
+    // what is compared: the same ones with another number of points or other
+    // parameters are captured anew at each call.)
     if (memcmp(w->pending, key, sizeof(key)) != 0 && memcmp(w->pending2, key, sizeof(key)) != 0) {
       memcpy(w->pending2, w->pending, sizeof(key));
       memcpy(w->pending, key, sizeof(key));

@@ -1102,9 +1102,9 @@ __global__ __launch_bounds__(kT) void k_map_knn(MapView m, const float* q, int64
 
 // ---------------------------------------------------------------- scan grid
 // Each scan's own voxel grid is CSR: the points of all scans sorted by (scan,
-// voxel key) (sorted[j] = x, y, z, original index bits), runs [seg_start,
-// seg_end) of equal (scan, key), and a hash table from (scan, key) to run
-// index (the scan id is kept in the slot's spare word and mixed into the hash).
+// voxel key) (sorted[j] = x, y, z, original index bits), runs [run_start,
+// run_end) of equal (scan, key), and a hash table from (scan, key) to a run's
+// start and length (a scan's cells are hashed into its own stretch of slots).
 constexpr uint32_t kNoRun = 0xFFFFFFFFu;
 
 struct GridView {
@@ -1227,8 +1227,8 @@ __global__ __launch_bounds__(kT) void k_apply_perm(const uint32_t* perm, int64_t
 // range at v = 1: 8 per axis), so one radix sort of (scan, kx - min, ky - min,
 // kz - min) replaces a 63-bit sort followed by a sort by scan: the same
 // order (both are lexicographic, stable on input order), in about half the
-// passes.  The range comes from a two-level reduction (no same-address
-// atomics); points without a finite, in-range key sort last in their scan.
+// passes.  The range comes from one launch, whose blocks raise seven shared words
+// by an atomic each; points without a finite, in-range key sort last in their scan.
 constexpr int kRangeBlocks = 1024;
 
 // floor(x / v) as voxel_index computes it, through an exact multiply by 1/v

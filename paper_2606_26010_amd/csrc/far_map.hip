@@ -119,10 +119,10 @@ __global__ __launch_bounds__(kT) void k_keys(const float* xyz, int64_t n, double
 // 2^32 - 1).
 // Of the lanes of a wave with the same voxel the first, which has the smallest
 // index, claims for all, as far as that is worth a round of compares: the first
-// lane left leads those with its voxel, until it leads fewer than kDsLed.  (One
-// claim a point serialised in scans of few voxels: 1M points in one voxel 1465 us,
-// in ten 890.)
-constexpr int kDsLed = 4;
+// lane left leads those with its voxel, until it leads no other.  (One claim a point
+// serialised in scans of few voxels: 1M points in one voxel 2067 us, in ten 1024 and
+// in thirty 485, now 127, 180 and 259.  Until it leads fewer than four: 127, 291 and
+// 362; the sort took 334 to 362.)
 __global__ __launch_bounds__(kT) void k_ds_claim(const float* xyz, int64_t n, double v,
                                                  Slot* slots, uint32_t mask, int log2_slots,
                                                  uint32_t* slot_of, uint32_t* oor) {
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(kT) void k_ds_claim(const float* xyz, int64_t n, do
     const uint64_t same = __ballot(key == k);
     if (key == k) lead = src;
     rest &= ~same;
-    if (__popcll(same) < kDsLed) break;
+    if (!(same & (same - 1))) break;
   }
   uint32_t at = kNoSlot;
   if (has && lead == lane) {

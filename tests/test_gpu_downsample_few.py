@@ -53,3 +53,24 @@ def test_one_voxel_is_not_much_slower_than_many():
     one, many = us(1), us(1000)
     print(f"1000000 points in one voxel {one:.0f} us, in 1000 voxels {many:.0f} us")
     assert one <= 2.5 * many
+
+
+def test_thirty_voxels_in_random_order():
+    """Where the lanes of a wave meet by twos: no slower than a few times the scan of
+    many voxels."""
+    from paper_2606_26010_amd import far
+
+    def us(voxels):
+        x = torch.from_numpy(scan(1000000, voxels, False)).cuda()
+        ts = []
+        for _ in range(12):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            far.far_voxel_downsample(x, 1.0)
+            torch.cuda.synchronize()
+            ts.append(time.perf_counter() - t)
+        return 1e6 * statistics.median(ts[2:])
+
+    few, many = us(21), us(1000)
+    print(f"1000000 points in 21 voxels {few:.0f} us, in 1000 {many:.0f} us")
+    assert few <= 2.5 * many

@@ -1060,14 +1060,19 @@ __global__ __launch_bounds__(kT) void k_map_cov(MapView m, float4* cov, float4* 
 // Bound by the latency of each lane's chain of voxels.  The neighbours come
 // from the query's voxel's row of the neighbour table, or its ghost's (an empty
 // voxel that is neither has nothing within v), read in one go; a hash probe
-// per neighbour took 124 us for 100k queries at k = 5, 62 us now.
+// per neighbour took 124 us for 100k queries at k = 5, 62 us now.  One wave a block,
+// so that a few thousand queries spread over the chip: 4000 at k = 5 and 32 63 and 223 us
+// in blocks of four waves (87 and 326 by probes), 55 and 182 so; at k = 32, with its
+// spilled registers, 4166 queries on a thin map had become slower (127 -> 135, now 114).
+// From 30k queries on it makes no difference.
+constexpr int kKnnThreads = 64;
 template <int K>
-__global__ __launch_bounds__(kT) void k_map_knn(MapView m, const float* q, int64_t n, int32_t k,
-                                                double r2, int32_t* idx, float* d2,
-                                                int32_t* count) {
-  __shared__ uint32_t rows[kT * kRowWords];
+__global__ __launch_bounds__(kKnnThreads) void k_map_knn(MapView m, const float* q, int64_t n,
+                                                         int32_t k, double r2, int32_t* idx,
+                                                         float* d2, int32_t* count) {
+  __shared__ uint32_t rows[kKnnThreads * kRowWords];
   uint32_t* lrow = rows + threadIdx.x * kRowWords;
-  int64_t i = int64_t(blockIdx.x) * kT + threadIdx.x;
+  int64_t i = int64_t(blockIdx.x) * kKnnThreads + threadIdx.x;
   if (i >= n) return;
   float x = q[i], y = q[n + i], z = q[2 * n + i];
   TopK<K> top;
@@ -2479,7 +2484,8 @@ far_status_t far_map_knn(far_map_t m, const float* q, int64_t n, int32_t k, doub
   double r2 = radius * radius;
   return dispatch_k(k, [&](auto KK) -> far_status_t {
     constexpr int K = decltype(KK)::value;
-    k_map_knn<K><<<blocks_for(n), kT, 0, st>>>(mv, q, n, k, r2, idx, d2, count);
+    k_map_knn<K><<<blocks_for(n, kKnnThreads), kKnnThreads, 0, st>>>(mv, q, n, k, r2, idx, d2,
+                                                                     count);
     FAR_HIP(hipGetLastError());
     return FAR_OK;
   });

@@ -1,0 +1,52 @@
+"""Neighbour queries by blocks of one wave: sizes around a wave, and a few thousand
+queries hardly slower than one wave of them."""
+import statistics
+import time
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2606_26010_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("k", [1, 5, 32])
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 1000])
+def test_against_the_oracle(orc, n, k):
+    from paper_2606_26010_amd import far
+    gm = far.Map(1.0, 20, -1.0, 1 << 14, 0, 5)
+    om = orc.Map(1.0, 20, 1.0 / 20 ** 0.5, 5, point_capacity=1 << 14, voxel_capacity=1 << 14)
+    b = synth.random_cloud(3, 4000, extent=3.0, dup_frac=0.05, on_faces=0.1)
+    assert gm.insert(torch.from_numpy(b).cuda()) == om.insert(b, check=False)[:2]
+    q = synth.random_cloud(n, n, extent=4.5)
+    g = gm.knn(torch.from_numpy(q).cuda(), k, 1.0)
+    np.testing.assert_array_equal(g[0].cpu().numpy(), om.knn(q, k, 1.0)[0])
+    gm.close()
+
+
+def test_a_few_thousand_queries():
+    from paper_2606_26010_amd import far
+    g = synth.rng(4)
+    x = g.uniform(0, 200, (3, 300000))
+    x[2] = 3 * np.sin(0.1 * x[0]) + g.normal(0, 0.02, x.shape[1])
+    x = torch.from_numpy(x.astype(np.float32)).cuda()
+    m = far.Map(1.0, 20, -1.0, 1 << 19, 1 << 17, 5)
+    m.insert(x)
+
+    def us(n):
+        q = x[:, :n].contiguous()
+        ts = []
+        for _ in range(32):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            m.knn(q, 32, 1.0)
+            torch.cuda.synchronize()
+            ts.append(time.perf_counter() - t)
+        return 1e6 * statistics.median(ts[2:])
+
+    few, many = us(64), us(4096)
+    print(f"64 queries {few:.0f} us, 4096 {many:.0f} us")
+    m.close()
+    assert many <= 1.35 * few

@@ -54,3 +54,32 @@ def test_cost_and_map_of_an_eviction_of_nothing():
     assert large.stats()["n_points"] == st["n_points"] - gone
     small.close()
     large.close()
+
+
+def test_emptying_a_small_map():
+    """One launch clears the voxels and the ghosts; the map then fills as a new one."""
+    from paper_2606_26010_amd import far
+    g = synth.rng(6)
+    x = torch.from_numpy(g.uniform(0, 8, (3, 280)).astype(np.float32)).cuda()
+    m = far.Map(1.0, 5, -1.0, 1000, 1000, 5)
+    m.insert(x)
+    want = m.export()
+    all_, none = [], []
+    for _ in range(32):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        assert m.evict((4.0, 4.0, 4.0), 1e5) == 0
+        none.append(time.perf_counter() - t)
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        assert m.evict((1e5, 0.0, 0.0), 1.0) == want[0].shape[1]
+        all_.append(time.perf_counter() - t)
+        assert m.stats()["n_points"] == m.stats()["n_voxels"] == 0
+        assert int((m.knn(x, 3, 1.0)[0] >= 0).sum()) == 0
+        m.insert(x)
+        for p, q in zip(want, m.export()):
+            assert torch.equal(p, q)
+    a, b = (1e6 * statistics.median(t[2:]) for t in (all_, none))
+    print(f"280 points: all evicted {a:.0f} us, none {b:.0f} us")
+    assert a <= b + 20.0
+    m.close()
